@@ -130,6 +130,15 @@ int64_t mdp_feasible_pairs(mdpvi_mdp_t h);
  * stored values are FP32.  From a V^0 with V^0 <= T V^0 (V^0 = 0 when every
  * reject cost is 0) the iterates increase monotonically and reach an exact
  * FP32 fixed point, so any tol > 0 is met.
+ * All hosts share one capacity and one set of rates, so an iterate that is
+ * invariant under host permutations (V^0 = 0, a constant, an earlier
+ * solution) stays so.  In automatic mode (mdp_set_sweep_form) the call checks
+ * V^0 on the device and, when it is invariant, sweeps one state per orbit of
+ * the permutations and writes the result to every state: the iterates of the
+ * full sweeps, bit for bit (for values within a factor of 2^21 of each other
+ * or zero, whose sums the sweeps form exactly; beyond that two forms may
+ * round a sum differently in its last FP64 place).  Otherwise every state is
+ * swept.  st->backups and st->bytes count the full state space either way.
  * Errors: MDPVI_EINVAL (NULL, tol <= 0 or NaN, max_iter < 1), MDPVI_ENOCONV
  * (V holds V^{max_iter}), MDPVI_ENAN, MDPVI_EDEVICE, MDPVI_ENOMEM.
  * st may be NULL.                                                           */
@@ -310,8 +319,9 @@ int vi_solve_bsdi(mdpvi_mdp_t h, float *V, double tol, int64_t max_iter, int32_t
  * sweep (tiles of T = 3 digits, each lane a chunk of four consecutive
  * occupancies along digit 0; compiled for K in 5..7, C = 10, J <= 3
  * distinct sizes of at most 3 units); evaluation runs in the tile form.
- * Automatic mode uses the form mdp_autotune recorded for the shape, else
- * the row form where it applies and a sweep's working set exceeds 256 MB,
+ * Automatic mode solves a V^0 that is invariant under host permutations on
+ * its orbits (vi_solve); for any other it uses the form mdp_autotune recorded
+ * for the shape, else the row form where it applies and a sweep's working set exceeds 256 MB,
  * else the tile form, else the exact-shape direct form, else the slab form.
  * Errors: MDPVI_EINVAL (NULL handle, t >= K, a slab that does not fit 64 KB
  * of LDS, or a tile or row form that does not apply).                       */
@@ -408,8 +418,10 @@ int32_t batch_tile_form_instances(mdpvi_batch_t b, int32_t op);
  * Synchronous.  Errors: MDPVI_EINVAL, MDPVI_ENOMEM, MDPVI_EDEVICE.          */
 int batch_autotune(mdpvi_batch_t b, int32_t trials, void *hip_stream, int32_t *opt, double *us);
 
-/* The forms the next vi_solve and policy_eval on this handle run (after the
- * automatic choice): vi, eval (host, nullable).  A value in 1..K-1 is a slab
+/* The forms in which the next vi_solve and policy_eval on this handle sweep
+ * the full state space (after the automatic choice; a vi_solve from an
+ * invariant V^0 in automatic mode sweeps its orbits instead): vi, eval (host,
+ * nullable).  A value in 1..K-1 is a slab
  * depth, 0 the direct form (the exact-shape one where it applies),
  * MDPVI_FORM_TILE + w the tile form, MDPVI_FORM_ROW + w the row form of
  * value iteration.  Errors: MDPVI_EINVAL (NULL handle).                     */

@@ -232,7 +232,8 @@ class MDP:
         _check(load().mdp_set_sweep_form(self._h, int(slab_digits)))
 
     def sweep_forms(self):
-        """(value-iteration form, evaluation form) the next solves will run."""
+        """(value-iteration form, evaluation form) in which the next solves
+        sweep the full state space (mdp_sweep_forms)."""
         a, b = _c_int32(), _c_int32()
         _check(load().mdp_sweep_forms(self._h, ctypes.byref(a), ctypes.byref(b)))
         return a.value, b.value

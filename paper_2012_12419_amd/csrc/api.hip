@@ -25,13 +25,31 @@
 #include "../../include/mdpvi.h"
 #include "kernels.hpp"
 #include "model.hpp"
+#include "orbit.hpp"
 #include "tile.hpp"
 
 using mdpvi::Ctl;
 using mdpvi::Model;
 
+// Scratch of a handle's orbit form: one device block (control words, residual
+// words, rank table, orbit table, two iterates and their arrival terms) and
+// the pinned mirror of the control words.
+struct OrbitPlan {
+  int applies = -1;             // -1: not yet asked
+  mdpvi::OrbitShape S{};
+  unsigned char* dev = nullptr;
+  mdpvi::OrbitCtl* ctl = nullptr;
+  mdpvi::OrbitCtl* mirror = nullptr;
+  double* res = nullptr;
+  float* V[2] = {};
+  double* A[2] = {};
+  hipEvent_t ev0 = nullptr, ev1 = nullptr, step[2] = {};
+  hipGraphExec_t chunk = nullptr;   // kOrbitChunk sweeps
+};
+
 struct mdpvi_mdp {
   Model M;
+  OrbitPlan orbit;
   int64_t feasible_pairs = 0;
   int device = -1;              // device of the scratch below (-1: none yet)
   void* vbuf = nullptr;         // second value buffer (ping-pong partner)
@@ -383,6 +401,15 @@ int final_residual(mdpvi_mdp* h, long long j, bool sum, uint32_t grid, hipStream
   return MDPVI_OK;
 }
 
+// The per-sweep timing events (mdp_set_timing), created on first use.
+int timing_events(mdpvi_mdp* h) {
+  if (h->sweep_ev) return MDPVI_OK;
+  h->sweep_ev = new (std::nothrow) hipEvent_t[2 * kMaxChunk]();
+  if (!h->sweep_ev) return fail(MDPVI_ENOMEM, "host allocation of timing events failed");
+  for (int64_t i = 0; i < 2 * kMaxChunk; ++i) HIP_TRY(hipEventCreate(&h->sweep_ev[i]));
+  return MDPVI_OK;
+}
+
 // Enqueue sweeps j = 0, 1, ... in chunks until the device reports the test
 // met or max_iter sweeps were issued; leaves the final iterate in buf0.
 // `sweep(j, in, out)` enqueues sweep j.
@@ -393,10 +420,9 @@ int run_loop(mdpvi_mdp* h, T* buf0, double tol, int64_t max_iter, hipStream_t s,
   T* buf[2] = {buf0, static_cast<T*>(h->vbuf)};
   HIP_TRY(mdpvi::launch_ctl_init(h->ctl, h->res, s));
   HIP_TRY(hipEventRecord(h->ev0, s));
-  if (h->timing && !h->sweep_ev) {
-    h->sweep_ev = new (std::nothrow) hipEvent_t[2 * kMaxChunk]();
-    if (!h->sweep_ev) return fail(MDPVI_ENOMEM, "host allocation of timing events failed");
-    for (int64_t i = 0; i < 2 * kMaxChunk; ++i) HIP_TRY(hipEventCreate(&h->sweep_ev[i]));
+  if (h->timing) {
+    const int trc = timing_events(h);
+    if (trc) return trc;
   }
   int64_t issued = 0;
   int64_t chunk = 8;
@@ -454,6 +480,228 @@ int run_loop(mdpvi_mdp* h, T* buf0, double tol, int64_t max_iter, hipStream_t s,
   if (std::isnan(res) || std::isinf(res))
     return fail(MDPVI_ENAN, "non-finite residual after %lld sweeps", (long long)final_iter);
   if (!converged)
+    return fail(MDPVI_ENOCONV, "residual %.3e >= tol %.3e after %lld sweeps (max_iter)", res, tol,
+                (long long)final_iter);
+  return MDPVI_OK;
+}
+
+// ---------------------------------------------------------------- orbit form
+
+constexpr int kOrbitRefused = 1;     // the starting iterate is not invariant under host permutations
+constexpr int64_t kOrbitLdsSweeps = 8192;   // most sweeps of one LDS-resident launch
+
+// The shape of M's orbits; false when the form does not cover it.
+bool orbit_shape(const Model& M, mdpvi::OrbitShape* S) {
+  if (!((M.K <= 8 && M.C <= 255) || M.C <= 15)) return false;   // digits packed into 64 bits
+  if (static_cast<int64_t>(M.K) * M.R > mdpvi::kOrbitBinom) return false;
+  uint64_t n = 1;   // binom(C + K, K), exact at every step
+  for (int i = 1; i <= M.K; ++i) {
+    n = n * static_cast<uint64_t>(M.C + i) / static_cast<uint64_t>(i);
+    if (n > mdpvi::kOrbitMax) return false;
+  }
+  S->K = M.K;
+  S->C = M.C;
+  S->J = M.J;
+  S->R = M.R;
+  S->L = M.J <= 2 ? M.J : M.J <= 4 ? 4 : 8;
+  S->dig_bits = M.K <= 8 ? 8 : 4;
+  S->n = static_cast<uint32_t>(n);
+  S->wide = n >= 65535 ? 1 : 0;
+  S->n_occ = static_cast<uint64_t>(M.n_occ);
+  return true;
+}
+
+// Whether the solve fits one workgroup and is faster there than with a
+// launch per sweep.  One workgroup's sweep costs 0.5 us and then, bound by
+// its LDS reads (3K + 2 per lane), about 63 ps per lane and read: 0.66 us at
+// K = 3, C = 8, J = 2 (330 lanes), 1.6 us at K = 5, C = 6, J = 3 (1,848),
+// 6.8 us at K = 5, C = 10, J = 2 (6,006).  A launched sweep takes 3.4-3.7 us
+// up to tens of thousands of lanes, and the first solve of a handle pays for
+// recording the chunk.  The line lies where the two meet.
+bool orbit_in_lds(const mdpvi::OrbitShape& S) {
+  return !S.wide && mdpvi::orbit_lds_bytes(S) <= mdpvi::kOrbitLds &&
+         static_cast<uint64_t>(S.n) * S.L * (3 * S.K + 2) <= 56000;
+}
+
+// Whether vi_solve tries the form.  Launched sweeps need at least four times
+// fewer orbits than occupancies (K = 2 has two: its full sweep is as fast);
+// a handful of sweeps does not pay for the check and the expansion.
+bool orbit_applies(mdpvi_mdp* h, int64_t max_iter) {
+  OrbitPlan& O = h->orbit;
+  if (O.applies < 0)
+    O.applies = orbit_shape(h->M, &O.S) && (orbit_in_lds(O.S) || O.S.n_occ >= 4ull * O.S.n) ? 1 : 0;
+  return O.applies == 1 && max_iter >= 16;
+}
+
+int orbit_ensure(mdpvi_mdp* h, hipStream_t s) {
+  OrbitPlan& O = h->orbit;
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  if (h->device >= 0 && h->device != dev)
+    return fail(MDPVI_EINVAL, "handle scratch lives on device %d, current device is %d", h->device, dev);
+  if (O.dev) return MDPVI_OK;
+  const Model& M = h->M;
+  const size_t n = O.S.n, rows = static_cast<size_t>(2 + M.J) * M.K;
+  size_t at = 0;
+  auto take = [&](size_t bytes) {
+    const size_t o = at;
+    at += (bytes + 255) / 256 * 256;
+    return o;
+  };
+  const size_t o_ctl = take(sizeof(mdpvi::OrbitCtl));
+  const size_t o_res = take(static_cast<size_t>(mdpvi::kResSlots) * mdpvi::kOrbitGrid * sizeof(double));
+  const size_t o_bin = take(static_cast<size_t>(M.K) * M.R * sizeof(uint32_t));
+  const size_t o_dig = take(n * sizeof(uint64_t));
+  const size_t o_rep = take(n * sizeof(uint32_t));
+  const size_t o_tab = take(rows * n * (O.S.wide ? 4 : 2));
+  size_t o_v[2], o_a[2];
+  for (int b = 0; b < 2; ++b) o_v[b] = take(n * O.S.L * sizeof(float));
+  for (int b = 0; b < 2; ++b) o_a[b] = take((n + 1) * sizeof(double));
+  if (!O.mirror) {
+    if (hipHostMalloc(reinterpret_cast<void**>(&O.mirror), sizeof(mdpvi::OrbitCtl), hipHostMallocDefault) !=
+        hipSuccess) {
+      O.mirror = nullptr;
+      return fail(MDPVI_ENOMEM, "hipHostMalloc of the control mirror failed");
+    }
+  }
+  for (hipEvent_t* e : {&O.ev0, &O.ev1})
+    if (!*e) HIP_TRY(hipEventCreate(e));
+  for (hipEvent_t& e : O.step)
+    if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  // the rank table: binom(v + i, i + 1) = sum_{u <= v} binom(u + i - 1, i)
+  std::vector<uint32_t> binom(static_cast<size_t>(M.K) * M.R);
+  for (int i = 0; i < M.K; ++i)
+    for (int v = 0; v < M.R; ++v)
+      binom[i * M.R + v] = i == 0 ? v : (v ? binom[i * M.R + v - 1] : 0) + (v ? binom[(i - 1) * M.R + v] : 0);
+  unsigned char* d = nullptr;
+  if (hipMalloc(reinterpret_cast<void**>(&d), at) != hipSuccess)
+    return fail(MDPVI_ENOMEM, "hipMalloc of %zu orbit bytes failed", at);
+  hipError_t e = hipMemcpy(d + o_bin, binom.data(), binom.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
+  O.S.binom = reinterpret_cast<uint32_t*>(d + o_bin);
+  O.S.dig = reinterpret_cast<uint64_t*>(d + o_dig);
+  O.S.rep = reinterpret_cast<uint32_t*>(d + o_rep);
+  O.S.tab = d + o_tab;
+  if (e == hipSuccess)
+    e = mdpvi::launch_orbit_table(O.S, M, reinterpret_cast<uint64_t*>(d + o_dig), reinterpret_cast<uint32_t*>(d + o_rep),
+                                  d + o_tab, s);
+  if (e != hipSuccess) {
+    (void)hipFree(d);
+    return fail_hip(e, "orbit table");
+  }
+  O.ctl = reinterpret_cast<mdpvi::OrbitCtl*>(d + o_ctl);
+  O.res = reinterpret_cast<double*>(d + o_res);
+  for (int b = 0; b < 2; ++b) {
+    O.V[b] = reinterpret_cast<float*>(d + o_v[b]);
+    O.A[b] = reinterpret_cast<double*>(d + o_a[b]);
+  }
+  O.dev = d;
+  h->device = dev;
+  return MDPVI_OK;
+}
+
+mdpvi::OrbitParams orbit_params(const Model& M) {
+  mdpvi::OrbitParams P;
+  for (int j = 0; j < mdpvi::kMaxJ; ++j) {
+    P.p[j] = M.p[j];
+    P.r_place[j] = M.r_place[j];
+    P.r_reject[j] = M.r_reject[j];
+  }
+  P.mu_L = M.mu_L;
+  P.nu_L = M.nu_L;
+  P.hold = M.hold;
+  P.gamma = M.gamma;
+  return P;
+}
+
+// Value iteration on the orbits; kOrbitRefused (V untouched) when V is not
+// invariant under host permutations.
+int orbit_vi(mdpvi_mdp* h, float* V, double tol, int64_t max_iter, hipStream_t s, mdpvi_stats* st) {
+  int rc = orbit_ensure(h, s);
+  if (rc) return rc;
+  OrbitPlan& O = h->orbit;
+  const Model& M = h->M;
+  const mdpvi::OrbitParams P = orbit_params(M);
+  volatile mdpvi::OrbitCtl* w = O.mirror;
+  if (h->timing && (rc = timing_events(h))) return rc;
+  w->done = -1;
+  w->flag = 0;
+  HIP_TRY(hipEventRecord(O.ev0, s));
+  HIP_TRY(mdpvi::launch_orbit_begin(O.S, P, M, V, O.V[0], O.A[0], O.A[1], O.ctl, O.mirror, O.res, tol, s));
+  int64_t issued = 0;
+  double sweep_ms = 0.0;
+  if (orbit_in_lds(O.S)) {
+    while (w->done < 0 && issued < max_iter) {
+      const int64_t n = std::min(kOrbitLdsSweeps, max_iter - issued);
+      if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[0], s));
+      HIP_TRY(mdpvi::launch_orbit_lds(O.S, P, O.V[0], O.V[1], O.A[0], O.A[1], O.ctl, O.mirror, issued, n, tol, s));
+      if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[1], s));
+      issued += n;
+      HIP_TRY(mdpvi::launch_orbit_expand(O.S, M, V, O.V[0], O.V[1], O.ctl, issued, s));
+      HIP_TRY(hipEventRecord(O.ev1, s));
+      HIP_TRY(hipEventSynchronize(O.ev1));
+      if (w->flag) return kOrbitRefused;
+      if (h->timing) {
+        float ms = 0.f;
+        HIP_TRY(hipEventElapsedTime(&ms, h->sweep_ev[0], h->sweep_ev[1]));
+        sweep_ms += ms;
+      }
+    }
+  } else {
+    // chunks of sweeps, one in flight while the host waits for the other; the
+    // first tells whether the form was refused
+    if (!O.chunk && !h->timing)
+      HIP_TRY(mdpvi::build_orbit_chunk(O.S, P, O.V, O.A, O.ctl, O.mirror, O.res, &O.chunk));
+    int cur = 0;
+    while (w->done < 0 && issued < max_iter) {
+      const int n = static_cast<int>(std::min<int64_t>(mdpvi::kOrbitChunk, max_iter - issued));
+      if (n == mdpvi::kOrbitChunk && !h->timing) {
+        HIP_TRY(hipGraphLaunch(O.chunk, s));
+      } else {
+        for (int i = 0; i < n; ++i) {
+          if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[2 * i], s));
+          HIP_TRY(mdpvi::launch_orbit_sweep(O.S, P, O.V, O.A, O.ctl, O.mirror, O.res, i, s));
+          if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[2 * i + 1], s));
+        }
+        HIP_TRY(mdpvi::launch_orbit_next(O.ctl, n, s));
+      }
+      HIP_TRY(hipEventRecord(O.step[cur], s));
+      const bool first = issued == 0;
+      issued += n;
+      if (first || h->timing) {
+        HIP_TRY(hipEventSynchronize(O.step[cur]));
+        if (w->flag) return kOrbitRefused;
+        for (int i = 0; h->timing && i < n; ++i) {
+          if (w->done >= 0 && issued - n + i >= w->done) break;   // sweeps that did no work
+          float ms = 0.f;
+          HIP_TRY(hipEventElapsedTime(&ms, h->sweep_ev[2 * i], h->sweep_ev[2 * i + 1]));
+          sweep_ms += ms;
+        }
+      } else if (issued > 2 * mdpvi::kOrbitChunk) {
+        HIP_TRY(hipEventSynchronize(O.step[cur ^ 1]));
+      }
+      cur ^= 1;
+    }
+    if (w->done < 0) HIP_TRY(mdpvi::launch_orbit_last_residual(O.S, O.res, issued, O.ctl, O.mirror, s));
+    HIP_TRY(mdpvi::launch_orbit_expand(O.S, M, V, O.V[0], O.V[1], O.ctl, issued, s));
+    HIP_TRY(hipEventRecord(O.ev1, s));
+    HIP_TRY(hipEventSynchronize(O.ev1));
+  }
+  const int64_t final_iter = w->done >= 0 ? w->done : issued;
+  const double res = w->residual;
+  float ms = 0.f;
+  HIP_TRY(hipEventElapsedTime(&ms, O.ev0, O.ev1));
+  if (st) {
+    st->iterations = final_iter;
+    st->residual_inf = res;
+    st->bound_inf = M.gamma / (1.0 - M.gamma) * res;
+    st->seconds = ms * 1e-3;
+    st->backups = static_cast<double>(h->feasible_pairs) * static_cast<double>(final_iter);
+    st->bytes = 8.0 * static_cast<double>(M.n_states) * static_cast<double>(final_iter);
+    st->sweep_seconds = sweep_ms * 1e-3;
+  }
+  if (std::isnan(res) || std::isinf(res))
+    return fail(MDPVI_ENAN, "non-finite residual after %lld sweeps", (long long)final_iter);
+  if (!(res < tol))
     return fail(MDPVI_ENOCONV, "residual %.3e >= tol %.3e after %lld sweeps (max_iter)", res, tol,
                 (long long)final_iter);
   return MDPVI_OK;
@@ -755,6 +1003,11 @@ void mdp_free(mdpvi_mdp_t h) {
     for (uint32_t* o : per_t)
       if (o) (void)hipFree(o);
   if (h->out_host) (void)hipHostFree(h->out_host);
+  if (h->orbit.chunk) (void)hipGraphExecDestroy(h->orbit.chunk);
+  if (h->orbit.dev) (void)hipFree(h->orbit.dev);
+  if (h->orbit.mirror) (void)hipHostFree(h->orbit.mirror);
+  for (hipEvent_t e : {h->orbit.ev0, h->orbit.ev1, h->orbit.step[0], h->orbit.step[1]})
+    if (e) (void)hipEventDestroy(e);
   if (h->sweep_ev) {
     for (int64_t i = 0; i < 2 * kMaxChunk; ++i)
       if (h->sweep_ev[i]) (void)hipEventDestroy(h->sweep_ev[i]);
@@ -1029,9 +1282,13 @@ int vi_solve(mdpvi_mdp_t h, float* V, double tol, int64_t max_iter, void* hip_st
   if (!h || !V) return fail(MDPVI_EINVAL, "NULL handle or value array");
   if (!(tol > 0)) return fail(MDPVI_EINVAL, "tol=%g must be > 0", tol);
   if (max_iter < 1) return fail(MDPVI_EINVAL, "max_iter=%lld must be >= 1", (long long)max_iter);
+  hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  if (h->slab_t == -1 && orbit_applies(h, max_iter)) {
+    const int orc = orbit_vi(h, V, tol, max_iter, s, st);
+    if (orc != kOrbitRefused) return orc;
+  }
   int rc = ensure_scratch(h, static_cast<size_t>(h->M.n_states) * sizeof(float));
   if (rc) return rc;
-  hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const Model& M = h->M;
   mdpvi::TileShape S{};
   const int form = vi_form(h, &S);

@@ -45,6 +45,17 @@ __device__ __forceinline__ void st_f64(BufView v, double x, uint32_t lane_off, u
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U32x2, x), v.r, lane_off, uni_off, 0);
 }
 
+// The part of a backup that no action changes: releases and idling
+// S = sum_k n_k V(n - 1_k) + (KC - |n|) V(n) and host resets rs = sum_k
+// V(n^{k<-0}), weighted.  S and rs have small whole-number weights, so for
+// FP32 values they are exact in FP64 (values within a factor of 2^22 of each
+// other: 24 bits, at most 8 of weight and 21 of range) and do not depend on
+// the order of the hosts: a sweep maps an iterate that is invariant under
+// host permutations to one that is, bit for bit.
+__device__ __forceinline__ double stay_sum(const Model& M, double S, double rs) {
+  return fma(M.nu_L, rs, M.mu_L * S);
+}
+
 // Digits n_0..n_{K-1} of occupancy index o (host 0 fastest).
 template <int KMAX, typename Idx>
 __device__ __forceinline__ void decode(const Model& M, Idx o, int (&n)[KMAX]) {

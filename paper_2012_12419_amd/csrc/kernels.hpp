@@ -42,6 +42,41 @@ int slab_digits(const Model& M);
 // arrival-term arrays of n_occ doubles, the first set from the initial
 // iterate by launch_eval_arrival_init.
 struct TileShape;
+struct OrbitShape;
+struct OrbitParams;
+struct OrbitCtl;
+
+// Orbit form of value iteration (orbit.hip).  launch_orbit_table fills the
+// table behind S; launch_orbit_begin sets the control words, the orbits'
+// values Vr and arrival terms A0 from V and raises ctl->flag when V is not
+// invariant under host permutations (mirror: the control words' copy in pinned
+// host memory, written by the kernels); then either sweeps (grid orbit_grid,
+// res: kResSlots * kOrbitGrid doubles, sweep j reads V[j % 2], A[j % 2]) or
+// LDS-resident solves of up to `most` sweeps each (orbit_lds_bytes of
+// dynamic LDS); launch_orbit_expand writes the iterate of ctl->done (or of
+// `issued` sweeps) to every state of V.
+hipError_t launch_orbit_table(const OrbitShape& S, const Model& M, uint64_t* dig, uint32_t* rep, void* tab,
+                              hipStream_t s);
+hipError_t launch_orbit_begin(const OrbitShape& S, const OrbitParams& P, const Model& M, const float* V, float* Vr,
+                              double* A0, double* A1, OrbitCtl* ctl, OrbitCtl* mirror, double* res, double tol,
+                              hipStream_t s);
+uint32_t orbit_grid(const OrbitShape& S);
+// Sweep i of a chunk (i < kOrbitChunk), and the chunk's end (n sweeps);
+// build_orbit_chunk records a whole chunk as a graph.
+hipError_t launch_orbit_sweep(const OrbitShape& S, const OrbitParams& P, float* const V[2], double* const A[2],
+                              OrbitCtl* ctl, OrbitCtl* mirror, double* res, int i, hipStream_t s);
+hipError_t launch_orbit_next(OrbitCtl* ctl, int n, hipStream_t s);
+hipError_t build_orbit_chunk(const OrbitShape& S, const OrbitParams& P, float* const V[2], double* const A[2],
+                             OrbitCtl* ctl, OrbitCtl* mirror, double* res, hipGraphExec_t* out);
+hipError_t launch_orbit_last_residual(const OrbitShape& S, const double* res, long long issued, const OrbitCtl* ctl,
+                                      OrbitCtl* mirror, hipStream_t s);
+size_t orbit_lds_bytes(const OrbitShape& S);
+hipError_t launch_orbit_lds(const OrbitShape& S, const OrbitParams& P, float* V0, float* V1, double* A0, double* A1,
+                            OrbitCtl* ctl, OrbitCtl* mirror, long long it0, long long most, double tol,
+                            hipStream_t s);
+hipError_t launch_orbit_expand(const OrbitShape& S, const Model& M, float* V, const float* V0, const float* V1,
+                               const OrbitCtl* ctl, long long issued, hipStream_t s);
+
 bool vi_tile_shape(const Model& M, TileShape* S);
 hipError_t launch_vi_tile(const Model& M, const TileShape& S, const float* Vin, float* Vout, const double* Ain,
                           double* Aout, Ctl* ctl, double* res, long long j, double tol, hipStream_t s);

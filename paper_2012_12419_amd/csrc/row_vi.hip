@@ -64,7 +64,7 @@ __global__ __launch_bounds__((RowGeo<R, 4>::BLOCK), MDPVI_ROW_WAVES) void vi_row
   const uint32_t loff = static_cast<uint32_t>(r * R + c4);   // element offset in the tile
   const uint32_t lo4 = loff * 4u, lo8 = loff * 8u;
   // per-lane weights that do not depend on the tile
-  const double mu1 = M.mu_L * n1, mu2 = M.mu_L * n2;
+  const double w1 = n1, w2 = n2;
   // LDS rows of the digit-1 and digit-2 neighbours
   const int rd1 = n1 > 0 ? r - 1 : r, rr1 = r - n1;
   const int rd2 = n2 > 0 ? r - R : r, rr2 = r - n2 * R;
@@ -102,9 +102,9 @@ __global__ __launch_bounds__((RowGeo<R, 4>::BLOCK), MDPVI_ROW_WAVES) void vi_row
     __syncthreads();
     if (act) {
       const int load0 = H.load_high + n1 + n2 + c4;   // units in use at the chunk's first occupancy
-      double muh[NH > 0 ? NH : 1];
+      double wh[NH > 0 ? NH : 1];
 #pragma unroll
-      for (int h = 0; h < NH; ++h) muh[h] = M.mu_L * H.nh[h];
+      for (int h = 0; h < NH; ++h) wh[h] = H.nh[h];
       double anew[4] = {0.0, 0.0, 0.0, 0.0};
       const bool full = !tail || G::TAIL == 4;
 #if MDPVI_ROW_CLASS_UNROLL
@@ -139,9 +139,8 @@ __global__ __launch_bounds__((RowGeo<R, 4>::BLOCK), MDPVI_ROW_WAVES) void vi_row
           const double* a0 = &Al[r * G::RPA + c4 + s];   // slot n_0 + s; -inf padding past the row
 #pragma unroll
           for (int p = 0; p < 4; ++p) {
-            const double idle = M.mu_L * static_cast<double>(M.KC - (load0 + p));
-            D[p] = idle * static_cast<double>(vs[p]);
-            D[p] = fma(M.mu_L * (c4 + p), static_cast<double>(p > 0 ? vs[p - 1] : vprev), D[p]);
+            D[p] = static_cast<double>(M.KC - (load0 + p)) * static_cast<double>(vs[p]);
+            D[p] = fma(static_cast<double>(c4 + p), static_cast<double>(p > 0 ? vs[p - 1] : vprev), D[p]);
             rs[p] = 0.0 + vrow0;
             ab[p] = a0[p];
           }
@@ -156,7 +155,7 @@ __global__ __launch_bounds__((RowGeo<R, 4>::BLOCK), MDPVI_ROW_WAVES) void vi_row
           const double aa[4] = {x.x, x.y, y.x, y.y};
 #pragma unroll
           for (int p = 0; p < 4; ++p) {
-            D[p] = fma(mu1, static_cast<double>(vd[p]), D[p]);
+            D[p] = fma(w1, static_cast<double>(vd[p]), D[p]);
             rs[p] += static_cast<double>(vr[p]);
             ab[p] = max_f64(ab[p], aa[p]);
           }
@@ -171,7 +170,7 @@ __global__ __launch_bounds__((RowGeo<R, 4>::BLOCK), MDPVI_ROW_WAVES) void vi_row
           const double aa[4] = {x.x, x.y, y.x, y.y};
 #pragma unroll
           for (int p = 0; p < 4; ++p) {
-            D[p] = fma(mu2, static_cast<double>(vd[p]), D[p]);
+            D[p] = fma(w2, static_cast<double>(vd[p]), D[p]);
             rs[p] += static_cast<double>(vr[p]);
             ab[p] = max_f64(ab[p], aa[p]);
           }
@@ -181,7 +180,7 @@ __global__ __launch_bounds__((RowGeo<R, 4>::BLOCK), MDPVI_ROW_WAVES) void vi_row
         for (int h = 0; h < NH; ++h) {
 #pragma unroll
           for (int p = 0; p < 4; ++p) {
-            D[p] = fma(muh[h], static_cast<double>(gd[h][p]), D[p]);
+            D[p] = fma(wh[h], static_cast<double>(gd[h][p]), D[p]);
             rs[p] += static_cast<double>(gr[h][p]);
             ab[p] = max_f64(ab[p], ga[h][p]);
           }
@@ -195,7 +194,7 @@ __global__ __launch_bounds__((RowGeo<R, 4>::BLOCK), MDPVI_ROW_WAVES) void vi_row
         float vn[4];
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-          const double Dp = fma(M.nu_L, rs[p], D[p]);
+          const double Dp = stay_sum(M, D[p], rs[p]);
           const double fu = static_cast<double>(M.KC - (load0 + p));
           const double best = max_f64(fma(M.gamma, a_rej[p], fma(-M.hold, fu, M.r_reject[e])),
                                       fma(M.gamma, ab[p], fma(-M.hold, fu, M.r_place[e])));

@@ -159,32 +159,31 @@ __global__ __launch_bounds__(kBlock) void vi_slab_kernel(Model M, int t, uint32_
         }
       }
     }
-    const double idle = M.mu_L * static_cast<double>(M.KC - load);
+    const double fu = static_cast<double>(M.KC - load);   // free units
 #pragma unroll
     for (int e = 0; e < JMAX; ++e) {
       if (e < M.J) {
         const uint32_t gbase = o + e * nocc;
         const uint32_t lbase = ol + e * slab_occ;
         const float vse = Vl[lbase];
-        double D = idle * static_cast<double>(vse);
+        double S = fu * static_cast<double>(vse);
         double rs = 0.0;
 #pragma unroll
         for (int k = 0; k < KMAX; ++k) {
           if (k < M.K) {
             const uint32_t st = static_cast<uint32_t>(M.stride[k]);
             if (k < t) {
-              if (n[k] > 0) D = fma(M.mu_L * n[k], static_cast<double>(Vl[lbase - st]), D);
+              if (n[k] > 0) S = fma(static_cast<double>(n[k]), static_cast<double>(Vl[lbase - st]), S);
               rs += static_cast<double>(Vl[lbase - static_cast<uint32_t>(n[k]) * st]);
             } else {
-              if (n[k] > 0) D = fma(M.mu_L * n[k], static_cast<double>(Vin[gbase - st]), D);
+              if (n[k] > 0) S = fma(static_cast<double>(n[k]), static_cast<double>(Vin[gbase - st]), S);
               float v = vse;
               if (n[k] > 0) v = Vin[gbase - static_cast<uint32_t>(n[k]) * st];
               rs += static_cast<double>(v);
             }
           }
         }
-        D = fma(M.nu_L, rs, D);
-        const double fu = static_cast<double>(M.KC - load);   // free units (under-utilisation penalty)
+        const double D = stay_sum(M, S, rs);
         double best = fma(M.gamma, a_rej, fma(-M.hold, fu, M.r_reject[e]));
         const int u = M.size_idx[e];
         double ab = 0.0;

@@ -55,24 +55,23 @@ __device__ __forceinline__ double backup_occupancy(const Model& M, const float* 
     }
   }
 
-  const double idle = M.mu_L * static_cast<double>(M.KC - load);
+  const double fu = static_cast<double>(M.KC - load);   // free units
   double dmax = 0.0;
 #pragma unroll
   for (int e = 0; e < JMAX; ++e) {
     if (e < M.J) {
       const Idx base = o + e * nocc;
-      double D = idle * static_cast<double>(vs[e]);
+      double S = fu * static_cast<double>(vs[e]);
       double rs = 0.0;
 #pragma unroll
       for (int k = 0; k < KMAX; ++k) {
         if (k < M.K) {
           const Idx st = static_cast<Idx>(M.stride[k]);
-          if (n[k] > 0) D = fma(M.mu_L * n[k], static_cast<double>(Vin[base - st]), D);
+          if (n[k] > 0) S = fma(static_cast<double>(n[k]), static_cast<double>(Vin[base - st]), S);
           rs += static_cast<double>(Vin[base - static_cast<Idx>(n[k]) * st]);
         }
       }
-      D = fma(M.nu_L, rs, D);
-      const double fu = static_cast<double>(M.KC - load);   // free units (under-utilisation penalty)
+      const double D = stay_sum(M, S, rs);
       double best = fma(M.gamma, a_rej, fma(-M.hold, fu, M.r_reject[e]));
       const int u = M.size_idx[e];
       double ab = 0.0;
@@ -177,19 +176,18 @@ __device__ __forceinline__ double backup_exact(const Model& M, BufView vin, floa
       any[e] = any[e] || fa[a][e];
     }
   }
-  const double idle = M.mu_L * static_cast<double>(M.KC - load);
+  const double fu = static_cast<double>(M.KC - load);   // free units
   double dmax = 0.0;
 #pragma unroll
   for (int e = 0; e < J; ++e) {
-    double D = idle * static_cast<double>(vs[e]);
+    double S = fu * static_cast<double>(vs[e]);
     double rs = 0.0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      if (n[k] > 0) D = fma(M.mu_L * n[k], static_cast<double>(vd[k][e]), D);
+      if (n[k] > 0) S = fma(static_cast<double>(n[k]), static_cast<double>(vd[k][e]), S);
       rs += static_cast<double>(vr[k][e]);
     }
-    D = fma(M.nu_L, rs, D);
-    const double fu = static_cast<double>(M.KC - load);   // free units (under-utilisation penalty)
+    const double D = stay_sum(M, S, rs);
     double best = fma(M.gamma, a_rej, fma(-M.hold, fu, M.r_reject[e]));
     const double q = fma(M.gamma, a_best[e], fma(-M.hold, fu, M.r_place[e]));
     best = (any[e] && q > best) ? q : best;
@@ -247,7 +245,7 @@ __device__ __forceinline__ double backup_arrival(const Model& M, BufView vin, Bu
       vr[a][e] = ld_f32(vin, r4, e * cls);
     }
   }
-  const double idle = M.mu_L * static_cast<double>(M.KC - load);
+  const double fu = static_cast<double>(M.KC - load);   // free units
   double dmax = 0.0, anew = 0.0;
   bool bad = false;
 #pragma unroll
@@ -255,16 +253,15 @@ __device__ __forceinline__ double backup_arrival(const Model& M, BufView vin, Bu
     double ab = aa[0][e];
 #pragma unroll
     for (int a = 1; a < K; ++a) ab = fmax(ab, aa[a][e]);
-    double D = idle * static_cast<double>(vs[e]);
+    double S = fu * static_cast<double>(vs[e]);
     double rs = 0.0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       // a host with n_k = 0 has weight 0 (its stand-in read is the state itself)
-      D = fma(M.mu_L * n[k], static_cast<double>(vd[k][e]), D);
+      S = fma(static_cast<double>(n[k]), static_cast<double>(vd[k][e]), S);
       rs += static_cast<double>(vr[k][e]);
     }
-    D = fma(M.nu_L, rs, D);
-    const double fu = static_cast<double>(M.KC - load);   // free units (under-utilisation penalty)
+    const double D = stay_sum(M, S, rs);
     const double best = fmax(fma(M.gamma, a_rej, fma(-M.hold, fu, M.r_reject[e])), fma(M.gamma, ab, fma(-M.hold, fu, M.r_place[e])));
     const float vn = static_cast<float>(fma(M.gamma, D, best));
     Vout[o + e * nocc] = vn;

@@ -82,22 +82,21 @@ __device__ __forceinline__ void tile_backup(const Model& M, const TileHigh<K, J,
       }
     }
   }
-  const double idle = M.mu_L * static_cast<double>(M.KC - load);
+  const double fu = static_cast<double>(M.KC - load);   // free units
   anew = 0.0;
 #pragma unroll
   for (int e = 0; e < J; ++e) {
     double ab = aa[0][e];
 #pragma unroll
     for (int a = 1; a < K; ++a) ab = fmax(ab, aa[a][e]);
-    double D = idle * static_cast<double>(vs[e]);
+    double S = fu * static_cast<double>(vs[e]);
     double rs = 0.0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      D = fma(M.mu_L * n[k], static_cast<double>(vd[k][e]), D);
+      S = fma(static_cast<double>(n[k]), static_cast<double>(vd[k][e]), S);
       rs += static_cast<double>(vr[k][e]);
     }
-    D = fma(M.nu_L, rs, D);
-    const double fu = static_cast<double>(M.KC - load);   // free units (under-utilisation penalty)
+    const double D = stay_sum(M, S, rs);
     const double best = fmax(fma(M.gamma, a_rej, fma(-M.hold, fu, M.r_reject[e])), fma(M.gamma, ab, fma(-M.hold, fu, M.r_place[e])));
     vn[e] = static_cast<float>(fma(M.gamma, D, best));
     anew = fma(M.p[e], static_cast<double>(vn[e]), anew);
