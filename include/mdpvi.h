@@ -183,6 +183,12 @@ int policy_extract_f64(mdpvi_mdp_t h, const double *V, uint8_t *pi, float *gap,
  * pi: device uint8[N], every entry a feasible action (checked: an infeasible
  * placement makes the call fail with MDPVI_EINVAL before any sweep);
  * V: device double[N], in: V^0 (warm start), out: V_pi to ||dV||_inf < tol.
+ * A policy whose target load (the occupancy of the host it places on, or
+ * none) is the same in all states that differ by a host permutation, such as
+ * the least-loaded heuristic, has an invariant value.  When V^0 is invariant
+ * too, to within tol/2, the sweeps run on one state per orbit, from its
+ * representative's V^0, in every sweep form (mdp_set_orbits); the result
+ * differs from that of the full sweeps in the rounding of FP64 sums.
  * Errors as vi_solve.                                                       */
 int policy_eval(mdpvi_mdp_t h, const uint8_t *pi, double *V, double tol,
                 int64_t max_iter, void *hip_stream, mdpvi_stats *st);
@@ -385,6 +391,13 @@ int batch_set_round_form(mdpvi_batch_t b, int32_t op, int32_t opt);
  * evaluation and adjoint calls on this batch use.  Errors: MDPVI_EINVAL.   */
 int batch_round_forms(mdpvi_batch_t b, int32_t *opt);
 
+/* Whether the batch's instances may be solved on the orbits of the host
+ * permutations: 1 (the default) where an instance's start, and policy, are
+ * invariant (vi_solve_batch with automatic round and tile forms,
+ * policy_eval_batch and the evaluations of policy_iteration_batch; as
+ * mdp_set_orbits, per instance); 0 never.  Errors: MDPVI_EINVAL (NULL).     */
+int batch_set_orbits(mdpvi_batch_t b, int32_t on);
+
 /* Tile form of the round kernels of operation op (0 value iteration, 1 FP64
  * evaluation) for the batch's instances of 4 or 5 hosts and up to 3 classes
  * of distinct sizes (a tuning knob: the same bits either way).  Each
@@ -458,6 +471,13 @@ int mdp_autotune(mdpvi_mdp_t h, const float *V, int32_t trials, void *hip_stream
  * exact-shape kernels with one occupancy per thread below 2^21 occupancies
  * and four above, else the generic ones; -1 for a NULL handle.             */
 int32_t mdp_adjoint_form(mdpvi_mdp_t h);
+
+/* Whether solves of this handle may run on the orbits of the host
+ * permutations (vi_solve in automatic mode, policy_eval and the evaluations of
+ * policy_iteration): 1 (the default) where the start, and the policy, are
+ * invariant; 0 never (a measurement aid: every state is then swept).
+ * Errors: MDPVI_EINVAL (NULL handle).                                       */
+int mdp_set_orbits(mdpvi_mdp_t h, int32_t on);
 
 /* Choice of the adjoint sweep kernels for this handle (a tuning knob: every
  * form gives bit-identical w and gradients).  0: automatic (the default);

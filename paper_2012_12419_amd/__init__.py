@@ -100,11 +100,13 @@ SIGNATURES = {
     "batch_set_round_form": (ctypes.c_int, [_vp, _c_int32, _c_int32]),
     "batch_round_forms": (ctypes.c_int, [_vp, ctypes.POINTER(_c_int32)]),
     "batch_set_tile_form": (ctypes.c_int, [_vp, _c_int32, _c_int32]),
+    "batch_set_orbits": (ctypes.c_int, [_vp, _c_int32]),
     "batch_tile_form_instances": (_c_int32, [_vp, _c_int32]),
     "batch_autotune": (ctypes.c_int, [_vp, _c_int32, _vp, ctypes.POINTER(_c_int32),
                                       ctypes.POINTER(_c_double)]),
     "mdp_set_timing": (ctypes.c_int, [_vp, _c_int32]),
     "mdp_set_sweep_form": (ctypes.c_int, [_vp, _c_int32]),
+    "mdp_set_orbits": (ctypes.c_int, [_vp, _c_int32]),
     "vi_solve_bsdi": (ctypes.c_int, [_vp, _vp, _c_double, _c_int64, _c_int32, _vp, ctypes.POINTER(Stats)]),
     "policy_iteration": (ctypes.c_int, [_vp, _vp, _vp, _c_double, _c_int64, _c_double, _c_int64, _vp,
                                         ctypes.POINTER(Stats), ctypes.POINTER(_c_int64)]),
@@ -230,6 +232,11 @@ class MDP:
         """-1 automatic, 0 direct, t in 1..K-1 LDS slab of t low digits,
         FORM_TILE the tile form (value iteration and evaluation)."""
         _check(load().mdp_set_sweep_form(self._h, int(slab_digits)))
+
+    def set_orbits(self, on: bool = True):
+        """Whether solves may run on the orbits of the host permutations
+        (mdp_set_orbits); off: every state is swept."""
+        _check(load().mdp_set_orbits(self._h, 1 if on else 0))
 
     def sweep_forms(self):
         """(value-iteration form, evaluation form) in which the next solves
@@ -420,6 +427,11 @@ class Batch:
         """Tile form of the round kernels of op ("vi" or "eval") for the
         instances it covers: 1 on, 0 off, -1 automatic."""
         _check(load().batch_set_tile_form(self._h, self.ROUND_OPS[op], int(mode)))
+
+    def set_orbits(self, on: bool = True):
+        """Whether instances may be solved on the orbits of the host
+        permutations (batch_set_orbits); off: every state is swept."""
+        _check(load().batch_set_orbits(self._h, 1 if on else 0))
 
     def tile_form_instances(self, op: str) -> int:
         """Instances the next call of op ("vi" or "eval") runs in the tile form."""

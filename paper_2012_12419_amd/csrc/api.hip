@@ -31,20 +31,18 @@
 using mdpvi::Ctl;
 using mdpvi::Model;
 
-// Scratch of a handle's orbit form: one device block (control words, residual
+// Scratch of a handle's orbit form: one device block (control and residual
 // words, rank table, orbit table, two iterates and their arrival terms) and
 // the pinned mirror of the control words.
 struct OrbitPlan {
-  int applies = -1;             // -1: not yet asked
+  int covered = -1;             // -1: not yet asked
   mdpvi::OrbitShape S{};
+  mdpvi::OrbitParams P{};
+  mdpvi::OrbitWork W{};
   unsigned char* dev = nullptr;
-  mdpvi::OrbitCtl* ctl = nullptr;
   mdpvi::OrbitCtl* mirror = nullptr;
-  double* res = nullptr;
-  float* V[2] = {};
-  double* A[2] = {};
   hipEvent_t ev0 = nullptr, ev1 = nullptr, step[2] = {};
-  hipGraphExec_t chunk = nullptr;   // kOrbitChunk sweeps
+  hipGraphExec_t chunk[2] = {};   // kOrbitChunk sweeps of value iteration, of evaluation
 };
 
 struct mdpvi_mdp {
@@ -68,6 +66,7 @@ struct mdpvi_mdp {
   double* out_host = nullptr;   // pinned, 2 * kMaxJ + 3 doubles
   bool timing = false;          // bracket every sweep with events
   int adjoint_form = 0;         // adjoint sweep form: 0 automatic, else a valid form
+  bool orbits = true;           // solve invariant problems on their orbits
   int slab_t = -1;              // sweep form: -1 automatic, 0 direct, t > 0 slab of t digits,
                                 // MDPVI_FORM_TILE the tile form
   hipEvent_t* sweep_ev = nullptr;   // 2 * kMaxChunk events (created on demand)
@@ -487,7 +486,9 @@ int run_loop(mdpvi_mdp* h, T* buf0, double tol, int64_t max_iter, hipStream_t s,
 
 // ---------------------------------------------------------------- orbit form
 
-constexpr int kOrbitRefused = 1;     // the starting iterate is not invariant under host permutations
+constexpr int kOrbitRefused = 1;      // the start or the policy is not invariant under host permutations
+constexpr int kOrbitInfeasible = 2;   // the policy has an infeasible action
+constexpr char kInfeasiblePolicy[] = "policy has an action that is not feasible in its state";
 constexpr int64_t kOrbitLdsSweeps = 8192;   // most sweeps of one LDS-resident launch
 
 // The shape of M's orbits; false when the form does not cover it.
@@ -508,29 +509,57 @@ bool orbit_shape(const Model& M, mdpvi::OrbitShape* S) {
   S->n = static_cast<uint32_t>(n);
   S->wide = n >= 65535 ? 1 : 0;
   S->n_occ = static_cast<uint64_t>(M.n_occ);
+  S->divR = M.divR;
   return true;
+}
+
+mdpvi::OrbitParams orbit_params(const Model& M) {
+  mdpvi::OrbitParams P;
+  for (int j = 0; j < mdpvi::kMaxJ; ++j) {
+    P.p[j] = M.p[j];
+    P.r_place[j] = M.r_place[j];
+    P.r_reject[j] = M.r_reject[j];
+    P.size[j] = M.size[j];
+  }
+  P.mu_L = M.mu_L;
+  P.nu_L = M.nu_L;
+  P.hold = M.hold;
+  P.gamma = M.gamma;
+  return P;
+}
+
+// The rank table: binom(v + i, i + 1) = sum_{u <= v} binom(u + i - 1, i).
+std::vector<uint32_t> orbit_binom(const mdpvi::OrbitShape& S) {
+  std::vector<uint32_t> b(static_cast<size_t>(S.K) * S.R);
+  for (int i = 0; i < S.K; ++i)
+    for (int v = 0; v < S.R; ++v)
+      b[i * S.R + v] = i == 0 ? v : v == 0 ? 0 : b[i * S.R + v - 1] + b[(i - 1) * S.R + v];
+  return b;
 }
 
 // Whether the solve fits one workgroup and is faster there than with a
 // launch per sweep.  One workgroup's sweep costs 0.5 us and then, bound by
-// its LDS reads (3K + 2 per lane), about 63 ps per lane and read: 0.66 us at
-// K = 3, C = 8, J = 2 (330 lanes), 1.6 us at K = 5, C = 6, J = 3 (1,848),
-// 6.8 us at K = 5, C = 10, J = 2 (6,006).  A launched sweep takes 3.4-3.7 us
-// up to tens of thousands of lanes, and the first solve of a handle pays for
-// recording the chunk.  The line lies where the two meet.
+// its LDS reads, about 63 ps per lane and 4-byte read (value iteration: 3K +
+// 2): 0.66 us at K = 3, C = 8, J = 2 (330 lanes), 1.6 us at K = 5, C = 6, J = 3
+// (1,848), 6.8 us at K = 5, C = 10, J = 2 (6,006).  A launched sweep takes
+// 3.4-3.7 us up to tens of thousands of lanes, and the first solve of a
+// handle pays for recording the chunk.  The line lies where the two meet.
+template <class Op>
 bool orbit_in_lds(const mdpvi::OrbitShape& S) {
-  return !S.wide && mdpvi::orbit_lds_bytes(S) <= mdpvi::kOrbitLds &&
-         static_cast<uint64_t>(S.n) * S.L * (3 * S.K + 2) <= 56000;
+  const uint64_t reads = Op::kEval ? 2 * (2 * S.K + 2) : 3 * S.K + 2;
+  return !S.wide && mdpvi::orbit_lds_bytes(S, sizeof(typename Op::T)) <= mdpvi::kOrbitLds &&
+         static_cast<uint64_t>(S.n) * S.L * reads <= 56000;
 }
 
-// Whether vi_solve tries the form.  Launched sweeps need at least four times
+// Whether a solve tries the form.  Launched sweeps need at least four times
 // fewer orbits than occupancies (K = 2 has two: its full sweep is as fast);
 // a handful of sweeps does not pay for the check and the expansion.
+template <class Op>
 bool orbit_applies(mdpvi_mdp* h, int64_t max_iter) {
   OrbitPlan& O = h->orbit;
-  if (O.applies < 0)
-    O.applies = orbit_shape(h->M, &O.S) && (orbit_in_lds(O.S) || O.S.n_occ >= 4ull * O.S.n) ? 1 : 0;
-  return O.applies == 1 && max_iter >= 16;
+  if (O.covered < 0) O.covered = orbit_shape(h->M, &O.S) ? 1 : 0;
+  return h->orbits && O.covered == 1 && max_iter >= mdpvi::kOrbitChunk &&
+         (orbit_in_lds<Op>(O.S) || O.S.n_occ >= 4ull * O.S.n);
 }
 
 int orbit_ensure(mdpvi_mdp* h, hipStream_t s) {
@@ -540,23 +569,25 @@ int orbit_ensure(mdpvi_mdp* h, hipStream_t s) {
   if (h->device >= 0 && h->device != dev)
     return fail(MDPVI_EINVAL, "handle scratch lives on device %d, current device is %d", h->device, dev);
   if (O.dev) return MDPVI_OK;
-  const Model& M = h->M;
-  const size_t n = O.S.n, rows = static_cast<size_t>(2 + M.J) * M.K;
+  const size_t n = O.S.n, rows = static_cast<size_t>(2 + O.S.J) * O.S.K;
   size_t at = 0;
   auto take = [&](size_t bytes) {
     const size_t o = at;
     at += (bytes + 255) / 256 * 256;
     return o;
   };
+  const std::vector<uint32_t> binom = orbit_binom(O.S);
   const size_t o_ctl = take(sizeof(mdpvi::OrbitCtl));
   const size_t o_res = take(static_cast<size_t>(mdpvi::kResSlots) * mdpvi::kOrbitGrid * sizeof(double));
-  const size_t o_bin = take(static_cast<size_t>(M.K) * M.R * sizeof(uint32_t));
+  const size_t o_bin = take(binom.size() * sizeof(uint32_t));
   const size_t o_dig = take(n * sizeof(uint64_t));
   const size_t o_rep = take(n * sizeof(uint32_t));
   const size_t o_tab = take(rows * n * (O.S.wide ? 4 : 2));
+  const size_t o_act = take(n * O.S.L * sizeof(uint32_t));
+  const size_t o_load = take(n * O.S.L * sizeof(int32_t));
   size_t o_v[2], o_a[2];
-  for (int b = 0; b < 2; ++b) o_v[b] = take(n * O.S.L * sizeof(float));
-  for (int b = 0; b < 2; ++b) o_a[b] = take((n + 1) * sizeof(double));
+  for (size_t& o : o_v) o = take(n * O.S.L * sizeof(double));
+  for (size_t& o : o_a) o = take((n + 1) * sizeof(double));
   if (!O.mirror) {
     if (hipHostMalloc(reinterpret_cast<void**>(&O.mirror), sizeof(mdpvi::OrbitCtl), hipHostMallocDefault) !=
         hipSuccess) {
@@ -568,78 +599,65 @@ int orbit_ensure(mdpvi_mdp* h, hipStream_t s) {
     if (!*e) HIP_TRY(hipEventCreate(e));
   for (hipEvent_t& e : O.step)
     if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-  // the rank table: binom(v + i, i + 1) = sum_{u <= v} binom(u + i - 1, i)
-  std::vector<uint32_t> binom(static_cast<size_t>(M.K) * M.R);
-  for (int i = 0; i < M.K; ++i)
-    for (int v = 0; v < M.R; ++v)
-      binom[i * M.R + v] = i == 0 ? v : (v ? binom[i * M.R + v - 1] : 0) + (v ? binom[(i - 1) * M.R + v] : 0);
   unsigned char* d = nullptr;
   if (hipMalloc(reinterpret_cast<void**>(&d), at) != hipSuccess)
     return fail(MDPVI_ENOMEM, "hipMalloc of %zu orbit bytes failed", at);
-  hipError_t e = hipMemcpy(d + o_bin, binom.data(), binom.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
   O.S.binom = reinterpret_cast<uint32_t*>(d + o_bin);
   O.S.dig = reinterpret_cast<uint64_t*>(d + o_dig);
   O.S.rep = reinterpret_cast<uint32_t*>(d + o_rep);
   O.S.tab = d + o_tab;
+  O.P = orbit_params(h->M);
+  for (int b = 0; b < 2; ++b) {
+    O.W.V[b] = d + o_v[b];
+    O.W.A[b] = reinterpret_cast<double*>(d + o_a[b]);
+  }
+  O.W.act = reinterpret_cast<uint32_t*>(d + o_act);
+  O.W.load = reinterpret_cast<int32_t*>(d + o_load);
+  O.W.res = reinterpret_cast<double*>(d + o_res);
+  O.W.ctl = reinterpret_cast<mdpvi::OrbitCtl*>(d + o_ctl);
+  hipError_t e = hipMemcpy(d + o_bin, binom.data(), binom.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess)
-    e = mdpvi::launch_orbit_table(O.S, M, reinterpret_cast<uint64_t*>(d + o_dig), reinterpret_cast<uint32_t*>(d + o_rep),
-                                  d + o_tab, s);
+    e = mdpvi::launch_orbit_table(O.S, O.P, reinterpret_cast<uint64_t*>(d + o_dig),
+                                  reinterpret_cast<uint32_t*>(d + o_rep), d + o_tab, s);
   if (e != hipSuccess) {
     (void)hipFree(d);
     return fail_hip(e, "orbit table");
-  }
-  O.ctl = reinterpret_cast<mdpvi::OrbitCtl*>(d + o_ctl);
-  O.res = reinterpret_cast<double*>(d + o_res);
-  for (int b = 0; b < 2; ++b) {
-    O.V[b] = reinterpret_cast<float*>(d + o_v[b]);
-    O.A[b] = reinterpret_cast<double*>(d + o_a[b]);
   }
   O.dev = d;
   h->device = dev;
   return MDPVI_OK;
 }
 
-mdpvi::OrbitParams orbit_params(const Model& M) {
-  mdpvi::OrbitParams P;
-  for (int j = 0; j < mdpvi::kMaxJ; ++j) {
-    P.p[j] = M.p[j];
-    P.r_place[j] = M.r_place[j];
-    P.r_reject[j] = M.r_reject[j];
-  }
-  P.mu_L = M.mu_L;
-  P.nu_L = M.nu_L;
-  P.hold = M.hold;
-  P.gamma = M.gamma;
-  return P;
-}
-
-// Value iteration on the orbits; kOrbitRefused (V untouched) when V is not
-// invariant under host permutations.
-int orbit_vi(mdpvi_mdp* h, float* V, double tol, int64_t max_iter, hipStream_t s, mdpvi_stats* st) {
+// Value iteration (pi NULL) or evaluation of pi on the orbits; kOrbitRefused
+// or kOrbitInfeasible (V untouched) when V or pi is not invariant under host
+// permutations, or pi has an infeasible action.
+template <class Op>
+int orbit_solve(mdpvi_mdp* h, const uint8_t* pi, typename Op::T* V, double tol, int64_t max_iter, hipStream_t s,
+                mdpvi_stats* st) {
   int rc = orbit_ensure(h, s);
   if (rc) return rc;
   OrbitPlan& O = h->orbit;
   const Model& M = h->M;
-  const mdpvi::OrbitParams P = orbit_params(M);
   volatile mdpvi::OrbitCtl* w = O.mirror;
   if (h->timing && (rc = timing_events(h))) return rc;
   w->done = -1;
   w->flag = 0;
+  w->bad = 0;
   HIP_TRY(hipEventRecord(O.ev0, s));
-  HIP_TRY(mdpvi::launch_orbit_begin(O.S, P, M, V, O.V[0], O.A[0], O.A[1], O.ctl, O.mirror, O.res, tol, s));
+  HIP_TRY(mdpvi::launch_orbit_begin<Op>(O.S, O.P, O.W, V, pi, tol, O.mirror, s));
   int64_t issued = 0;
   double sweep_ms = 0.0;
-  if (orbit_in_lds(O.S)) {
+  if (orbit_in_lds<Op>(O.S)) {
     while (w->done < 0 && issued < max_iter) {
       const int64_t n = std::min(kOrbitLdsSweeps, max_iter - issued);
       if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[0], s));
-      HIP_TRY(mdpvi::launch_orbit_lds(O.S, P, O.V[0], O.V[1], O.A[0], O.A[1], O.ctl, O.mirror, issued, n, tol, s));
+      HIP_TRY(mdpvi::launch_orbit_lds<Op>(O.S, O.P, O.W, O.mirror, issued, n, tol, s));
       if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[1], s));
       issued += n;
-      HIP_TRY(mdpvi::launch_orbit_expand(O.S, M, V, O.V[0], O.V[1], O.ctl, issued, s));
+      HIP_TRY(mdpvi::launch_orbit_expand<Op>(O.S, O.W, V, issued, s));
       HIP_TRY(hipEventRecord(O.ev1, s));
       HIP_TRY(hipEventSynchronize(O.ev1));
-      if (w->flag) return kOrbitRefused;
+      if (w->flag) return w->bad ? kOrbitInfeasible : kOrbitRefused;
       if (h->timing) {
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, h->sweep_ev[0], h->sweep_ev[1]));
@@ -648,41 +666,40 @@ int orbit_vi(mdpvi_mdp* h, float* V, double tol, int64_t max_iter, hipStream_t s
     }
   } else {
     // chunks of sweeps, one in flight while the host waits for the other; the
-    // first tells whether the form was refused
-    if (!O.chunk && !h->timing)
-      HIP_TRY(mdpvi::build_orbit_chunk(O.S, P, O.V, O.A, O.ctl, O.mirror, O.res, &O.chunk));
-    int cur = 0;
-    while (w->done < 0 && issued < max_iter) {
+    // first only after the check, so that a refused call sweeps nothing
+    hipGraphExec_t& chunk = O.chunk[Op::kEval ? 1 : 0];
+    HIP_TRY(hipEventRecord(O.step[0], s));
+    HIP_TRY(hipEventSynchronize(O.step[0]));
+    if (w->flag) return w->bad ? kOrbitInfeasible : kOrbitRefused;
+    if (!chunk && !h->timing) HIP_TRY(mdpvi::build_orbit_chunk<Op>(O.S, O.P, O.W, O.mirror, &chunk));
+    for (int k = 0; w->done < 0 && issued < max_iter; ++k) {
       const int n = static_cast<int>(std::min<int64_t>(mdpvi::kOrbitChunk, max_iter - issued));
       if (n == mdpvi::kOrbitChunk && !h->timing) {
-        HIP_TRY(hipGraphLaunch(O.chunk, s));
+        HIP_TRY(hipGraphLaunch(chunk, s));
       } else {
         for (int i = 0; i < n; ++i) {
           if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[2 * i], s));
-          HIP_TRY(mdpvi::launch_orbit_sweep(O.S, P, O.V, O.A, O.ctl, O.mirror, O.res, i, s));
+          HIP_TRY(mdpvi::launch_orbit_sweep<Op>(O.S, O.P, O.W, O.mirror, i, s));
           if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[2 * i + 1], s));
         }
-        HIP_TRY(mdpvi::launch_orbit_next(O.ctl, n, s));
+        HIP_TRY(mdpvi::launch_orbit_next(O.W.ctl, n, s));
       }
-      HIP_TRY(hipEventRecord(O.step[cur], s));
-      const bool first = issued == 0;
+      HIP_TRY(hipEventRecord(O.step[k & 1], s));
       issued += n;
-      if (first || h->timing) {
-        HIP_TRY(hipEventSynchronize(O.step[cur]));
-        if (w->flag) return kOrbitRefused;
-        for (int i = 0; h->timing && i < n; ++i) {
+      if (h->timing) {
+        HIP_TRY(hipEventSynchronize(O.step[k & 1]));
+        for (int i = 0; i < n; ++i) {
           if (w->done >= 0 && issued - n + i >= w->done) break;   // sweeps that did no work
           float ms = 0.f;
           HIP_TRY(hipEventElapsedTime(&ms, h->sweep_ev[2 * i], h->sweep_ev[2 * i + 1]));
           sweep_ms += ms;
         }
-      } else if (issued > 2 * mdpvi::kOrbitChunk) {
-        HIP_TRY(hipEventSynchronize(O.step[cur ^ 1]));
+      } else if (k > 0) {
+        HIP_TRY(hipEventSynchronize(O.step[(k - 1) & 1]));
       }
-      cur ^= 1;
     }
-    if (w->done < 0) HIP_TRY(mdpvi::launch_orbit_last_residual(O.S, O.res, issued, O.ctl, O.mirror, s));
-    HIP_TRY(mdpvi::launch_orbit_expand(O.S, M, V, O.V[0], O.V[1], O.ctl, issued, s));
+    HIP_TRY(mdpvi::launch_orbit_last_residual(O.S, O.W, issued, O.mirror, s));
+    HIP_TRY(mdpvi::launch_orbit_expand<Op>(O.S, O.W, V, issued, s));
     HIP_TRY(hipEventRecord(O.ev1, s));
     HIP_TRY(hipEventSynchronize(O.ev1));
   }
@@ -691,12 +708,13 @@ int orbit_vi(mdpvi_mdp* h, float* V, double tol, int64_t max_iter, hipStream_t s
   float ms = 0.f;
   HIP_TRY(hipEventElapsedTime(&ms, O.ev0, O.ev1));
   if (st) {
+    const double states = static_cast<double>(M.n_states);
     st->iterations = final_iter;
     st->residual_inf = res;
     st->bound_inf = M.gamma / (1.0 - M.gamma) * res;
     st->seconds = ms * 1e-3;
-    st->backups = static_cast<double>(h->feasible_pairs) * static_cast<double>(final_iter);
-    st->bytes = 8.0 * static_cast<double>(M.n_states) * static_cast<double>(final_iter);
+    st->backups = (Op::kEval ? states : static_cast<double>(h->feasible_pairs)) * static_cast<double>(final_iter);
+    st->bytes = (Op::kEval ? 17.0 : 8.0) * states * static_cast<double>(final_iter);
     st->sweep_seconds = sweep_ms * 1e-3;
   }
   if (std::isnan(res) || std::isinf(res))
@@ -895,7 +913,48 @@ int fill_model(const mdpvi_params* p, Model& M, int64_t& pairs_out) {
 
 }  // namespace
 
+// The orbit form's plan of a batch: the instances it covers ("entries"), one
+// device block with their tables and buffers, and per operation (0 value
+// iteration, 1 evaluation) the lists of its launches.
+struct OrbitBatch {
+  struct List {                   // entries solved LDS-resident by one kernel
+    bool main_kernel, small;
+    std::vector<int32_t> entries;
+    const int32_t* dev = nullptr;
+    size_t lds = 0;
+  };
+  struct Rounds {                 // entries swept by one kernel, a launch per sweep
+    bool main_kernel;
+    std::vector<int32_t> entries;
+    std::vector<mdpvi::Tile> tiles;
+    const int32_t* dev = nullptr;
+    const mdpvi::Tile* d_tiles = nullptr;
+    mdpvi::Tile* d_act[2] = {};   // the tiles still running
+  };
+  struct Operation {
+    std::vector<List> lds;
+    std::vector<Rounds> rounds;
+  };
+  bool built = false;
+  std::vector<int32_t> inst;      // entry -> instance
+  Operation op[2];
+  unsigned char* dev = nullptr;
+  mdpvi::OrbitInst* d_inst = nullptr;
+  const int32_t* d_slot = nullptr;
+  const mdpvi::Tile* d_otiles = nullptr;
+  int n_otiles = 0;
+  mdpvi::OrbitCtl* d_ctl = nullptr;   // [entries]
+  int* d_words = nullptr;             // [0] round instances running, then per rounds list: all tiles, [2] active
+  mdpvi::OrbitCtl* h_ctl = nullptr;   // pinned
+  int* h_words = nullptr;             // pinned, two copies
+  hipStream_t small = nullptr;
+  hipEvent_t fork = nullptr, join[2] = {}, step[2] = {};
+};
+constexpr int kOrbitWords = 8;
+
 struct mdpvi_batch {
+  OrbitBatch orbit;
+  bool orbits = true;                // solve invariant instances on their orbits
   int n = 0;
   std::vector<Model> models;
   std::vector<int64_t> offsets;      // n + 1 state offsets
@@ -956,6 +1015,9 @@ struct mdpvi_batch {
   double* d_A[2] = {nullptr, nullptr};          // FP64 arrival terms of the round-form instances (VI)
   int* d_active[2] = {nullptr, nullptr};        // per-instance flags of batched policy iteration
   int* h_active = nullptr;                      // pinned
+  int* d_left = nullptr;                        // flags of the instances an evaluation sweeps in full
+  int* h_left = nullptr;                        // pinned
+  int32_t* d_sub = nullptr;                     // the LDS-resident instances among some (VI), on first use
   uint8_t* d_pbuf = nullptr;                    // policy scratch (round check), on first use
   int64_t a_total = 0;                          // their length: sum of n_occ + max(1, tocc)
   double* d_lines = nullptr;                    // the adjoint's reset-line sums (BatchInst::loff)
@@ -1003,7 +1065,8 @@ void mdp_free(mdpvi_mdp_t h) {
     for (uint32_t* o : per_t)
       if (o) (void)hipFree(o);
   if (h->out_host) (void)hipHostFree(h->out_host);
-  if (h->orbit.chunk) (void)hipGraphExecDestroy(h->orbit.chunk);
+  for (hipGraphExec_t g : h->orbit.chunk)
+    if (g) (void)hipGraphExecDestroy(g);
   if (h->orbit.dev) (void)hipFree(h->orbit.dev);
   if (h->orbit.mirror) (void)hipHostFree(h->orbit.mirror);
   for (hipEvent_t e : {h->orbit.ev0, h->orbit.ev1, h->orbit.step[0], h->orbit.step[1]})
@@ -1021,6 +1084,12 @@ int mdp_sweep_forms(mdpvi_mdp_t h, int32_t* vi, int32_t* eval) {
   mdpvi::TileShape S{};
   if (vi) *vi = vi_form(h, &S);
   if (eval) *eval = eval_form(h, &S);
+  return MDPVI_OK;
+}
+
+int mdp_set_orbits(mdpvi_mdp_t h, int32_t on) {
+  if (!h) return fail(MDPVI_EINVAL, "NULL handle");
+  h->orbits = on != 0;
   return MDPVI_OK;
 }
 
@@ -1283,8 +1352,8 @@ int vi_solve(mdpvi_mdp_t h, float* V, double tol, int64_t max_iter, void* hip_st
   if (!(tol > 0)) return fail(MDPVI_EINVAL, "tol=%g must be > 0", tol);
   if (max_iter < 1) return fail(MDPVI_EINVAL, "max_iter=%lld must be >= 1", (long long)max_iter);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  if (h->slab_t == -1 && orbit_applies(h, max_iter)) {
-    const int orc = orbit_vi(h, V, tol, max_iter, s, st);
+  if (h->slab_t == -1 && orbit_applies<mdpvi::OrbitVi>(h, max_iter)) {
+    const int orc = orbit_solve<mdpvi::OrbitVi>(h, nullptr, V, tol, max_iter, s, st);
     if (orc != kOrbitRefused) return orc;
   }
   int rc = ensure_scratch(h, static_cast<size_t>(h->M.n_states) * sizeof(float));
@@ -1537,16 +1606,23 @@ int policy_eval(mdpvi_mdp_t h, const uint8_t* pi, double* V, double tol, int64_t
   if (!h || !V || !pi) return fail(MDPVI_EINVAL, "NULL handle, policy or value array");
   if (!(tol > 0)) return fail(MDPVI_EINVAL, "tol=%g must be > 0", tol);
   if (max_iter < 1) return fail(MDPVI_EINVAL, "max_iter=%lld must be >= 1", (long long)max_iter);
-  int rc = ensure_scratch(h, static_cast<size_t>(h->M.n_states) * sizeof(double));
-  if (rc) return rc;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const Model& M = h->M;
-  HIP_TRY(mdpvi::launch_ctl_init(h->ctl, h->res, s));
-  HIP_TRY(mdpvi::launch_policy_check(M, pi, h->ctl, s));
-  HIP_TRY(hipMemcpyAsync(h->ctl_host, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  if (h->ctl_host->flag)
-    return fail(MDPVI_EINVAL, "policy has an action that is not feasible in its state");
+  const bool tried = orbit_applies<mdpvi::OrbitEval>(h, max_iter);
+  if (tried) {   // its check also covers feasibility
+    const int orc = orbit_solve<mdpvi::OrbitEval>(h, pi, V, tol, max_iter, s, st);
+    if (orc == kOrbitInfeasible) return fail(MDPVI_EINVAL, "%s", kInfeasiblePolicy);
+    if (orc != kOrbitRefused) return orc;
+  }
+  int rc = ensure_scratch(h, static_cast<size_t>(M.n_states) * sizeof(double));
+  if (rc) return rc;
+  if (!tried) {
+    HIP_TRY(mdpvi::launch_ctl_init(h->ctl, h->res, s));
+    HIP_TRY(mdpvi::launch_policy_check(M, pi, h->ctl, s));
+    HIP_TRY(hipMemcpyAsync(h->ctl_host, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    if (h->ctl_host->flag) return fail(MDPVI_EINVAL, "%s", kInfeasiblePolicy);
+  }
   return eval_run(h, pi, V, tol, max_iter, s, st);
 }
 
@@ -1618,7 +1694,7 @@ int policy_iteration(mdpvi_mdp_t h, uint8_t* pi, double* V, double eval_tol, int
   HIP_TRY(hipMemcpyAsync(h->ctl_host, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   if (h->ctl_host->flag)
-    return fail(MDPVI_EINVAL, "policy has an action that is not feasible in its state");
+    return fail(MDPVI_EINVAL, "%s", kInfeasiblePolicy);
   const auto t0 = std::chrono::steady_clock::now();
   mdpvi_stats tot{};
   int64_t r = 0;
@@ -1626,7 +1702,10 @@ int policy_iteration(mdpvi_mdp_t h, uint8_t* pi, double* V, double eval_tol, int
   while (r < max_rounds && !stable) {
     ++r;
     mdpvi_stats e{};
-    rc = eval_run(h, pi, V, eval_tol, eval_max_iter, s, &e);
+    rc = kOrbitRefused;
+    if (orbit_applies<mdpvi::OrbitEval>(h, eval_max_iter))
+      rc = orbit_solve<mdpvi::OrbitEval>(h, pi, V, eval_tol, eval_max_iter, s, &e);
+    if (rc == kOrbitRefused) rc = eval_run(h, pi, V, eval_tol, eval_max_iter, s, &e);
     tot.iterations += e.iterations;
     tot.residual_inf = e.residual_inf;
     tot.bound_inf = e.bound_inf;
@@ -1673,7 +1752,7 @@ int vi_adjoint(mdpvi_mdp_t h, const uint8_t* pi, const double* V_pi, float* w, d
   HIP_TRY(hipMemcpyAsync(h->ctl_host, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   if (h->ctl_host->flag)
-    return fail(MDPVI_EINVAL, "policy has an action that is not feasible in its state");
+    return fail(MDPVI_EINVAL, "%s", kInfeasiblePolicy);
   const int aform = adjoint_form(h);
   rc = run_loop<float>(
       h, w, tol, max_iter, s, st, 9.0 * M.n_states, static_cast<double>(M.n_states),
@@ -1880,11 +1959,12 @@ int ensure_batch_device(mdpvi_batch* b) {
     if ((rc = dalloc(reinterpret_cast<void**>(&b->d_A[a]), b->a_total * sizeof(double)))) return rc;
     if ((rc = dalloc(reinterpret_cast<void**>(&b->d_active[a]), n * sizeof(int)))) return rc;
   }
-  if (hipHostMalloc(reinterpret_cast<void**>(&b->h_active), std::max(n, 1) * sizeof(int), hipHostMallocDefault) !=
-      hipSuccess) {
-    b->h_active = nullptr;
-    return fail(MDPVI_ENOMEM, "hipHostMalloc of the batch flags failed");
-  }
+  if ((rc = dalloc(reinterpret_cast<void**>(&b->d_left), n * sizeof(int)))) return rc;
+  for (int** h : {&b->h_active, &b->h_left})
+    if (hipHostMalloc(reinterpret_cast<void**>(h), std::max(n, 1) * sizeof(int), hipHostMallocDefault) != hipSuccess) {
+      *h = nullptr;
+      return fail(MDPVI_ENOMEM, "hipHostMalloc of the batch flags failed");
+    }
   for (int oi = 0; oi < 3; ++oi) {
     if ((rc = dalloc(reinterpret_cast<void**>(&b->d_rtiles[oi]), b->rtiles[oi].size() * sizeof(mdpvi::Tile))))
       return rc;
@@ -2092,6 +2172,14 @@ int mdp_build_batch(const mdpvi_params* p, int32_t n, mdpvi_batch_t* out) {
 void mdp_free_batch(mdpvi_batch_t b) {
   if (!b) return;
   if (b->side) (void)hipStreamSynchronize(b->side);
+  if (b->orbit.small) (void)hipStreamSynchronize(b->orbit.small);
+  (void)hipFree(b->orbit.dev);
+  (void)hipFree(b->d_sub);
+  if (b->orbit.h_ctl) (void)hipHostFree(b->orbit.h_ctl);
+  if (b->orbit.h_words) (void)hipHostFree(b->orbit.h_words);
+  if (b->orbit.small) (void)hipStreamDestroy(b->orbit.small);
+  for (hipEvent_t e : {b->orbit.fork, b->orbit.join[0], b->orbit.join[1], b->orbit.step[0], b->orbit.step[1]})
+    if (e) (void)hipEventDestroy(e);
   (void)hipFree(b->d_inst);
   (void)hipFree(b->d_lds);
   (void)hipFree(b->d_round);
@@ -2125,6 +2213,8 @@ void mdp_free_batch(mdpvi_batch_t b) {
   (void)hipFree(b->d_active[0]);
   (void)hipFree(b->d_active[1]);
   if (b->h_active) (void)hipHostFree(b->h_active);
+  if (b->h_left) (void)hipHostFree(b->h_left);
+  (void)hipFree(b->d_left);
   for (int oi = 0; oi < 3; ++oi) {
     (void)hipFree(b->d_rtiles[oi]);
     (void)hipFree(b->d_rtiles_all[oi]);
@@ -2160,25 +2250,355 @@ int batch_offsets(mdpvi_batch_t b, int64_t* offsets) {
   return MDPVI_OK;
 }
 
-int vi_solve_batch(mdpvi_batch_t b, float* V, double tol, int64_t max_iter, void* hip_stream,
-                   mdpvi_stats* st, int64_t* iterations, double* residuals) {
-  if (!b || !V) return fail(MDPVI_EINVAL, "NULL batch or value array");
-  if (!(tol > 0)) return fail(MDPVI_EINVAL, "tol=%g must be > 0", tol);
-  if (max_iter < 1) return fail(MDPVI_EINVAL, "max_iter=%lld must be >= 1", (long long)max_iter);
-  int rc = ensure_batch_device(b);
+}  // extern "C"
+
+namespace {
+
+// The entries and lists of the batch's orbit form, and their device block.
+int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
+  OrbitBatch& O = b->orbit;
+  if (O.built) return MDPVI_OK;
+  std::vector<mdpvi::OrbitInst> inst;
+  std::vector<int32_t> slot(b->n, -1);
+  std::vector<mdpvi::Tile> otiles, ttiles;
+  O.inst.clear();
+  for (auto& op : O.op) op = OrbitBatch::Operation();
+  for (int i = 0; i < b->n; ++i) {
+    const Model& M = b->models[i];
+    mdpvi::OrbitInst I{};
+    if (!orbit_shape(M, &I.S) || I.S.wide) continue;
+    const bool lds = orbit_in_lds<mdpvi::OrbitVi>(I.S) && orbit_in_lds<mdpvi::OrbitEval>(I.S);
+    if (!lds && I.S.n_occ < 4ull * I.S.n) continue;
+    I.P = orbit_params(M);
+    I.offset = b->offsets[i];
+    I.grid = mdpvi::orbit_grid(I.S);
+    I.inst = i;
+    slot[i] = static_cast<int32_t>(inst.size());
+    O.inst.push_back(i);
+    for (uint32_t r = 0; r < I.S.n; r += 256) otiles.push_back({slot[i], r});
+    inst.push_back(I);
+  }
+  const int n = static_cast<int>(inst.size());
+  // lists: LDS-resident solves with the longest first (a sweep costs its
+  // lanes, the sweeps to convergence grow like 1/(1 - gamma))
+  for (int op = 0; op < 2; ++op) {
+    OrbitBatch::Operation& L = O.op[op];
+    const size_t value = op ? sizeof(double) : sizeof(float);
+    for (bool main_kernel : {true, false}) {
+      OrbitBatch::Rounds R;
+      R.main_kernel = main_kernel;
+      OrbitBatch::List lists[2];   // big, small
+      for (bool small : {false, true}) {
+        lists[small].main_kernel = main_kernel;
+        lists[small].small = small;
+      }
+      for (int e = 0; e < n; ++e) {
+        const mdpvi::OrbitShape& S = inst[e].S;
+        if ((S.K <= 5 && S.L <= 4) != main_kernel) continue;
+        if (op ? orbit_in_lds<mdpvi::OrbitEval>(S) : orbit_in_lds<mdpvi::OrbitVi>(S)) {
+          OrbitBatch::List& l = lists[S.n * S.L <= mdpvi::kOrbitSmallBlock];
+          l.entries.push_back(e);
+          l.lds = std::max(l.lds, mdpvi::orbit_lds_bytes(S, value));
+        } else {
+          R.entries.push_back(e);
+          for (uint32_t g = 0; g < inst[e].grid; ++g) R.tiles.push_back({e, g});
+        }
+      }
+      for (auto& l : lists) {
+        std::sort(l.entries.begin(), l.entries.end(), [&](int32_t x, int32_t y) {
+          auto cost = [&](int32_t e) {
+            return static_cast<double>(inst[e].S.n) * inst[e].S.L * inst[e].S.K /
+                   (1.0 - b->models[inst[e].inst].gamma + 1e-3);
+          };
+          const double cx = cost(x), cy = cost(y);
+          return cx != cy ? cx > cy : x < y;
+        });
+        if (!l.entries.empty()) L.lds.push_back(l);
+      }
+      if (!R.entries.empty()) L.rounds.push_back(R);
+    }
+  }
+  O.n_otiles = static_cast<int>(otiles.size());
+  if (n == 0) {
+    O.built = true;
+    return MDPVI_OK;
+  }
+  size_t at = 0;
+  auto take = [&](size_t bytes) {
+    const size_t o = at;
+    at += (bytes + 255) / 256 * 256;
+    return o;
+  };
+  std::vector<unsigned char> up;   // what is uploaded: the start of the block
+  auto put = [&](const void* p, size_t bytes) {
+    const size_t o = take(bytes);
+    up.resize(at);
+    if (bytes) std::memcpy(up.data() + o, p, bytes);
+    return o;
+  };
+  const size_t o_inst = take(n * sizeof(mdpvi::OrbitInst));   // filled below
+  const size_t o_slot = put(slot.data(), slot.size() * sizeof(int32_t));
+  const size_t o_ot = put(otiles.data(), otiles.size() * sizeof(mdpvi::Tile));
+  std::vector<size_t> o_list, o_rlist, o_rt;
+  int words[kOrbitWords] = {};
+  for (auto& L : O.op) {
+    for (auto& l : L.lds) o_list.push_back(put(l.entries.data(), l.entries.size() * sizeof(int32_t)));
+    for (auto& r : L.rounds) {
+      o_rlist.push_back(put(r.entries.data(), r.entries.size() * sizeof(int32_t)));
+      o_rt.push_back(put(r.tiles.data(), r.tiles.size() * sizeof(mdpvi::Tile)));
+    }
+  }
+  const size_t o_words = put(words, sizeof words);
+  // one table per (K, C, sizes), one rank table per (K, C)
+  std::map<std::vector<int>, int> shapes;   // -> the entry that owns the table
+  std::vector<size_t> o_bin(n), o_dig(n), o_rep(n), o_tab(n);
+  for (int e = 0; e < n; ++e) {
+    const Model& M = b->models[inst[e].inst];
+    const mdpvi::OrbitShape& S = inst[e].S;
+    std::vector<int> key = {M.K, M.C, M.J};
+    key.insert(key.end(), M.size, M.size + M.J);
+    auto it = shapes.find(key);
+    if (it == shapes.end()) {
+      shapes[key] = e;
+      const std::vector<uint32_t> binom = orbit_binom(S);
+      o_bin[e] = put(binom.data(), binom.size() * sizeof(uint32_t));
+      for (uint32_t r = 0; r < S.n; r += 256) ttiles.push_back({e, r});
+    }
+  }
+  const size_t o_tt = put(ttiles.data(), ttiles.size() * sizeof(mdpvi::Tile));
+  const size_t uploaded = at;
+  for (int e = 0; e < n; ++e) {
+    const Model& M = b->models[inst[e].inst];
+    const mdpvi::OrbitShape& S = inst[e].S;
+    std::vector<int> key = {M.K, M.C, M.J};
+    key.insert(key.end(), M.size, M.size + M.J);
+    const int owner = shapes[key];
+    if (owner == e) {
+      o_dig[e] = take(S.n * sizeof(uint64_t));
+      o_rep[e] = take(S.n * sizeof(uint32_t));
+      o_tab[e] = take(static_cast<size_t>(2 + S.J) * S.K * S.n * sizeof(uint16_t));
+    }
+    o_bin[e] = o_bin[owner];
+    o_dig[e] = o_dig[owner];
+    o_rep[e] = o_rep[owner];
+    o_tab[e] = o_tab[owner];
+  }
+  const size_t o_ctl = take(n * sizeof(mdpvi::OrbitCtl));
+  std::vector<char> round(n, 0);
+  for (auto& L : O.op)
+    for (auto& r : L.rounds)
+      for (int32_t e : r.entries) round[e] = 1;
+  std::vector<size_t> o_buf[7];   // V0 V1 A0 A1 act load res
+  for (int e = 0; e < n; ++e) {
+    const mdpvi::OrbitShape& S = inst[e].S;
+    const size_t v = static_cast<size_t>(S.n) * S.L;
+    for (int k = 0; k < 2; ++k) o_buf[k].push_back(take(v * sizeof(double)));
+    for (int k = 2; k < 4; ++k) o_buf[k].push_back(take((S.n + 1) * sizeof(double)));
+    for (int k = 4; k < 6; ++k) o_buf[k].push_back(take(v * sizeof(uint32_t)));
+    o_buf[6].push_back(round[e] ? take(static_cast<size_t>(mdpvi::kResSlots) * mdpvi::kOrbitGrid * sizeof(double)) : 0);
+  }
+  std::vector<size_t> o_act;
+  for (auto& L : O.op)
+    for (auto& r : L.rounds)
+      for (int k = 0; k < 2; ++k) o_act.push_back(take(r.tiles.size() * sizeof(mdpvi::Tile)));
+  unsigned char* d = nullptr;
+  if (hipMalloc(reinterpret_cast<void**>(&d), at) != hipSuccess)
+    return fail(MDPVI_ENOMEM, "hipMalloc of %zu orbit bytes failed", at);
+  for (int e = 0; e < n; ++e) {
+    mdpvi::OrbitInst& I = inst[e];
+    I.S.binom = reinterpret_cast<uint32_t*>(d + o_bin[e]);
+    I.S.dig = reinterpret_cast<uint64_t*>(d + o_dig[e]);
+    I.S.rep = reinterpret_cast<uint32_t*>(d + o_rep[e]);
+    I.S.tab = d + o_tab[e];
+    for (int k = 0; k < 2; ++k) {
+      I.W.V[k] = d + o_buf[k][e];
+      I.W.A[k] = reinterpret_cast<double*>(d + o_buf[2 + k][e]);
+    }
+    I.W.act = reinterpret_cast<uint32_t*>(d + o_buf[4][e]);
+    I.W.load = reinterpret_cast<int32_t*>(d + o_buf[5][e]);
+    I.W.res = round[e] ? reinterpret_cast<double*>(d + o_buf[6][e]) : nullptr;
+    I.W.ctl = reinterpret_cast<mdpvi::OrbitCtl*>(d + o_ctl) + e;
+  }
+  std::memcpy(up.data() + o_inst, inst.data(), n * sizeof(mdpvi::OrbitInst));
+  O.d_inst = reinterpret_cast<mdpvi::OrbitInst*>(d + o_inst);
+  hipError_t e = hipMemcpy(d, up.data(), uploaded, hipMemcpyHostToDevice);
+  if (e == hipSuccess)
+    e = mdpvi::launch_orbit_batch_table(O.d_inst, reinterpret_cast<mdpvi::Tile*>(d + o_tt),
+                                        static_cast<int>(ttiles.size()), s);
+  if (e == hipSuccess && !O.h_ctl)
+    e = hipHostMalloc(reinterpret_cast<void**>(&O.h_ctl), n * sizeof(mdpvi::OrbitCtl), hipHostMallocDefault);
+  if (e == hipSuccess && !O.h_words)
+    e = hipHostMalloc(reinterpret_cast<void**>(&O.h_words), 2 * kOrbitWords * sizeof(int), hipHostMallocDefault);
+  if (e == hipSuccess && !O.small) e = hipStreamCreateWithFlags(&O.small, hipStreamNonBlocking);
+  for (hipEvent_t* ev : {&O.fork, &O.join[0], &O.join[1], &O.step[0], &O.step[1]})
+    if (e == hipSuccess && !*ev) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
+  if (e != hipSuccess) {
+    (void)hipStreamSynchronize(s);
+    (void)hipFree(d);
+    return fail_hip(e, "batch orbit plan");
+  }
+  O.d_slot = reinterpret_cast<int32_t*>(d + o_slot);
+  O.d_otiles = reinterpret_cast<mdpvi::Tile*>(d + o_ot);
+  O.d_words = reinterpret_cast<int*>(d + o_words);
+  O.d_ctl = reinterpret_cast<mdpvi::OrbitCtl*>(d + o_ctl);
+  size_t il = 0, ir = 0, ia = 0;
+  for (auto& L : O.op) {
+    for (auto& l : L.lds) l.dev = reinterpret_cast<int32_t*>(d + o_list[il++]);
+    for (auto& r : L.rounds) {
+      r.dev = reinterpret_cast<int32_t*>(d + o_rlist[ir]);
+      r.d_tiles = reinterpret_cast<mdpvi::Tile*>(d + o_rt[ir++]);
+      for (auto& act : r.d_act) act = reinterpret_cast<mdpvi::Tile*>(d + o_act[ia++]);
+    }
+  }
+  O.dev = d;
+  O.built = true;
+  return MDPVI_OK;
+}
+
+// Whether a call tries the orbit form at all.
+bool orbit_batch_applies(const mdpvi_batch* b, int64_t max_iter) {
+  return b->orbits && max_iter >= mdpvi::kOrbitChunk && !(b->orbit.built && b->orbit.inst.empty());
+}
+
+// Value iteration (pi NULL) or evaluation of pi on the orbits, for the
+// instances with active[i] != 0 (device, nullable: all; h_active its host
+// copy).  done[i] := sweeps and residual of the instances solved; *n_left
+// counts the active ones that were not (refused or not covered), whose V is
+// untouched.
+template <class Op>
+int orbit_batch_solve(mdpvi_batch* b, const uint8_t* pi, typename Op::T* V, double tol, int64_t max_iter,
+                      hipStream_t s, const int* active, std::vector<mdpvi::BatchOut>& done, int* n_left) {
+  int rc = orbit_batch_ensure(b, s);
   if (rc) return rc;
-  hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  OrbitBatch& O = b->orbit;
+  const int n = static_cast<int>(O.inst.size()), nt = static_cast<int>(b->tiles_all.size());
+  if (n == 0) return MDPVI_OK;
+  OrbitBatch::Operation& L = O.op[Op::kEval ? 1 : 0];
+  auto on = [&](int32_t e) { return !active || b->h_active[O.inst[e]]; };
+  int n_round = 0;
+  for (auto& r : L.rounds)
+    for (int32_t e : r.entries) n_round += on(e) ? 1 : 0;
+  HIP_TRY(mdpvi::launch_orbit_batch_begin<Op>(O.d_inst, O.d_slot, O.d_otiles, O.n_otiles, b->d_tiles_all, nt, V, pi,
+                                              active, tol, O.d_words, n_round, s));
+  int64_t lds_sweeps = 0;
+  auto lds = [&]() -> hipError_t {
+    const int64_t m = std::min(kOrbitLdsSweeps, max_iter - lds_sweeps);
+    hipError_t e = hipEventRecord(O.fork, s);
+    for (int k = 0; k < 2 && e == hipSuccess; ++k) {   // the larger instances first
+      const hipStream_t q = k ? O.small : b->side;
+      e = hipStreamWaitEvent(q, O.fork, 0);
+      for (auto& l : L.lds)
+        if (e == hipSuccess && l.small == (k == 1))
+          e = mdpvi::launch_orbit_batch_lds<Op>(O.d_inst, l.dev, static_cast<int>(l.entries.size()), l.main_kernel,
+                                                l.small, l.lds, lds_sweeps, m, tol, q);
+      if (e == hipSuccess) e = hipEventRecord(O.join[k], q);
+    }
+    lds_sweeps += m;
+    return e;
+  };
+  HIP_TRY(lds());
+  int64_t issued = 0;
+  if (n_round > 0) {
+    // chunks of rounds; the tiles still running are compacted after each, and
+    // the host reads their counts one chunk late
+    const size_t nr = L.rounds.size();
+    std::vector<const mdpvi::Tile*> tiles(nr);
+    std::vector<int*> cnt(nr);
+    std::vector<int> most(nr);
+    for (size_t q = 0; q < nr; ++q) {
+      tiles[q] = L.rounds[q].d_tiles;
+      most[q] = static_cast<int>(L.rounds[q].tiles.size());
+      cnt[q] = O.d_words + 1 + 3 * q;
+      HIP_TRY(mdpvi::launch_orbit_set(cnt[q], most[q], s));
+    }
+    for (int k = 0; issued < max_iter; ++k) {
+      const int64_t m = std::min<int64_t>(mdpvi::kOrbitChunk, max_iter - issued);
+      for (int64_t j = issued; j < issued + m; ++j)
+        for (size_t q = 0; q < nr; ++q)
+          HIP_TRY(mdpvi::launch_orbit_round<Op>(O.d_inst, tiles[q], cnt[q], most[q], L.rounds[q].main_kernel,
+                                                O.d_words, j, s));
+      issued += m;
+      for (size_t q = 0; q < nr; ++q) {
+        int* to = O.d_words + 2 + 3 * q + (k & 1);
+        HIP_TRY(mdpvi::launch_orbit_compact(O.d_inst, tiles[q], cnt[q], most[q], L.rounds[q].d_act[k & 1], to, s));
+        tiles[q] = L.rounds[q].d_act[k & 1];
+        cnt[q] = to;
+      }
+      HIP_TRY(hipMemcpyAsync(O.h_words + (k & 1) * kOrbitWords, O.d_words, kOrbitWords * sizeof(int),
+                             hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipEventRecord(O.step[k & 1], s));
+      if (k > 0) {
+        HIP_TRY(hipEventSynchronize(O.step[(k - 1) & 1]));
+        const int* h = O.h_words + ((k - 1) & 1) * kOrbitWords;
+        if (h[0] <= 0) break;
+        for (size_t q = 0; q < nr; ++q) most[q] = std::min(most[q], h[2 + 3 * q + ((k - 1) & 1)]);
+      }
+    }
+    for (auto& r : L.rounds)
+      HIP_TRY(mdpvi::launch_orbit_batch_residual(O.d_inst, r.dev, static_cast<int>(r.entries.size()), issued, s));
+  }
+  std::vector<char> in_round(n, 0);
+  for (auto& r : L.rounds)
+    for (int32_t e : r.entries) in_round[e] = 1;
+  for (;;) {
+    HIP_TRY(hipStreamWaitEvent(s, O.join[0], 0));
+    HIP_TRY(hipStreamWaitEvent(s, O.join[1], 0));
+    // an LDS-resident instance that has not stopped ran lds_sweeps, a round
+    // instance `issued`: both are max_iter when the last pass comes here
+    HIP_TRY(mdpvi::launch_orbit_batch_expand<Op>(O.d_inst, O.d_slot, b->d_tiles_all, nt, V,
+                                                 lds_sweeps < max_iter ? issued : max_iter, s));
+    HIP_TRY(hipMemcpyAsync(O.h_ctl, O.d_ctl, n * sizeof(mdpvi::OrbitCtl), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    bool more = false;
+    for (int e = 0; e < n; ++e) more = more || (!in_round[e] && O.h_ctl[e].done < 0 && !O.h_ctl[e].flag);
+    if (!more || lds_sweeps >= max_iter) break;
+    HIP_TRY(lds());
+  }
+  for (int e = 0; e < n; ++e) {
+    if (!on(e) || O.h_ctl[e].flag) continue;
+    const long long it = O.h_ctl[e].done >= 0 ? O.h_ctl[e].done : max_iter;
+    done[O.inst[e]] = {it, O.h_ctl[e].residual};
+    --*n_left;
+  }
+  return MDPVI_OK;
+}
+
+}  // namespace
+
+namespace {
+
+// Value iteration by full sweeps of every instance, or of those with
+// on[i] != 0 (on: h_active, uploaded here); their outputs into h_out.
+int batch_vi_full(mdpvi_batch* b, float* V, double tol, int64_t max_iter, hipStream_t s, const int* on) {
   const int n_round = static_cast<int>(b->round_list.size());
-  const int n_lds = static_cast<int>(b->lds_list.size());
-  HIP_TRY(mdpvi::launch_batch_ctl_init(b->d_ctl, b->d_round, n_round, b->d_remaining, b->d_flags, 0, s));
-  HIP_TRY(hipEventRecord(b->ev0, s));
+  int n_lds = static_cast<int>(b->lds_list.size()), n_run = n_round;
+  const int32_t* lds_list = b->d_lds;
+  if (on) {
+    std::vector<int32_t> sub;
+    for (int32_t i : b->lds_list)
+      if (on[i]) sub.push_back(i);
+    if (!b->d_sub && hipMalloc(reinterpret_cast<void**>(&b->d_sub), b->n * sizeof(int32_t)) != hipSuccess) {
+      b->d_sub = nullptr;
+      return fail(MDPVI_ENOMEM, "hipMalloc of a batch list failed");
+    }
+    n_lds = static_cast<int>(sub.size());
+    if (n_lds) HIP_TRY(hipMemcpyAsync(b->d_sub, sub.data(), n_lds * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));   // the list above is this call's own
+    lds_list = b->d_sub;
+    n_run = 0;
+    for (int32_t i : b->round_list) n_run += on[i] ? 1 : 0;
+    HIP_TRY(hipMemcpyAsync(b->d_active[0], on, b->n * sizeof(int), hipMemcpyHostToDevice, s));
+    HIP_TRY(mdpvi::launch_batch_ctl_activate(b->d_ctl, b->d_active[0], b->n, b->d_remaining, n_run, s));
+  } else {
+    HIP_TRY(mdpvi::launch_batch_ctl_init(b->d_ctl, b->d_round, n_round, b->d_remaining, b->d_flags, 0, s));
+  }
   HIP_TRY(hipEventRecord(b->ev_fork, s));
   HIP_TRY(hipStreamWaitEvent(b->side, b->ev_fork, 0));
-  HIP_TRY(mdpvi::launch_batch_lds_vi(b->d_inst, b->d_lds, n_lds, b->lds_maxK, b->lds_maxJ, b->lds_bytes,
+  HIP_TRY(mdpvi::launch_batch_lds_vi(b->d_inst, lds_list, n_lds, b->lds_maxK, b->lds_maxJ, b->lds_bytes,
                                      V, tol, max_iter, b->d_out, b->side));
   HIP_TRY(hipEventRecord(b->ev_join, b->side));
   int64_t issued = 0;
-  if (n_round > 0) {
+  if (n_run > 0) {
     int64_t chunk = 8;
     const int opt = batch_opt(b, 0);
     const int oi = opt_index(opt);
@@ -2191,6 +2611,17 @@ int vi_solve_batch(mdpvi_batch_t b, float* V, double tol, int64_t max_iter, void
     int nvt = tile ? static_cast<int>(b->vt_tiles.size()) : 0;
     const mdpvi::Tile* tiles = tile ? b->d_rtiles_nt[oi] : b->d_rtiles[oi];
     int nt = static_cast<int>(tile ? b->rtiles_nt[oi].size() : b->rtiles[oi].size()), cur = 0;
+    if (on) {   // only their tiles
+      HIP_TRY(mdpvi::launch_batch_compact(tiles, nt, b->d_ctl, b->d_act[cur], b->d_remaining + 1, s));
+      HIP_TRY(mdpvi::launch_batch_compact(vtiles, nvt, b->d_ctl, b->d_vact[cur], b->d_remaining + 2, s));
+      HIP_TRY(hipMemcpyAsync(b->h_remaining, b->d_remaining, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipStreamSynchronize(s));
+      tiles = b->d_act[cur];
+      nt = b->h_remaining[1];
+      vtiles = b->d_vact[cur];
+      nvt = b->h_remaining[2];
+      cur ^= 1;
+    }
     while (issued < max_iter) {
       const int64_t m = std::min<int64_t>(chunk, max_iter - issued);
       for (int64_t k = 0; k < m; ++k) {
@@ -2219,6 +2650,36 @@ int vi_solve_batch(mdpvi_batch_t b, float* V, double tol, int64_t max_iter, void
   }
   HIP_TRY(hipStreamWaitEvent(s, b->ev_join, 0));
   HIP_TRY(hipMemcpyAsync(b->h_out, b->d_out, b->n * sizeof(mdpvi::BatchOut), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  return MDPVI_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int vi_solve_batch(mdpvi_batch_t b, float* V, double tol, int64_t max_iter, void* hip_stream,
+                   mdpvi_stats* st, int64_t* iterations, double* residuals) {
+  if (!b || !V) return fail(MDPVI_EINVAL, "NULL batch or value array");
+  if (!(tol > 0)) return fail(MDPVI_EINVAL, "tol=%g must be > 0", tol);
+  if (max_iter < 1) return fail(MDPVI_EINVAL, "max_iter=%lld must be >= 1", (long long)max_iter);
+  int rc = ensure_batch_device(b);
+  if (rc) return rc;
+  hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  HIP_TRY(hipEventRecord(b->ev0, s));
+  std::vector<mdpvi::BatchOut> done(b->n, mdpvi::BatchOut{0, 0.0});
+  int n_left = b->n;
+  if (b->round_opt[0] == 0 && b->tile_mode[0] < 0 && orbit_batch_applies(b, max_iter)) {
+    rc = orbit_batch_solve<mdpvi::OrbitVi>(b, nullptr, V, tol, max_iter, s, nullptr, done, &n_left);
+    if (rc) return rc;
+  }
+  if (n_left > 0) {
+    for (int i = 0; i < b->n; ++i) b->h_active[i] = done[i].iterations == 0;
+    rc = batch_vi_full(b, V, tol, max_iter, s, n_left < b->n ? b->h_active : nullptr);
+    if (rc) return rc;
+  }
+  for (int i = 0; i < b->n; ++i)
+    if (done[i].iterations > 0) b->h_out[i] = done[i];
   HIP_TRY(hipEventRecord(b->ev1, s));
   HIP_TRY(hipEventSynchronize(b->ev1));
   float ms = 0.f;
@@ -2282,6 +2743,8 @@ int batch_check_policy(mdpvi_batch* b, const uint8_t* pi, hipStream_t s, int* ba
 // With `active` (device int[n], nullable), only the instances with
 // active[i] != 0 (n_active of them) are swept; the others keep their values
 // and report 0 sweeps.
+// given (nullable): outputs of the instances already solved (the orbit form;
+// the caller has recorded the call's first event); n_active may be 0 then.
 // The round loop over every instance (or the active ones): round(j, tiles,
 // n, tiles2, n2) issues round j over the direct-form tiles and the
 // tile-form tiles (tiles2: the evaluation's, or none), which are compacted
@@ -2290,10 +2753,14 @@ template <typename Round, typename Finish>
 int batch_all_rounds(mdpvi_batch* b, const mdpvi::Tile* tiles, int nt, const mdpvi::Tile* tiles2, int nt2,
                      double tol, int64_t max_iter, hipStream_t s, mdpvi_stats* st, int64_t* iterations,
                      double* residuals, double bytes_per_state, Round round, Finish finish,
-                     const int* active = nullptr, int n_active = 0) {
+                     const int* active = nullptr, int n_active = 0,
+                     const std::vector<mdpvi::BatchOut>* given = nullptr) {
   int64_t issued = 0, chunk = 8;
   int cur = 0;
-  if (active) {
+  if (!given) HIP_TRY(hipEventRecord(b->ev0, s));
+  if (active && n_active == 0) {
+    nt = nt2 = 0;
+  } else if (active) {
     HIP_TRY(mdpvi::launch_batch_ctl_activate(b->d_ctl, active, b->n, b->d_remaining, n_active, s));
     HIP_TRY(mdpvi::launch_batch_compact(tiles, nt, b->d_ctl, b->d_act[cur], b->d_remaining + 1, s));
     HIP_TRY(mdpvi::launch_batch_compact(tiles2, nt2, b->d_ctl, b->d_eact[cur], b->d_remaining + 2, s));
@@ -2307,7 +2774,6 @@ int batch_all_rounds(mdpvi_batch* b, const mdpvi::Tile* tiles, int nt, const mdp
   } else {
     HIP_TRY(mdpvi::launch_batch_ctl_init(b->d_ctl, b->d_all, b->n, b->d_remaining, b->d_flags, 0, s));
   }
-  HIP_TRY(hipEventRecord(b->ev0, s));
   while (issued < max_iter && nt + nt2 > 0) {
     const int64_t m = std::min<int64_t>(chunk, max_iter - issued);
     for (int64_t k = 0; k < m; ++k) HIP_TRY(round(issued + k, tiles, nt, tiles2, nt2));
@@ -2325,10 +2791,16 @@ int batch_all_rounds(mdpvi_batch* b, const mdpvi::Tile* tiles, int nt, const mdp
     cur ^= 1;
     if (chunk < kMaxChunk) chunk *= 2;
   }
-  HIP_TRY(finish(issued));
-  HIP_TRY(hipMemcpyAsync(b->h_out, b->d_out, b->n * sizeof(mdpvi::BatchOut), hipMemcpyDeviceToHost, s));
+  if (active && n_active == 0) {
+    for (int i = 0; i < b->n; ++i) b->h_out[i] = mdpvi::BatchOut{0, 0.0};
+  } else {
+    HIP_TRY(finish(issued));
+    HIP_TRY(hipMemcpyAsync(b->h_out, b->d_out, b->n * sizeof(mdpvi::BatchOut), hipMemcpyDeviceToHost, s));
+  }
   HIP_TRY(hipEventRecord(b->ev1, s));
   HIP_TRY(hipEventSynchronize(b->ev1));
+  for (int i = 0; given && i < b->n; ++i)
+    if ((*given)[i].iterations > 0) b->h_out[i] = (*given)[i];
   float ms = 0.f;
   HIP_TRY(hipEventElapsedTime(&ms, b->ev0, b->ev1));
   int64_t max_it = 0, not_conv = 0, nan = 0;
@@ -2415,6 +2887,16 @@ int policy_eval_batch(mdpvi_batch_t b, const uint8_t* pi, double* V, double tol,
   int bad = -1;
   if ((rc = batch_check_policy(b, pi, s, &bad))) return rc;
   if (bad >= 0) return fail(MDPVI_EINVAL, "instance %d: policy has an infeasible action", bad);
+  std::vector<mdpvi::BatchOut> done(b->n, mdpvi::BatchOut{0, 0.0});
+  int n_left = b->n;
+  HIP_TRY(hipEventRecord(b->ev0, s));
+  if (orbit_batch_applies(b, max_iter) &&
+      (rc = orbit_batch_solve<mdpvi::OrbitEval>(b, pi, V, tol, max_iter, s, nullptr, done, &n_left)))
+    return rc;
+  if (n_left < b->n) {
+    for (int i = 0; i < b->n; ++i) b->h_active[i] = done[i].iterations == 0;
+    HIP_TRY(hipMemcpyAsync(b->d_active[0], b->h_active, b->n * sizeof(int), hipMemcpyHostToDevice, s));
+  }
   double* W = static_cast<double*>(b->W2);
   const int opt = batch_opt(b, 1);
   EvalLists L = eval_lists(b, opt);
@@ -2428,7 +2910,8 @@ int policy_eval_batch(mdpvi_batch_t b, const uint8_t* pi, double* V, double tol,
       },
       [&](int64_t issued) {
         return mdpvi::launch_batch_eval_finish(b->d_inst, b->d_all, b->n, V, W, b->d_ctl, issued, b->d_out, s);
-      });
+      },
+      n_left < b->n ? b->d_active[0] : nullptr, n_left, &done);
 }
 
 int policy_iteration_batch(mdpvi_batch_t b, uint8_t* pi, double* V, double eval_tol, int64_t eval_max_iter,
@@ -2466,6 +2949,18 @@ int policy_iteration_batch(mdpvi_batch_t b, uint8_t* pi, double* V, double eval_
     for (int i = 0; i < n; ++i)
       if (b->h_active[i]) ++rr[i];
     mdpvi_stats e{};
+    std::vector<mdpvi::BatchOut> done(n, mdpvi::BatchOut{0, 0.0});
+    int n_left = n_active;
+    HIP_TRY(hipEventRecord(b->ev0, s));
+    if (orbit_batch_applies(b, eval_max_iter) &&
+        (rc = orbit_batch_solve<mdpvi::OrbitEval>(b, pi, V, eval_tol, eval_max_iter, s, b->d_active[a], done, &n_left)))
+      break;
+    const int* left = b->d_active[a];   // the instances evaluated by full sweeps
+    if (n_left < n_active) {
+      for (int i = 0; i < n; ++i) b->h_left[i] = b->h_active[i] && done[i].iterations == 0;
+      HIP_TRY(hipMemcpyAsync(b->d_left, b->h_left, n * sizeof(int), hipMemcpyHostToDevice, s));
+      left = b->d_left;
+    }
     if (L.n2) HIP_TRY(mdpvi::launch_batch_eval_arrival_init(b->d_inst, L.t2, L.n2, V, b->d_E[0], s));
     rc = batch_all_rounds(
         b, L.t, L.n, L.t2, L.n2, eval_tol, eval_max_iter, s, &e, nullptr, nullptr, 17.0,
@@ -2477,7 +2972,7 @@ int policy_iteration_batch(mdpvi_batch_t b, uint8_t* pi, double* V, double eval_
         [&](int64_t issued) {
           return mdpvi::launch_batch_eval_finish(b->d_inst, b->d_all, n, V, W, b->d_ctl, issued, b->d_out, s);
         },
-        b->d_active[a], n_active);
+        left, n_left, &done);
     tot.iterations += e.iterations;
     tot.residual_inf = std::max(tot.residual_inf, e.residual_inf);
     tot.bound_inf = std::max(tot.bound_inf, e.bound_inf);
@@ -2559,6 +3054,12 @@ int batch_set_round_form(mdpvi_batch_t b, int32_t op, int32_t opt) {
 int batch_round_forms(mdpvi_batch_t b, int32_t* opt) {
   if (!b || !opt) return fail(MDPVI_EINVAL, "NULL batch or output");
   for (int op = 0; op < 3; ++op) opt[op] = batch_opt(b, op);
+  return MDPVI_OK;
+}
+
+int batch_set_orbits(mdpvi_batch_t b, int32_t on) {
+  if (!b) return fail(MDPVI_EINVAL, "NULL batch");
+  b->orbits = on != 0;
   return MDPVI_OK;
 }
 

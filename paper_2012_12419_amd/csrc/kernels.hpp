@@ -4,6 +4,7 @@
 
 #include "batch.hpp"
 #include "model.hpp"
+#include "orbit.hpp"
 
 namespace mdpvi {
 
@@ -42,40 +43,67 @@ int slab_digits(const Model& M);
 // arrival-term arrays of n_occ doubles, the first set from the initial
 // iterate by launch_eval_arrival_init.
 struct TileShape;
-struct OrbitShape;
-struct OrbitParams;
-struct OrbitCtl;
 
-// Orbit form of value iteration (orbit.hip).  launch_orbit_table fills the
-// table behind S; launch_orbit_begin sets the control words, the orbits'
-// values Vr and arrival terms A0 from V and raises ctl->flag when V is not
-// invariant under host permutations (mirror: the control words' copy in pinned
-// host memory, written by the kernels); then either sweeps (grid orbit_grid,
-// res: kResSlots * kOrbitGrid doubles, sweep j reads V[j % 2], A[j % 2]) or
-// LDS-resident solves of up to `most` sweeps each (orbit_lds_bytes of
-// dynamic LDS); launch_orbit_expand writes the iterate of ctl->done (or of
+// Orbit form (orbit.hip; Op: OrbitVi or OrbitEval).  launch_orbit_table fills
+// the table behind S; launch_orbit_begin sets the control and residual words
+// and the orbits' start from V (and the policy pi) and raises the flag when
+// V or pi is not invariant under host permutations (mirror: the control
+// words' copy in pinned host memory, written by the kernels); then either
+// sweeps (orbit_grid workgroups; a chunk's sweeps i = 0.. and its end, or a
+// whole chunk recorded as a graph) or LDS-resident solves of up to `most`
+// sweeps each; launch_orbit_expand writes the iterate of ctl->done (or of
 // `issued` sweeps) to every state of V.
-hipError_t launch_orbit_table(const OrbitShape& S, const Model& M, uint64_t* dig, uint32_t* rep, void* tab,
+hipError_t launch_orbit_table(const OrbitShape& S, const OrbitParams& P, uint64_t* dig, uint32_t* rep, void* tab,
                               hipStream_t s);
-hipError_t launch_orbit_begin(const OrbitShape& S, const OrbitParams& P, const Model& M, const float* V, float* Vr,
-                              double* A0, double* A1, OrbitCtl* ctl, OrbitCtl* mirror, double* res, double tol,
-                              hipStream_t s);
+template <class Op>
+hipError_t launch_orbit_begin(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, const typename Op::T* V,
+                              const uint8_t* pi, double tol, OrbitCtl* mirror, hipStream_t s);
 uint32_t orbit_grid(const OrbitShape& S);
-// Sweep i of a chunk (i < kOrbitChunk), and the chunk's end (n sweeps);
-// build_orbit_chunk records a whole chunk as a graph.
-hipError_t launch_orbit_sweep(const OrbitShape& S, const OrbitParams& P, float* const V[2], double* const A[2],
-                              OrbitCtl* ctl, OrbitCtl* mirror, double* res, int i, hipStream_t s);
+template <class Op>
+hipError_t launch_orbit_sweep(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, OrbitCtl* mirror, int i,
+                              hipStream_t s);
 hipError_t launch_orbit_next(OrbitCtl* ctl, int n, hipStream_t s);
-hipError_t build_orbit_chunk(const OrbitShape& S, const OrbitParams& P, float* const V[2], double* const A[2],
-                             OrbitCtl* ctl, OrbitCtl* mirror, double* res, hipGraphExec_t* out);
-hipError_t launch_orbit_last_residual(const OrbitShape& S, const double* res, long long issued, const OrbitCtl* ctl,
-                                      OrbitCtl* mirror, hipStream_t s);
-size_t orbit_lds_bytes(const OrbitShape& S);
-hipError_t launch_orbit_lds(const OrbitShape& S, const OrbitParams& P, float* V0, float* V1, double* A0, double* A1,
-                            OrbitCtl* ctl, OrbitCtl* mirror, long long it0, long long most, double tol,
-                            hipStream_t s);
-hipError_t launch_orbit_expand(const OrbitShape& S, const Model& M, float* V, const float* V0, const float* V1,
-                               const OrbitCtl* ctl, long long issued, hipStream_t s);
+template <class Op>
+hipError_t build_orbit_chunk(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, OrbitCtl* mirror,
+                             hipGraphExec_t* out);
+hipError_t launch_orbit_last_residual(const OrbitShape& S, const OrbitWork& W, long long issued, OrbitCtl* mirror,
+                                      hipStream_t s);
+// Dynamic LDS of an LDS-resident solve whose values have `value` bytes.
+inline size_t orbit_lds_bytes(const OrbitShape& S, size_t value) {
+  return 2 * (static_cast<size_t>(S.n) + 1) * 8 + 2 * static_cast<size_t>(S.n) * S.L * value;
+}
+template <class Op>
+hipError_t launch_orbit_lds(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, OrbitCtl* mirror,
+                            long long it0, long long most, double tol, hipStream_t s);
+template <class Op>
+hipError_t launch_orbit_expand(const OrbitShape& S, const OrbitWork& W, typename Op::T* V, long long issued,
+                               hipStream_t s);
+
+// Orbit form of a batch (orbit_batch.hip).  slot: batch instance -> entry of
+// insts or -1; otiles: {entry, first orbit} of 256 orbits each; tiles: the
+// batch's tiles over every instance; active (nullable): instances to solve.
+// main_kernel: every listed instance has K <= 5 and J <= 4.
+hipError_t launch_orbit_batch_table(const OrbitInst* insts, const Tile* tiles, int n_tiles, hipStream_t s);
+template <class Op>
+hipError_t launch_orbit_batch_begin(const OrbitInst* insts, const int32_t* slot, const Tile* otiles, int n_otiles,
+                                    const Tile* tiles, int n_tiles, const typename Op::T* V, const uint8_t* pi,
+                                    const int* active, double tol, int* remaining, int n_remaining, hipStream_t s);
+template <class Op>
+hipError_t launch_orbit_batch_expand(const OrbitInst* insts, const int32_t* slot, const Tile* tiles, int n_tiles,
+                                     typename Op::T* V, long long issued, hipStream_t s);
+template <class Op>
+hipError_t launch_orbit_batch_lds(const OrbitInst* insts, const int32_t* list, int n_list, bool main_kernel,
+                                  bool small, size_t lds, long long it0, long long most, double tol, hipStream_t s);
+// A round over the first *n_tiles (at most most_tiles) tiles {entry,
+// workgroup of its grid}; the tiles still running after it.
+template <class Op>
+hipError_t launch_orbit_round(const OrbitInst* insts, const Tile* tiles, const int* n_tiles, int most_tiles,
+                              bool main_kernel, int* remaining, long long j, hipStream_t s);
+hipError_t launch_orbit_compact(const OrbitInst* insts, const Tile* in, const int* n_in, int most_in, Tile* out,
+                                int* n_out, hipStream_t s);
+hipError_t launch_orbit_set(int* p, int v, hipStream_t s);
+hipError_t launch_orbit_batch_residual(const OrbitInst* insts, const int32_t* list, int n_list, long long issued,
+                                       hipStream_t s);
 
 bool vi_tile_shape(const Model& M, TileShape* S);
 hipError_t launch_vi_tile(const Model& M, const TileShape& S, const float* Vin, float* Vout, const double* Ain,

@@ -1,297 +1,116 @@
-// orbit.hip -- kernels of the orbit form of value iteration (orbit.hpp): the
-// rank table, the check that a starting iterate is invariant under host
+// orbit.hip -- kernels of the orbit form (orbit.hpp) of one instance: the
+// rank table, the check that a start (and a policy) is invariant under host
 // permutations, sweeps over the orbits (one launch each, or all of them in
 // one workgroup's LDS) and the expansion to the full state space.
 //
-// Measured against the full sweeps of the same solve (to ||dV|| < 1e-6, wall
-// time): K = 6, C = 10, J = 3 47.5 -> 5.7 ms (31 -> 3.6 us per sweep); K = 7
-// 565 -> 7.2 ms (408 -> 4.5 us); K = 4, C = 12, J = 3 2.7 -> 1.7 ms; in LDS
-// K = 3, C = 8, J = 2 1.80 -> 0.17 ms (0.63 us per sweep).
+// Measured against the full sweeps of the same solve.  Value iteration to
+// ||dV|| < 1e-6, wall time: K = 6, C = 10, J = 3 47.5 -> 5.7 ms (31 -> 3.6 us
+// per sweep); K = 7 565 -> 7.2 ms (408 -> 4.5 us); K = 4, C = 12, J = 3 2.7 ->
+// 1.7 ms; in LDS K = 3, C = 8, J = 2 1.80 -> 0.17 ms (0.63 us per sweep).
+// Evaluation of the least-loaded heuristic to 1e-10: K = 6, C = 10, J = 3 94 ->
+// 8.2 ms (43 -> 3.6 us per sweep); in LDS K = 3, C = 8, J = 2 2.4 -> 0.24 ms.
 #include "kernels.hpp"
 #include "orbit.hpp"
+#include "orbit_impl.hpp"
 
 namespace mdpvi {
 
 // ------------------------------------------------------------------ table
 
-// One thread per orbit: unranks it and ranks the orbits its backup reads.
 template <int KX, typename Idx>
-__global__ __launch_bounds__(256) void orbit_table_kernel(OrbitShape S, const Model M, uint64_t* __restrict__ dig,
+__global__ __launch_bounds__(256) void orbit_table_kernel(OrbitShape S, OrbitParams P, uint64_t* __restrict__ dig,
                                                           uint32_t* __restrict__ rep, Idx* __restrict__ tab) {
   __shared__ uint32_t B[kOrbitBinom];
-  for (int i = threadIdx.x; i < S.K * S.R; i += blockDim.x) B[i] = S.binom[i];
-  __syncthreads();
+  orbit_stage_binom(S, B);
   const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= S.n) return;
-  const int K = S.K, R = S.R;
-  int n[KX];
-  uint32_t left = r;
-  int v = S.C;
-  uint64_t packed = 0;
-  uint64_t o = 0;
-#pragma unroll
-  for (int i = KX - 1; i >= 0; --i) {
-    n[i] = 0;
-    if (i < K) {
-      while (B[i * R + v] > left) --v;   // B[i R] = 0: ends at v = 0
-      left -= B[i * R + v];
-      n[i] = v;
-      packed |= static_cast<uint64_t>(v) << (S.dig_bits * i);
-      o += static_cast<uint64_t>(v) * static_cast<uint64_t>(M.stride[i]);
-    }
-  }
-  dig[r] = packed;
-  rep[r] = static_cast<uint32_t>(o);
-#pragma unroll
-  for (int k = 0; k < KX; ++k) {
-    if (k < K) {
-      // one unit less: the first position of the run of equal digits moves
-      int p = k;
-#pragma unroll
-      for (int i = KX - 1; i >= 0; --i)
-        if (i < k && n[i] == n[k]) p = i;
-      const uint32_t rel = n[k] > 0 ? r - B[p * R + n[k]] + B[p * R + n[k] - 1] : r;
-      tab[static_cast<size_t>(k) * S.n + r] = static_cast<Idx>(rel);
-      // emptied: the positions below k move up by one
-      uint32_t q = 0;
-#pragma unroll
-      for (int i = 0; i < KX; ++i) {
-        if (i < K && i < k) q += B[(i + 1) * R + n[i]];
-        if (i < K && i > k) q += B[i * R + n[i]];
-      }
-      tab[static_cast<size_t>(K + k) * S.n + r] = static_cast<Idx>(q);
-      // a class-e task placed: the positions above k with a smaller digit
-      // than the new one move down
-      for (int e = 0; e < S.J; ++e) {
-        const int w = n[k] + M.size[e];
-        uint32_t t = S.n;
-        if (w <= S.C) {
-          t = 0;
-          int at = k;
-#pragma unroll
-          for (int i = 0; i < KX; ++i) {
-            if (i < K && i != k) {
-              if (i > k && n[i] < w) {
-                t += B[(i - 1) * R + n[i]];
-                at = i;
-              } else {
-                t += B[i * R + n[i]];
-              }
-            }
-          }
-          t += B[at * R + w];
-        }
-        tab[static_cast<size_t>((2 + e) * K + k) * S.n + r] = static_cast<Idx>(t);
-      }
-    }
-  }
+  if (r < S.n) orbit_table<KX, Idx>(S, P, B, r, dig, rep, tab);
 }
 
 // ------------------------------------------------------------ start and end
 
-// The orbits' values and arrival terms from the representatives of V, the
-// -inf entries and the control words.
-__global__ __launch_bounds__(256) void orbit_begin_kernel(OrbitShape S, OrbitParams P, const float* __restrict__ V,
-                                                          float* __restrict__ Vr, double* __restrict__ A0,
-                                                          double* __restrict__ A1, OrbitCtl* ctl, double* res,
-                                                          double tol) {
+template <class Op>
+__global__ __launch_bounds__(256) void orbit_begin_kernel(OrbitShape S, OrbitParams P, OrbitWork W,
+                                                          const typename Op::T* __restrict__ V,
+                                                          const uint8_t* __restrict__ pi, double tol) {
   const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
   // the slot before the first sweep's holds one word that passes no test
   if (blockIdx.x == 0)
     for (uint32_t w = threadIdx.x; w < kResSlots * kOrbitGrid; w += blockDim.x)
-      res[w] = w == (kResSlots - 1) * kOrbitGrid ? INFINITY : 0.0;
+      W.res[w] = w == (kResSlots - 1) * kOrbitGrid ? INFINITY : 0.0;
   if (r == 0) {
-    ctl->done = -1;
-    ctl->flag = 0;
-    ctl->base = 0;
-    ctl->tol = tol;
-    A0[S.n] = -INFINITY;
-    A1[S.n] = -INFINITY;
+    W.ctl->done = -1;
+    W.ctl->flag = 0;
+    W.ctl->bad = 0;
+    W.ctl->base = 0;
+    W.ctl->tol = tol;
+    W.A[0][S.n] = -INFINITY;
+    W.A[1][S.n] = -INFINITY;
   }
-  if (r >= S.n) return;
-  const uint32_t o = S.rep[r];
-  double a = 0.0;
-  for (int e = 0; e < S.L; ++e) {
-    const float v = e < S.J ? V[o + static_cast<uint64_t>(e) * S.n_occ] : 0.0f;
-    Vr[r * static_cast<uint32_t>(S.L) + e] = v;
-    if (e < S.J) a = fma(P.p[e], static_cast<double>(v), a);
-  }
-  A0[r] = a;
+  if (r < S.n) orbit_begin<Op>(S, P, W, V, pi, r);
 }
 
-// Compares every state with its orbit's representative, bit for bit; raises
-// ctl->flag where one differs.
-template <int KX>
-__global__ __launch_bounds__(256) void orbit_check_kernel(OrbitShape S, FastDiv divR, const float* __restrict__ V,
-                                                          const float* __restrict__ Vr, OrbitCtl* ctl,
+// Every state against its orbit's representative.
+template <class Op, int KX>
+__global__ __launch_bounds__(256) void orbit_check_kernel(OrbitShape S, OrbitParams P, OrbitWork W,
+                                                          const typename Op::T* __restrict__ V,
+                                                          const uint8_t* __restrict__ pi, double delta,
                                                           OrbitCtl* mirror) {
   __shared__ uint32_t B[kOrbitBinom];
-  for (int i = threadIdx.x; i < S.K * S.R; i += blockDim.x) B[i] = S.binom[i];
-  __syncthreads();
-  bool bad = false;
+  orbit_stage_binom(S, B);
+  bool bad = false, infeasible = false;
   const uint64_t step = static_cast<uint64_t>(gridDim.x) * blockDim.x;
-  for (uint64_t o = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; o < S.n_occ; o += step) {
-    const uint32_t r = orbit_rank<KX>(S.K, S.R, divR, B, static_cast<uint32_t>(o));
-    for (int e = 0; e < S.J; ++e)
-      bad = bad || __float_as_uint(V[o + static_cast<uint64_t>(e) * S.n_occ]) !=
-                       __float_as_uint(Vr[r * static_cast<uint32_t>(S.L) + e]);
-  }
-  if (__ballot(bad) != 0 && threadIdx.x % kWave == 0) {
-    volatile long long* f = &ctl->flag;
-    if (*f == 0) {
-      *f = 1;
-      ctl->tol = NAN;   // no residual is >= NaN: every sweep stops
-      mirror->flag = 1;
-    }
-  }
+  for (uint64_t o = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; o < S.n_occ; o += step)
+    bad = orbit_differs<Op, KX>(S, P, W, B, V, pi, delta, static_cast<uint32_t>(o), infeasible) || bad;
+  const bool any = __ballot(bad || infeasible) != 0, inf = __ballot(infeasible) != 0;
+  if (any && threadIdx.x % kWave == 0) orbit_refuse(W.ctl, mirror, inf);
 }
 
 // V := the final iterate (ctl->done, or `issued` sweeps when none stopped the
-// loop) at every state; nothing when the form was refused.  Workgroup 0
-// records the index and the residual.
-template <int KX>
-__global__ __launch_bounds__(256) void orbit_expand_kernel(OrbitShape S, FastDiv divR, float* __restrict__ V,
-                                                           const float* __restrict__ V0,
-                                                           const float* __restrict__ V1, const OrbitCtl* ctl,
-                                                           long long issued) {
-  if (ctl->flag) return;
-  const long long done = ctl->done;
-  const float* __restrict__ Vr = ((done >= 0 ? done : issued) & 1) ? V1 : V0;
+// loop) at every state; nothing when the form was refused.
+template <class Op, int KX>
+__global__ __launch_bounds__(256) void orbit_expand_kernel(OrbitShape S, OrbitWork W,
+                                                           typename Op::T* __restrict__ V, long long issued) {
+  using T = typename Op::T;
+  if (W.ctl->flag) return;
+  const long long done = W.ctl->done;
+  const T* Vr = static_cast<const T*>(W.V[(done >= 0 ? done : issued) & 1]);
   __shared__ uint32_t B[kOrbitBinom];
-  for (int i = threadIdx.x; i < S.K * S.R; i += blockDim.x) B[i] = S.binom[i];
-  __syncthreads();
+  orbit_stage_binom(S, B);
   const uint64_t step = static_cast<uint64_t>(gridDim.x) * blockDim.x;
-  for (uint64_t o = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; o < S.n_occ; o += step) {
-    const uint32_t r = orbit_rank<KX>(S.K, S.R, divR, B, static_cast<uint32_t>(o));
-    for (int e = 0; e < S.J; ++e)
-      V[o + static_cast<uint64_t>(e) * S.n_occ] = Vr[r * static_cast<uint32_t>(S.L) + e];
-  }
+  for (uint64_t o = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; o < S.n_occ; o += step)
+    orbit_expand<T, KX>(S, B, Vr, V, static_cast<uint32_t>(o));
 }
 
 // ----------------------------------------------------------------- sweeps
 
-// One sweep over the orbits, L lanes per orbit (one per class), each
-// workgroup the orbits of its lanes and every grid-th such group after them.
-// A sweep of a few thousand orbits is bound by latency (8,008 orbits at
-// K = 6, C = 10 are two wavefronts per CU), so its loads form two dependent
-// steps only, table rows and then values, and nothing waits for the stop
-// test: the tolerance and the previous sweep's residual words are loaded
-// first, the backup runs, and only the stores wait for the verdict.  Every
-// workgroup leaves its largest |V' - V| in its own word of slot i mod 4; the
-// next sweep's workgroups each read all of them (at most kOrbitGrid).  A
-// stopped sweep passes the residual on, so that every later one stops too.
-//
-// i: the sweep's place in its chunk, known when the chunk is built; the chunk
-// starts after ctl->base sweeps, a multiple of kOrbitChunk, so that i alone
-// decides the buffers and the residual slot.  A small kernel after the chunk
-// moves base on.  A chunk is a recorded graph: issued one by one, the launches
-// are bound by the host (5.3 us each at 360 bytes of arguments); a graph node
-// with no work takes 2.0 us, the table rows 0.85, values and backup 0.7, the
-// verdict and the residual 0.2.
-template <int K, int L, typename Idx>
-__global__ __launch_bounds__(kOrbitBlock) void orbit_sweep_kernel(OrbitShape S, OrbitParams P, const float* Vin,
-                                                                  float* Vout, const double* Ain, double* Aout,
-                                                                  OrbitCtl* ctl, OrbitCtl* mirror, double* res,
-                                                                  uint32_t grid, int i) {
-  __shared__ double part[kOrbitBlock / kWave];
-  __shared__ int go[kOrbitBlock / kWave], bad[kOrbitBlock / kWave];
-  constexpr uint32_t kWords = kOrbitGrid / kOrbitBlock;
-  const BufView prev = make_view(res + static_cast<size_t>((i + kResSlots - 1) % kResSlots) * kOrbitGrid,
-                                 kOrbitGrid * 8u);
-  const double tol = load_agent(&ctl->tol);
-  double pw[kWords];
-#pragma unroll
-  for (uint32_t w = 0; w < kWords; ++w)
-    pw[w] = w * kOrbitBlock < grid ? ld_f64(prev, threadIdx.x * 8u, w * kOrbitBlock * 8u) : 0.0;
-  const int lane = threadIdx.x % kWave;
-  const int wid = threadIdx.x / kWave;
-  const uint32_t e = threadIdx.x % L;
-  const uint32_t ec = e < static_cast<uint32_t>(S.J) ? e : 0;
-  const double r_place = pick(P.r_place, ec, L), r_reject = pick(P.r_reject, ec, L);
-  const TabView<Idx> tab = tab_view<Idx>(S);
-  const F32View vin{make_view(Vin, S.n * L * 4u)};
-  const F64View ain{make_view(Ain, (S.n + 1) * 8u)};
-  const BufView dig{make_view(S.dig, S.n * 8u)};
-  const BufView vout = make_view(Vout, S.n * L * 4u), aout = make_view(Aout, S.n * 8u);
-  constexpr uint32_t per = kOrbitBlock / L;
-  double dmax = 0.0;
-  bool nan = false;
-  bool tested = false;
-  for (uint32_t base = blockIdx.x * per; base < S.n; base += grid * per) {
-    const uint32_t r = base + threadIdx.x / L;
-    const uint32_t rc = r < S.n ? r : S.n - 1;
-    OrbitIdx<K> x;
-    orbit_load_idx<K>(S, tab, rc, ec, x);
-    const uint64_t dg = __builtin_bit_cast(uint64_t, ld_f64(dig, rc * 8u, 0));
-    float own;
-    const float vn = orbit_backup<K, L>(S, x, dg, vin, ain, rc, ec, r_place, r_reject, P, own);
-    const double anew = orbit_arrival<L>(vn, S.J, P);
-    const double d = fabs(static_cast<double>(vn) - static_cast<double>(own));
-    nan = nan || d != d;
-    dmax = orbit_max(dmax, d);
-    if (!tested) {   // the verdict on the sweep before, once per workgroup
-      tested = true;
-      bool up = false, bd = false;
-#pragma unroll
-      for (uint32_t w = 0; w < kWords; ++w) {
-        up = up || pw[w] >= tol;
-        bd = bd || pw[w] != pw[w];
-      }
-      const bool wu = __ballot(up) != 0, wb = __ballot(bd) != 0;
-      if (lane == 0) {
-        go[wid] = wu;
-        bad[wid] = wb;
-      }
-      __syncthreads();
-      bool any = false, anyb = false;
-#pragma unroll
-      for (int w = 0; w < kOrbitBlock / kWave; ++w) {
-        any = any || go[w];
-        anyb = anyb || bad[w];
-      }
-      if (!any || anyb) {
-        // stopped: every word of this slot becomes the last residual
-        double pm = pw[0];
-#pragma unroll
-        for (uint32_t w = 1; w < kWords; ++w) pm = (pw[w] > pm || pw[w] != pw[w]) ? pw[w] : pm;
-        pm = wave_max(pm);
-        if (lane == 0) part[wid] = pm;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-#pragma unroll
-          for (int w = 0; w < kOrbitBlock / kWave; ++w) pm = (part[w] > pm || part[w] != part[w]) ? part[w] : pm;
-          res[static_cast<size_t>(i % kResSlots) * kOrbitGrid + blockIdx.x] = pm;
-          if (blockIdx.x == 0 && ctl->flag == 0 && ctl->done < 0) {
-            ctl->done = ctl->base + i;
-            mirror->residual = pm;
-            mirror->done = ctl->base + i;
-          }
-        }
-        return;
-      }
+// Sweep i of a chunk (orbit_sweep).  The chunk starts after ctl->base sweeps,
+// a multiple of kOrbitChunk, so that i alone decides the buffers and the
+// residual slot; a small kernel after the chunk moves base on.  A chunk is a
+// recorded graph: issued one by one, the launches are bound by the host (5.3
+// us each at 360 bytes of arguments); a graph node with no work takes 2.0 us,
+// the table rows 0.85, values and backup 0.7, the verdict and the residual
+// 0.2 (K = 6, C = 10, J = 3).
+template <class Op, int K, int L, typename Idx>
+__global__ __launch_bounds__(kOrbitBlock) void orbit_sweep_kernel(OrbitShape S, OrbitParams P, OrbitWork W,
+                                                                  OrbitCtl* mirror, uint32_t grid, int i) {
+  orbit_sweep<Op, K, L, Idx>(S, P, W, i, blockIdx.x, grid, [&](double residual) {
+    OrbitCtl* ctl = W.ctl;
+    if (ctl->flag == 0 && ctl->done < 0) {
+      ctl->done = ctl->base + i;
+      mirror->residual = residual;
+      mirror->done = ctl->base + i;
     }
-    if (r < S.n && e < static_cast<uint32_t>(S.J)) {
-      st_f32(vout, vn, (r * L + e) * 4u, 0);
-      if (e == 0) st_f64(aout, anew, r * 8u, 0);
-    }
-  }
-  dmax = wave_max_last(dmax);
-  const bool wn = __ballot(nan) != 0;
-  if (lane == kWave - 1) part[wid] = wn ? NAN : dmax;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double m = part[0];
-#pragma unroll
-    for (int w = 1; w < kOrbitBlock / kWave; ++w) m = (part[w] > m || part[w] != part[w]) ? part[w] : m;
-    res[static_cast<size_t>(i % kResSlots) * kOrbitGrid + blockIdx.x] = m;
-  }
+  });
 }
 
+// Moves the chunk's base on by n sweeps.
+__global__ void orbit_next_kernel(OrbitCtl* ctl, int n) { ctl->base += n; }
+
 // The residual of the last of `issued` sweeps when none stopped the loop.
-__global__ __launch_bounds__(256) void orbit_last_residual_kernel(const double* res, uint32_t grid, long long issued,
-                                                                  const OrbitCtl* ctl, OrbitCtl* mirror) {
+__global__ __launch_bounds__(256) void orbit_last_residual_kernel(OrbitWork W, uint32_t grid, long long issued,
+                                                                  OrbitCtl* mirror) {
   __shared__ double part[256 / kWave];
-  const double* w = res + static_cast<size_t>((issued - 1) % kResSlots) * kOrbitGrid;
+  const double* w = W.res + static_cast<size_t>((issued - 1) % kResSlots) * kOrbitGrid;
   double m = 0.0;
   for (uint32_t b = threadIdx.x; b < grid; b += 256) {
     const double v = w[b];
@@ -300,142 +119,27 @@ __global__ __launch_bounds__(256) void orbit_last_residual_kernel(const double* 
   m = wave_max(m);
   if (threadIdx.x % kWave == 0) part[threadIdx.x / kWave] = m;
   __syncthreads();
-  if (threadIdx.x == 0 && ctl->done < 0) {
+  if (threadIdx.x == 0 && W.ctl->done < 0) {
     for (int i = 1; i < 256 / kWave; ++i) m = (part[i] > m || part[i] != part[i]) ? part[i] : m;
     mirror->residual = m;
   }
 }
 
-// ------------------------------------------------------------- LDS solve
-
-// Up to `most` sweeps by one workgroup with both iterates and both arrays of
-// arrival terms in LDS: one barrier per sweep, no launch.  Lane t owns the
-// classes of orbits t / L, t / L + threads / L, ..; with HOIST the table
-// rows of its (at most HOIST) orbits stay in registers, else they are read
-// from the caches every sweep.  it0: sweeps done before this launch.
-template <int K, int L, int HOIST>
-__global__ __launch_bounds__(kOrbitLdsBlock) void orbit_lds_kernel(OrbitShape S, OrbitParams P, float* __restrict__ V0,
-                                                                   float* __restrict__ V1, double* __restrict__ A0,
-                                                                   double* __restrict__ A1, OrbitCtl* ctl,
-                                                                   OrbitCtl* mirror, long long it0, long long most, double tol) {
-  if (ctl->flag || ctl->done >= 0) return;
-  extern __shared__ double orbit_lds[];
-  __shared__ int up[3], bad[3];
-  __shared__ double part[kOrbitLdsBlock / kWave];
-  const TabView<uint16_t> tab = tab_view<uint16_t>(S);
-  const uint32_t n = S.n, na = n + 1;
-  double* Aa = orbit_lds;
-  double* Ab = Aa + na;
-  float* Va = reinterpret_cast<float*>(Ab + na);
-  float* Vb = Va + n * L;
-  const float* Vg = (it0 & 1) ? V1 : V0;
-  const double* Ag = (it0 & 1) ? A1 : A0;
-  for (uint32_t i = threadIdx.x; i < n * L; i += blockDim.x) {
-    Va[i] = Vg[i];
-    Vb[i] = 0.0f;
-  }
-  for (uint32_t i = threadIdx.x; i < na; i += blockDim.x) {
-    Aa[i] = Ag[i];
-    Ab[i] = -INFINITY;   // entry n stays -inf
-  }
-  if (threadIdx.x < 3) {
-    up[threadIdx.x] = 0;
-    bad[threadIdx.x] = 0;
-  }
-  const int lane = threadIdx.x % kWave;
-  const uint32_t e = threadIdx.x % L;
-  const uint32_t ec = e < static_cast<uint32_t>(S.J) ? e : 0;
-  const double r_place = pick(P.r_place, ec, L), r_reject = pick(P.r_reject, ec, L);
-  const uint32_t per = blockDim.x / L;
-  const uint32_t first = threadIdx.x / L;
-  constexpr int H = HOIST > 0 ? HOIST : 1;
-  OrbitIdx<K> hx[H];
-  uint64_t hd[H];
-  if constexpr (HOIST > 0) {
-#pragma unroll
-    for (int h = 0; h < HOIST; ++h) {
-      const uint32_t r = first + h * per;
-      const uint32_t rc = r < n ? r : n - 1;
-      orbit_load_idx<K>(S, tab, rc, ec, hx[h]);
-      hd[h] = S.dig[rc];
-    }
-  }
-  __syncthreads();
-  double dmax = 0.0;
-  long long it = 0;
-  bool stop = false;
-  int slot = 0;
-  while (it < most) {
-    dmax = 0.0;
-    bool nan = false;
-    auto one = [&](uint32_t r, uint32_t rc, const OrbitIdx<K>& x, uint64_t dig) {
-      float own;
-      const float vn = orbit_backup<K, L>(S, x, dig, LdsView<float>{Va}, LdsView<double>{Aa}, rc, ec, r_place, r_reject, P, own);
-      const double anew = orbit_arrival<L>(vn, S.J, P);
-      const double d = fabs(static_cast<double>(vn) - static_cast<double>(own));
-      dmax = orbit_max(dmax, d);
-      nan = nan || d != d;
-      if (r < n && e < static_cast<uint32_t>(S.J)) {
-        Vb[r * L + e] = vn;
-        if (e == 0) Ab[r] = anew;
-      }
-    };
-    if constexpr (HOIST > 0) {
-#pragma unroll
-      for (int h = 0; h < HOIST; ++h) {
-        const uint32_t r = first + h * per;
-        one(r, r < n ? r : n - 1, hx[h], hd[h]);
-      }
-    } else {
-      for (uint32_t base = 0; base < n; base += per) {
-        const uint32_t r = base + first;
-        const uint32_t rc = r < n ? r : n - 1;
-        OrbitIdx<K> x;
-        orbit_load_idx<K>(S, tab, rc, ec, x);
-        one(r, rc, x, S.dig[rc]);
-      }
-    }
-    if (nan) dmax = NAN;
-    if (__ballot(!(dmax < tol)) != 0 && lane == 0) up[slot] = 1;
-    if (__ballot(nan) != 0 && lane == 0) bad[slot] = 1;
-    __syncthreads();
-    const bool more = up[slot] != 0 && bad[slot] == 0;
-    ++it;
-    double* ta = Aa;
-    Aa = Ab;
-    Ab = ta;
-    float* tv = Va;
-    Va = Vb;
-    Vb = tv;
-    // the words of the sweep before this one, which every wavefront has read,
-    // are cleared for the sweep after the next
-    const int old = slot == 0 ? 2 : slot - 1;
-    if (threadIdx.x == 0) {
-      up[old] = 0;
-      bad[old] = 0;
-    }
-    slot = slot == 2 ? 0 : slot + 1;
-    if (!more) {
-      stop = true;
-      break;
-    }
-  }
-  dmax = wave_max(dmax);
-  if (lane == 0) part[threadIdx.x / kWave] = dmax;
-  float* Vo = ((it0 + it) & 1) ? V1 : V0;
-  double* Ao = ((it0 + it) & 1) ? A1 : A0;
-  for (uint32_t i = threadIdx.x; i < n * L; i += blockDim.x) Vo[i] = Va[i];
-  for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) Ao[i] = Aa[i];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double m = part[0];
-    for (uint32_t w = 1; w < blockDim.x / kWave; ++w) m = (part[w] > m || part[w] != part[w]) ? part[w] : m;
-    mirror->residual = m;
-    if (stop) {
-      ctl->done = it0 + it;
-      mirror->done = it0 + it;
-    }
-  }
+// The LDS-resident solve (orbit_lds).
+template <class Op, int K, int L, int HOIST>
+__global__ __launch_bounds__(kOrbitLdsBlock) void orbit_lds_kernel(OrbitShape S, OrbitParams P, OrbitWork W,
+                                                                   OrbitCtl* mirror, long long it0, long long most,
+                                                                   double tol) {
+  extern __shared__ double orbit_lds_mem[];
+  if (W.ctl->flag || W.ctl->done >= 0) return;
+  orbit_lds<Op, K, L, HOIST, kOrbitLdsBlock>(S, P, W, it0, most, tol, orbit_lds_mem,
+                                             [&](long long it, double residual, bool stopped) {
+                                               mirror->residual = residual;
+                                               if (stopped) {
+                                                 W.ctl->done = it;
+                                                 mirror->done = it;
+                                               }
+                                             });
 }
 
 // --------------------------------------------------------------- launchers
@@ -453,11 +157,11 @@ __global__ __launch_bounds__(kOrbitLdsBlock) void orbit_lds_kernel(OrbitShape S,
     default: CALL(16);          \
   }
 
-hipError_t launch_orbit_table(const OrbitShape& S, const Model& M, uint64_t* dig, uint32_t* rep, void* tab,
+hipError_t launch_orbit_table(const OrbitShape& S, const OrbitParams& P, uint64_t* dig, uint32_t* rep, void* tab,
                               hipStream_t s) {
   const uint32_t grid = (S.n + 255) / 256;
-#define MDPVI_CALL(KX_, T_)                                                                              \
-  hipLaunchKernelGGL((orbit_table_kernel<KX_, T_>), dim3(grid), dim3(256), 0, s, S, M, dig, rep, \
+#define MDPVI_CALL(KX_, T_)                                                                      \
+  hipLaunchKernelGGL((orbit_table_kernel<KX_, T_>), dim3(grid), dim3(256), 0, s, S, P, dig, rep, \
                      static_cast<T_*>(tab))
   if (S.wide) {
     if (S.K <= 4) MDPVI_CALL(4, uint32_t);
@@ -480,23 +184,24 @@ static uint32_t full_grid(const OrbitShape& S) {
   return static_cast<uint32_t>(g < 8192 ? g : 8192);
 }
 
-hipError_t launch_orbit_begin(const OrbitShape& S, const OrbitParams& P, const Model& M, const float* V, float* Vr,
-                              double* A0, double* A1, OrbitCtl* ctl, OrbitCtl* mirror, double* res, double tol,
-                              hipStream_t s) {
-  hipLaunchKernelGGL(orbit_begin_kernel, dim3((S.n + 255) / 256), dim3(256), 0, s, S, P, V, Vr, A0, A1, ctl, res,
-                     tol);
-#define MDPVI_CALL(KX_)                                                                                            \
-  hipLaunchKernelGGL((orbit_check_kernel<KX_>), dim3(full_grid(S)), dim3(256), 0, s, S, M.divR, V, \
-                     static_cast<const float*>(Vr), ctl, mirror)
+template <class Op>
+hipError_t launch_orbit_begin(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, const typename Op::T* V,
+                              const uint8_t* pi, double tol, OrbitCtl* mirror, hipStream_t s) {
+  hipLaunchKernelGGL((orbit_begin_kernel<Op>), dim3((S.n + 255) / 256), dim3(256), 0, s, S, P, W, V, pi, tol);
+  const double delta = 0.5 * tol;
+#define MDPVI_CALL(KX_)                                                                                      \
+  hipLaunchKernelGGL((orbit_check_kernel<Op, KX_>), dim3(full_grid(S)), dim3(256), 0, s, S, P, W, V, pi, delta, \
+                     mirror)
   MDPVI_ORBIT_K(S.K, MDPVI_CALL)
 #undef MDPVI_CALL
   return hipGetLastError();
 }
 
-hipError_t launch_orbit_expand(const OrbitShape& S, const Model& M, float* V, const float* V0, const float* V1,
-                               const OrbitCtl* ctl, long long issued, hipStream_t s) {
+template <class Op>
+hipError_t launch_orbit_expand(const OrbitShape& S, const OrbitWork& W, typename Op::T* V, long long issued,
+                               hipStream_t s) {
 #define MDPVI_CALL(KX_) \
-  hipLaunchKernelGGL((orbit_expand_kernel<KX_>), dim3(full_grid(S)), dim3(256), 0, s, S, M.divR, V, V0, V1, ctl, issued)
+  hipLaunchKernelGGL((orbit_expand_kernel<Op, KX_>), dim3(full_grid(S)), dim3(256), 0, s, S, W, V, issued)
   MDPVI_ORBIT_K(S.K, MDPVI_CALL)
 #undef MDPVI_CALL
   return hipGetLastError();
@@ -508,47 +213,44 @@ uint32_t orbit_grid(const OrbitShape& S) {
   return static_cast<uint32_t>(g < kOrbitGrid ? g : kOrbitGrid);
 }
 
-template <int K, typename Idx>
+template <class Op, int K, typename Idx>
 static const void* sweep_l(int L) {
   switch (L) {
-    case 1: return reinterpret_cast<const void*>(&orbit_sweep_kernel<K, 1, Idx>);
-    case 2: return reinterpret_cast<const void*>(&orbit_sweep_kernel<K, 2, Idx>);
-    case 4: return reinterpret_cast<const void*>(&orbit_sweep_kernel<K, 4, Idx>);
-    default: return reinterpret_cast<const void*>(&orbit_sweep_kernel<K, 8, Idx>);
+    case 1: return reinterpret_cast<const void*>(&orbit_sweep_kernel<Op, K, 1, Idx>);
+    case 2: return reinterpret_cast<const void*>(&orbit_sweep_kernel<Op, K, 2, Idx>);
+    case 4: return reinterpret_cast<const void*>(&orbit_sweep_kernel<Op, K, 4, Idx>);
+    default: return reinterpret_cast<const void*>(&orbit_sweep_kernel<Op, K, 8, Idx>);
   }
 }
 
+template <class Op>
 static const void* sweep_fn(const OrbitShape& S) {
   const void* f = nullptr;
-#define MDPVI_CALL(K_) f = S.wide ? sweep_l<K_, uint32_t>(S.L) : sweep_l<K_, uint16_t>(S.L)
+#define MDPVI_CALL(K_) f = S.wide ? sweep_l<Op, K_, uint32_t>(S.L) : sweep_l<Op, K_, uint16_t>(S.L)
   MDPVI_ORBIT_K(S.K, MDPVI_CALL)
 #undef MDPVI_CALL
   return f;
 }
 
-hipError_t launch_orbit_sweep(const OrbitShape& S, const OrbitParams& P, float* const V[2], double* const A[2],
-                              OrbitCtl* ctl, OrbitCtl* mirror, double* res, int i, hipStream_t s) {
+template <class Op>
+hipError_t launch_orbit_sweep(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, OrbitCtl* mirror, int i,
+                              hipStream_t s) {
   OrbitShape sh = S;
   OrbitParams pr = P;
-  const float* vin = V[i & 1];
-  float* vout = V[(i + 1) & 1];
-  const double* ain = A[i & 1];
-  double* aout = A[(i + 1) & 1];
+  OrbitWork w = orbit_work(W, i);
   uint32_t grid = orbit_grid(S);
-  void* args[] = {&sh, &pr, &vin, &vout, &ain, &aout, &ctl, &mirror, &res, &grid, &i};
-  return hipLaunchKernel(sweep_fn(S), dim3(grid), dim3(kOrbitBlock), args, 0, s);
+  void* args[] = {&sh, &pr, &w, &mirror, &grid, &i};
+  return hipLaunchKernel(sweep_fn<Op>(S), dim3(grid), dim3(kOrbitBlock), args, 0, s);
 }
-
-// Moves the chunk's base on by n sweeps (after the sweeps of the chunk).
-__global__ void orbit_next_kernel(OrbitCtl* ctl, int n) { ctl->base += n; }
 
 hipError_t launch_orbit_next(OrbitCtl* ctl, int n, hipStream_t s) {
   hipLaunchKernelGGL(orbit_next_kernel, dim3(1), dim3(1), 0, s, ctl, n);
   return hipGetLastError();
 }
 
-hipError_t build_orbit_chunk(const OrbitShape& S, const OrbitParams& P, float* const V[2], double* const A[2],
-                             OrbitCtl* ctl, OrbitCtl* mirror, double* res, hipGraphExec_t* out) {
+template <class Op>
+hipError_t build_orbit_chunk(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, OrbitCtl* mirror,
+                             hipGraphExec_t* out) {
   *out = nullptr;
   hipGraph_t g = nullptr;
   hipError_t e = hipGraphCreate(&g, 0);
@@ -558,15 +260,12 @@ hipError_t build_orbit_chunk(const OrbitShape& S, const OrbitParams& P, float* c
   uint32_t grid = orbit_grid(S);
   hipGraphNode_t node = nullptr;
   for (int i = 0; i <= kOrbitChunk && e == hipSuccess; ++i) {
-    const float* vin = V[i & 1];
-    float* vout = V[(i + 1) & 1];
-    const double* ain = A[i & 1];
-    double* aout = A[(i + 1) & 1];
-    void* args[] = {&sh, &pr, &vin, &vout, &ain, &aout, &ctl, &mirror, &res, &grid, &i};
+    OrbitWork w = orbit_work(W, i);
+    void* args[] = {&sh, &pr, &w, &mirror, &grid, &i};
     int n = kOrbitChunk;
-    void* last[] = {&ctl, &n};
+    void* last[] = {&w.ctl, &n};
     hipKernelNodeParams p{};
-    p.func = const_cast<void*>(i < kOrbitChunk ? sweep_fn(S) : reinterpret_cast<const void*>(&orbit_next_kernel));
+    p.func = const_cast<void*>(i < kOrbitChunk ? sweep_fn<Op>(S) : reinterpret_cast<const void*>(&orbit_next_kernel));
     p.gridDim = i < kOrbitChunk ? dim3(grid) : dim3(1);
     p.blockDim = i < kOrbitChunk ? dim3(kOrbitBlock) : dim3(1);
     p.kernelParams = i < kOrbitChunk ? args : last;
@@ -578,26 +277,20 @@ hipError_t build_orbit_chunk(const OrbitShape& S, const OrbitParams& P, float* c
   return e;
 }
 
-hipError_t launch_orbit_last_residual(const OrbitShape& S, const double* res, long long issued, const OrbitCtl* ctl,
-                                      OrbitCtl* mirror, hipStream_t s) {
-  hipLaunchKernelGGL(orbit_last_residual_kernel, dim3(1), dim3(256), 0, s, res, orbit_grid(S), issued, ctl,
-                     mirror);
+hipError_t launch_orbit_last_residual(const OrbitShape& S, const OrbitWork& W, long long issued, OrbitCtl* mirror,
+                                      hipStream_t s) {
+  hipLaunchKernelGGL(orbit_last_residual_kernel, dim3(1), dim3(256), 0, s, W, orbit_grid(S), issued, mirror);
   return hipGetLastError();
 }
 
-size_t orbit_lds_bytes(const OrbitShape& S) {
-  return 2 * (static_cast<size_t>(S.n) + 1) * 8 + 2 * static_cast<size_t>(S.n) * S.L * 4;
-}
-
-template <int K, int L>
-static void lds_h(const OrbitShape& S, const OrbitParams& P, float* V0, float* V1, double* A0, double* A1,
-                  OrbitCtl* ctl, OrbitCtl* mirror, long long it0, long long most, double tol, hipStream_t s) {
+template <class Op, int K, int L>
+static void lds_h(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, OrbitCtl* mirror, long long it0,
+                  long long most, double tol, hipStream_t s) {
   const uint32_t lanes = S.n * L;
   const uint32_t threads = lanes < kOrbitLdsBlock ? (lanes + kWave - 1) / kWave * kWave : kOrbitLdsBlock;
-  const size_t lds = orbit_lds_bytes(S);
-#define MDPVI_CALL(H_)                                                                                             \
-  hipLaunchKernelGGL((orbit_lds_kernel<K, L, H_>), dim3(1), dim3(threads), lds, s, S, P, V0, V1, A0, A1, ctl, mirror, \
-                     it0, most, tol)
+  const size_t lds = orbit_lds_bytes(S, sizeof(typename Op::T));
+#define MDPVI_CALL(H_)                                                                                         \
+  hipLaunchKernelGGL((orbit_lds_kernel<Op, K, L, H_>), dim3(1), dim3(threads), lds, s, S, P, W, mirror, it0, most, tol)
   // the table rows of more orbits, or of more hosts, would not fit the 128
   // registers that 16 wavefronts leave a lane
   if (K <= 8 && lanes <= threads) MDPVI_CALL((K <= 8 ? 1 : 0));
@@ -606,23 +299,38 @@ static void lds_h(const OrbitShape& S, const OrbitParams& P, float* V0, float* V
 #undef MDPVI_CALL
 }
 
-template <int K>
-static void lds_l(const OrbitShape& S, const OrbitParams& P, float* V0, float* V1, double* A0, double* A1,
-                  OrbitCtl* ctl, OrbitCtl* mirror, long long it0, long long most, double tol, hipStream_t s) {
+template <class Op, int K>
+static void lds_l(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, OrbitCtl* mirror, long long it0,
+                  long long most, double tol, hipStream_t s) {
   switch (S.L) {
-    case 1: lds_h<K, 1>(S, P, V0, V1, A0, A1, ctl, mirror, it0, most, tol, s); break;
-    case 2: lds_h<K, 2>(S, P, V0, V1, A0, A1, ctl, mirror, it0, most, tol, s); break;
-    case 4: lds_h<K, 4>(S, P, V0, V1, A0, A1, ctl, mirror, it0, most, tol, s); break;
-    default: lds_h<K, 8>(S, P, V0, V1, A0, A1, ctl, mirror, it0, most, tol, s);
+    case 1: lds_h<Op, K, 1>(S, P, W, mirror, it0, most, tol, s); break;
+    case 2: lds_h<Op, K, 2>(S, P, W, mirror, it0, most, tol, s); break;
+    case 4: lds_h<Op, K, 4>(S, P, W, mirror, it0, most, tol, s); break;
+    default: lds_h<Op, K, 8>(S, P, W, mirror, it0, most, tol, s);
   }
 }
 
-hipError_t launch_orbit_lds(const OrbitShape& S, const OrbitParams& P, float* V0, float* V1, double* A0, double* A1,
-                            OrbitCtl* ctl, OrbitCtl* mirror, long long it0, long long most, double tol, hipStream_t s) {
-#define MDPVI_CALL(K_) lds_l<K_>(S, P, V0, V1, A0, A1, ctl, mirror, it0, most, tol, s)
+template <class Op>
+hipError_t launch_orbit_lds(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, OrbitCtl* mirror,
+                            long long it0, long long most, double tol, hipStream_t s) {
+#define MDPVI_CALL(K_) lds_l<Op, K_>(S, P, W, mirror, it0, most, tol, s)
   MDPVI_ORBIT_K(S.K, MDPVI_CALL)
 #undef MDPVI_CALL
   return hipGetLastError();
 }
+
+#define MDPVI_ORBIT_OP(OP_)                                                                                         \
+  template hipError_t launch_orbit_begin<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&,              \
+                                              const OP_::T*, const uint8_t*, double, OrbitCtl*, hipStream_t);       \
+  template hipError_t launch_orbit_expand<OP_>(const OrbitShape&, const OrbitWork&, OP_::T*, long long,             \
+                                               hipStream_t);                                                        \
+  template hipError_t launch_orbit_sweep<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&, OrbitCtl*,   \
+                                              int, hipStream_t);                                                    \
+  template hipError_t build_orbit_chunk<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&, OrbitCtl*,    \
+                                             hipGraphExec_t*);                                                      \
+  template hipError_t launch_orbit_lds<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&, OrbitCtl*,     \
+                                            long long, long long, double, hipStream_t);
+MDPVI_ORBIT_OP(OrbitVi)
+MDPVI_ORBIT_OP(OrbitEval)
 
 }  // namespace mdpvi

@@ -1,13 +1,18 @@
-// orbit.hpp -- value iteration on the orbits of the host permutations.
+// orbit.hpp -- value iteration and fixed-policy evaluation on the orbits of
+// the host permutations.
 //
 // All hosts share one capacity and one set of rates, so permuting the hosts
-// maps the chain onto itself: an iterate that is invariant under host
-// permutations (V^0 = 0, any constant, any earlier solution) stays so, and a
-// Jacobi sweep needs one backup per orbit and class instead of one per state.
+// maps the chain onto itself.  Value iteration: an iterate that is invariant
+// under host permutations (V^0 = 0, any constant, any earlier solution) stays
+// so, and a Jacobi sweep needs one backup per orbit and class instead of one
+// per state.  Evaluation: so too where the policy's target load (the
+// occupancy of the host it places on, or none) is the same over each orbit;
+// which of several equally loaded hosts it names does not matter.
 // The orbits of the (C+1)^K occupancies are the multisets of K digits in
 // 0..C, binom(C+K, K) of them (8,008 against 1,771,561 at K = 6, C = 10).
-// Every sum of a backup is exact or independent of the host order
-// (stay_sum), so the orbit iterates are the full sweeps' bit for bit.
+// Value iteration's sums are exact or independent of the host order
+// (stay_sum), so its orbit iterates are the full sweeps' bit for bit;
+// evaluation's differ from them in the rounding of its FP64 sums.
 //
 // An orbit is named by its rank in the combinatorial number system: with
 // the digits ascending, n_0 <= .. <= n_{K-1},
@@ -20,6 +25,8 @@
 //                      -inf entry of the arrival terms, where it has no room)
 #pragma once
 
+#include <type_traits>
+
 #include "device.hpp"
 
 namespace mdpvi {
@@ -30,17 +37,30 @@ constexpr int kOrbitBlock = 128;               // threads of a sweep workgroup
 constexpr uint32_t kOrbitGrid = 1024;          // most workgroups of a sweep
 constexpr int kOrbitChunk = 32;                // sweeps of a chunk (a multiple of kResSlots)
 constexpr int kOrbitLdsBlock = 1024;           // most threads of an LDS-resident solve
-constexpr size_t kOrbitLds = 160 * 1024 - 2048;   // its dynamic LDS
+constexpr int kOrbitSmallBlock = 256;          // ... of a batch's instances of at most as many lanes
+constexpr int kOrbitBigBlock = 512;            // ... of its larger ones
+constexpr size_t kOrbitLds = 156 * 1024;       // its dynamic LDS (the kernels hold up to 4 KB more)
+
+// The two operations: the stored type of the iterates.
+struct OrbitVi {
+  using T = float;
+  static constexpr bool kEval = false;
+};
+struct OrbitEval {
+  using T = double;
+  static constexpr bool kEval = true;
+};
 
 // Control words of an orbit solve, in device memory and, as the host's copy,
 // in pinned host memory.
 struct OrbitCtl {
   long long done;      // -1 while running, else the index of the final iterate
-  double residual;     // its residual (the host's copy only)
-  long long flag;      // 1: the starting iterate is not invariant
+  double residual;     // its residual
+  long long flag;      // 1: the start or the policy is not invariant, or an action infeasible
+  long long bad;       // 1: an action is infeasible
   long long base;      // sweeps done before the chunk that runs (device copy)
   double tol;          // the stopping tolerance (device copy)
-  long long pad[11];
+  long long pad[10];
 };
 
 struct OrbitShape {
@@ -50,42 +70,89 @@ struct OrbitShape {
   int32_t wide;           // 1: table entries of 32 bits, 0: of 16
   uint32_t n;             // orbits
   uint64_t n_occ;
+  FastDiv divR;
   const uint32_t* binom;  // [K][C+1]: binom(v + i, i + 1)
   const uint64_t* dig;    // [n]: the ascending digits, packed
   const uint32_t* rep;    // [n]: the occupancy index of the representative
   const void* tab;        // [(2 + J) K][n]
 };
 
-// The parameters an orbit backup needs (a by-value kernel argument).
+// The parameters an orbit backup needs.
 struct OrbitParams {
   double p[kMaxJ], r_place[kMaxJ], r_reject[kMaxJ];
   double mu_L, nu_L, hold, gamma;
+  int32_t size[kMaxJ];
 };
 
+// The buffers of a solve.
+struct OrbitWork {
+  void* V[2];          // iterates [n][L]
+  double* A[2];        // their arrival terms [n + 1], the last -inf
+  uint32_t* act;       // evaluation [n][L]: rank the arrival leads to, top bit: placed on a host
+  int32_t* load;       // evaluation [n][L]: the policy's target load, -1 the paid cloud
+  double* res;         // residual words: kResSlots slots of kOrbitGrid
+  OrbitCtl* ctl;
+};
+
+// One instance of a batch (orbit_batch.hip).
+struct OrbitInst {
+  OrbitShape S;
+  OrbitParams P;
+  OrbitWork W;          // W.res: launched sweeps only
+  int64_t offset;       // its first state in the concatenated arrays
+  uint32_t grid;        // workgroups of its sweeps
+  int32_t inst;         // its index in the batch
+};
+
+// W as the sweep of (chunk) index i reads and writes it.
+__host__ __device__ inline OrbitWork orbit_work(const OrbitWork& W, long long i) {
+  OrbitWork w = W;
+  if (i & 1) {
+    w.V[0] = W.V[1];
+    w.V[1] = W.V[0];
+    w.A[0] = W.A[1];
+    w.A[1] = W.A[0];
+  }
+  return w;
+}
+
+// x[e] for a lane's e < L, x the same for the wavefront.  Every entry goes
+// through a scalar register and a select: indexed by lane, the parameters
+// would be kept in scratch memory.
 __device__ __forceinline__ double pick(const double (&x)[kMaxJ], int e, int L) {
-  double v = x[0];
+  double v = 0.0;
 #pragma unroll
-  for (int i = 1; i < kMaxJ; ++i)
-    if (i < L) v = e == i ? x[i] : v;
+  for (int i = 0; i < kMaxJ; ++i)
+    if (i < L) {
+      const long long b = __double_as_longlong(x[i]);
+      const unsigned lo = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(b)));
+      const unsigned hi = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)));
+      const double s = __longlong_as_double(static_cast<long long>(static_cast<unsigned long long>(hi) << 32 | lo));
+      v = e == i ? s : v;
+    }
   return v;
 }
 
-// Rank of the digits of occupancy o (KX hosts; KX = 16: any K up to 16, the
-// digits beyond K read as zero and sorted to the front).  B: the rank table
-// in LDS.
+// Digits of occupancy o (KX = K hosts, or 16 for any K up to 16: the digits
+// beyond K are zero).
 template <int KX>
-__device__ __forceinline__ uint32_t orbit_rank(int K, int R, FastDiv divR, const uint32_t* B, uint32_t o) {
-  int n[KX];
+__device__ __forceinline__ void orbit_digits(const OrbitShape& S, uint32_t o, int (&n)[KX]) {
 #pragma unroll
   for (int k = 0; k < KX; ++k) {
-    if (KX <= 8 || k < K) {
-      const uint32_t q = fast_div(o, divR);
-      n[k] = static_cast<int>(o - q * static_cast<uint32_t>(R));
+    if (KX <= 8 || k < S.K) {
+      const uint32_t q = fast_div(o, S.divR);
+      n[k] = static_cast<int>(o - q * static_cast<uint32_t>(S.R));
       o = q;
     } else {
       n[k] = 0;
     }
   }
+}
+
+// Rank of the digits n (sorted here; padding digits sort to the front).  B:
+// the rank table in LDS.
+template <int KX>
+__device__ __forceinline__ uint32_t orbit_rank(const OrbitShape& S, const uint32_t* B, int (&n)[KX]) {
 #pragma unroll
   for (int a = 0; a < KX - 1; ++a) {
 #pragma unroll
@@ -98,8 +165,8 @@ __device__ __forceinline__ uint32_t orbit_rank(int K, int R, FastDiv divR, const
   uint32_t r = 0;
 #pragma unroll
   for (int k = 0; k < KX; ++k) {
-    const int pos = KX <= 8 ? k : k - (KX - K);   // padding digits are zero and add nothing
-    if (KX <= 8 || pos >= 0) r += B[pos * R + n[k]];
+    const int pos = KX <= 8 ? k : k - (KX - S.K);   // padding digits are zero and add nothing
+    if (KX <= 8 || pos >= 0) r += B[pos * S.R + n[k]];
   }
   return r;
 }
@@ -120,38 +187,53 @@ template <typename Idx>
 __device__ __forceinline__ TabView<Idx> tab_view(const OrbitShape& S) {
   return {make_view(S.tab, static_cast<uint32_t>(sizeof(Idx)) * S.n * static_cast<uint32_t>((2 + S.J) * S.K))};
 }
-struct F32View {
+template <typename T>
+struct GlobalView {
   BufView v;
-  __device__ __forceinline__ float operator()(uint32_t i) const { return ld_f32(v, i * 4u, 0); }
+  __device__ __forceinline__ T operator()(uint32_t i) const {
+    if constexpr (sizeof(T) == 4)
+      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(v.r, i * 4u, 0, 0));
+    else
+      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(v.r, i * 8u, 0, 0));
+  }
 };
-struct F64View {
-  BufView v;
-  __device__ __forceinline__ double operator()(uint32_t i) const { return ld_f64(v, i * 8u, 0); }
-};
+template <typename T>
+__device__ __forceinline__ GlobalView<T> global_view(const void* p, uint32_t n) {
+  return {make_view(p, n * static_cast<uint32_t>(sizeof(T)))};
+}
 template <typename T>
 struct LdsView {
   const T* p;
   __device__ __forceinline__ T operator()(uint32_t i) const { return p[i]; }
 };
 
-// One lane's part of an orbit backup: class e of orbit r.  KX = K hosts, or
-// 16 for any K of 9..16 (the positions beyond K read the orbit itself with
-// weight 0 and the -inf entry).
-template <int KX>
+// What one lane's backup (class e of orbit r) reads.  KX = K hosts, or 16 for
+// any K of 9..16 (the positions beyond K read the orbit itself with weight 0
+// and the -inf entry).
+template <class Op, int KX>
 struct OrbitIdx {
-  uint32_t rel[KX], rst[KX], plc[KX];
+  uint32_t rel[KX], rst[KX];
+  uint32_t plc[Op::kEval ? 1 : KX];   // evaluation: the orbit's act word
+  uint64_t dig;
 };
 
-template <int KX, class Tab>
-__device__ __forceinline__ void orbit_load_idx(const OrbitShape& S, Tab tab, uint32_t r, int e, OrbitIdx<KX>& x) {
+template <class Op, int KX, class Tab>
+__device__ __forceinline__ void orbit_load_idx(const OrbitShape& S, Tab tab, GlobalView<uint64_t> dig,
+                                               GlobalView<uint32_t> act, uint32_t r, uint32_t e,
+                                               OrbitIdx<Op, KX>& x) {
   const int K = KX <= 8 ? KX : S.K;
-  const uint32_t rp = static_cast<uint32_t>(e * K) * S.n + r;
+  const uint32_t rp = e * static_cast<uint32_t>(K) * S.n + r;
 #pragma unroll
   for (int k = 0; k < KX; ++k) x.rel[k] = k < K ? tab(r, static_cast<uint32_t>(k) * S.n) : r;
+  if constexpr (Op::kEval) {
+    x.plc[0] = act(r * static_cast<uint32_t>(S.L) + e);
+  } else {
 #pragma unroll
-  for (int k = 0; k < KX; ++k) x.plc[k] = k < K ? tab(rp, static_cast<uint32_t>(2 * K + k) * S.n) : S.n;
+    for (int k = 0; k < KX; ++k) x.plc[k] = k < K ? tab(rp, static_cast<uint32_t>(2 * K + k) * S.n) : S.n;
+  }
 #pragma unroll
   for (int k = 0; k < KX; ++k) x.rst[k] = k < K ? tab(r, static_cast<uint32_t>(K + k) * S.n) : r;
+  x.dig = dig(r);
 }
 
 template <int KX>
@@ -166,66 +248,82 @@ __device__ __forceinline__ double orbit_max(double a, double b) {
   return r;
 }
 
-// The new value of (r, e): the arithmetic of backup_arrival (sweep_impl.hpp).
-template <int KX, int L, class VV, class AV>
-__device__ __forceinline__ float orbit_backup(const OrbitShape& S, const OrbitIdx<KX>& x, uint64_t dig, VV V, AV A,
-                                              uint32_t r, uint32_t e, double r_place, double r_reject,
-                                              const OrbitParams& P, float& own) {
+// The new value of (r, e).  Value iteration: the arithmetic of backup_arrival
+// (sweep_impl.hpp).
+template <class Op, int KX, int L, class VV, class AV>
+__device__ __forceinline__ typename Op::T orbit_backup(const OrbitShape& S, const OrbitIdx<Op, KX>& x, VV V, AV A,
+                                                       uint32_t r, uint32_t e, double r_place, double r_reject,
+                                                       const OrbitParams& P, typename Op::T& own) {
+  using T = typename Op::T;
+  constexpr int NA = Op::kEval ? 1 : KX;
   const int K = KX <= 8 ? KX : S.K;
   own = V(r * L + e);
-  const double a_rej = A(r);
-  float vd[KX], vr[KX];
-  double aa[KX];
+  T vd[KX], vr[KX];
+  double aa[NA], a_rej = 0.0;
 #pragma unroll
   for (int k = 0; k < KX; ++k) vd[k] = V(x.rel[k] * L + e);
+  if constexpr (Op::kEval) {
+    aa[0] = A(x.plc[0] & 0x7fffffffu);
+  } else {
+    a_rej = A(r);
 #pragma unroll
-  for (int k = 0; k < KX; ++k) aa[k] = A(x.plc[k]);
+    for (int k = 0; k < KX; ++k) aa[k] = A(x.plc[k]);
+  }
 #pragma unroll
   for (int k = 0; k < KX; ++k) vr[k] = V(x.rst[k] * L + e);
   int load = 0;
 #pragma unroll
-  for (int k = 0; k < KX; ++k) load += orbit_digit<KX>(dig, k);
+  for (int k = 0; k < KX; ++k) load += orbit_digit<KX>(x.dig, k);
   const double fu = static_cast<double>(S.K * S.C - load);   // free units
   double sum = fu * static_cast<double>(own), rs = 0.0, ab = aa[0];
 #pragma unroll
   for (int k = 0; k < KX; ++k)
-    sum = fma(static_cast<double>(orbit_digit<KX>(dig, k)), static_cast<double>(vd[k]), sum);
+    sum = fma(static_cast<double>(orbit_digit<KX>(x.dig, k)), static_cast<double>(vd[k]), sum);
 #pragma unroll
-  for (int k = 1; k < KX; ++k) ab = orbit_max(ab, aa[k]);
+  for (int k = 1; k < NA; ++k) ab = orbit_max(ab, aa[k]);
 #pragma unroll
   for (int k = 0; k < KX; ++k) rs += k < K ? static_cast<double>(vr[k]) : 0.0;
   const double D = fma(P.nu_L, rs, P.mu_L * sum);   // stay_sum
-  const double best = orbit_max(fma(P.gamma, a_rej, fma(-P.hold, fu, r_reject)),
-                                fma(P.gamma, ab, fma(-P.hold, fu, r_place)));
-  return static_cast<float>(fma(P.gamma, D, best));
-}
-
-// v of lane `e` of the group of L neighbouring lanes.
-template <int L, int E>
-__device__ __forceinline__ float group_lane(float v) {
-  if constexpr (L == 1) return v;
-  const int b = __float_as_int(v);
-  if constexpr (L == 2)
-    return __int_as_float(__builtin_amdgcn_mov_dpp(b, E == 0 ? 0xA0 : 0xF5, 0xf, 0xf, true));   // quad_perm
-  else if constexpr (L == 4)
-    return __int_as_float(__builtin_amdgcn_mov_dpp(b, 0x55 * E, 0xf, 0xf, true));
+  double best;
+  if constexpr (Op::kEval)
+    best = fma(P.gamma, ab, fma(-P.hold, fu, x.plc[0] >> 31 ? r_place : r_reject));
   else
-    return __shfl(v, (static_cast<int>(threadIdx.x) % kWave & ~(L - 1)) + E, kWave);
+    best = orbit_max(fma(P.gamma, a_rej, fma(-P.hold, fu, r_reject)), fma(P.gamma, ab, fma(-P.hold, fu, r_place)));
+  return static_cast<T>(fma(P.gamma, D, best));
 }
 
+// v of lane E of the group of L neighbouring lanes.
 template <int L, int E>
-__device__ __forceinline__ double arrival_chain(float vn, int J, const OrbitParams& P, double a) {
-  const float v = group_lane<L, E>(vn);
-  if (E < J) a = fma(P.p[E], static_cast<double>(v), a);
-  if constexpr (E + 1 < L) return arrival_chain<L, E + 1>(vn, J, P, a);
-  return a;
+__device__ __forceinline__ int group_lane_b32(int b) {
+  if constexpr (L == 2)
+    return __builtin_amdgcn_mov_dpp(b, E == 0 ? 0xA0 : 0xF5, 0xf, 0xf, true);   // quad_perm
+  else if constexpr (L == 4)
+    return __builtin_amdgcn_mov_dpp(b, 0x55 * E, 0xf, 0xf, true);
+  else
+    return __shfl(b, (static_cast<int>(threadIdx.x) % kWave & ~(L - 1)) + E, kWave);
+}
+template <int L, int E, typename T>
+__device__ __forceinline__ T group_lane(T v) {
+  if constexpr (L == 1) {
+    return v;
+  } else if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, group_lane_b32<L, E>(__builtin_bit_cast(int, v)));
+  } else {
+    const long long b = __builtin_bit_cast(long long, v);
+    const unsigned lo = static_cast<unsigned>(group_lane_b32<L, E>(static_cast<int>(b)));
+    const unsigned hi = static_cast<unsigned>(group_lane_b32<L, E>(static_cast<int>(b >> 32)));
+    return __builtin_bit_cast(T, static_cast<long long>(static_cast<unsigned long long>(hi) << 32 | lo));
+  }
 }
 
 // The arrival term of an orbit from the new values of its lanes: the FMA
 // chain of backup_arrival.
-template <int L>
-__device__ __forceinline__ double orbit_arrival(float vn, int J, const OrbitParams& P) {
-  return arrival_chain<L, 0>(vn, J, P, 0.0);
+template <int L, int E = 0, typename T>
+__device__ __forceinline__ double orbit_arrival(T vn, int J, const OrbitParams& P, double a = 0.0) {
+  const T v = group_lane<L, E>(vn);
+  if (E < J) a = fma(P.p[E], static_cast<double>(v), a);
+  if constexpr (E + 1 < L) return orbit_arrival<L, E + 1>(vn, J, P, a);
+  return a;
 }
 
 // Largest of the wavefront's v (not NaN) in lane 63: row shifts, then the

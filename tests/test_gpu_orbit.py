@@ -30,7 +30,8 @@ def _inst(K, C, J, **kw):
 # byte packs and beyond (4-bit digits, 16-host loops); launched sweeps of one
 # group per workgroup; 32-bit table entries
 SHAPES = [(1, 1, 1), (1, 40, 3), (2, 9, 2), (2, 60, 1), (3, 5, 8), (4, 6, 5), (5, 5, 1), (5, 6, 3), (6, 4, 2),
-          (8, 2, 2), (8, 3, 3), (9, 2, 2), (16, 1, 1), (12, 1, 1), (5, 9, 2), (4, 12, 3), (6, 7, 4)]
+          (8, 2, 2), (8, 3, 3), (9, 2, 2), (16, 1, 1), (12, 1, 1), (5, 9, 2), (4, 12, 3), (6, 7, 4),
+          (2, 46, 3)]   # the most LDS of an evaluation in one workgroup
 
 
 def _solve(mdpvi, p, form, V0, tol, max_iter=1_000_000):
@@ -114,3 +115,170 @@ def test_one_handle_many_calls(mdpvi):
             mdp.vi_solve(V, tol=1e-6, stream=side)
         torch.cuda.current_stream().wait_stream(side)
         assert torch.equal(V.view(torch.int32), ref.view(torch.int32)), k
+
+
+# ------------------------------------------------------------- evaluation
+#
+# The orbit sweeps and the full ones form the same FP64 sums in another
+# order: per sweep at most 4 K + 8 roundings of 2^-53 of the largest value
+# differ, and the sweeps contract by gamma, so the iterates stay within
+# 2 (4 K + 8) 2^-53 / (1 - gamma) of each other relative to it.
+
+
+def _eval_tol(p):
+    return 2 * (4 * p.K + 8) * 2.0 ** -53 / (1 - p.gamma)
+
+
+def _evaluate(mdpvi, p, orbits, pi, V0=None, tol=1e-10, max_iter=1_000_000, form=-1):
+    import torch
+    mdp = mdpvi.MDP.from_instance(p)
+    mdp.set_orbits(orbits)
+    mdp.set_sweep_form(form)
+    V = torch.zeros(p.num_states, dtype=torch.float64, device="cuda") if V0 is None else V0.clone()
+    try:
+        _, st = mdp.policy_eval(pi, V, tol=tol, max_iter=max_iter)
+        code = 0
+    except mdpvi.MdpviError as e:
+        st, code = e.stats, e.code
+    return V, st, code
+
+
+@pytest.mark.parametrize("K,C,J", SHAPES)
+@pytest.mark.parametrize("costs", [False, True])
+def test_evaluation_near_full_sweeps(mdpvi, K, C, J, costs):
+    kw = dict(reject_cost=[0.2 + 0.1 * j for j in range(J)], idle_unit_cost=0.03) if costs else {}
+    p = _inst(K, C, J, **kw)
+    pi = mdpvi.MDP.from_instance(p).policy_greedy("least_loaded")
+    for tol, most in ((1e-10, 1_000_000), (1e-30, 33), (1e-30, 64)):
+        a, sa, ca = _evaluate(mdpvi, p, False, pi, tol=tol, max_iter=most)
+        b, sb, cb = _evaluate(mdpvi, p, True, pi, tol=tol, max_iter=most)
+        assert ca == cb and abs(sa["iterations"] - sb["iterations"]) <= 1
+        slack = (sa["residual_inf"] + sb["residual_inf"]) if sa["iterations"] != sb["iterations"] else 0.0
+        scale = float(a.abs().max())
+        assert float((a - b).abs().max()) <= _eval_tol(p) * scale + slack
+
+
+@pytest.mark.parametrize("K,C,J", [(3, 8, 2), (5, 9, 2)])
+def test_evaluation_of_other_policies_and_starts(mdpvi, K, C, J):
+    """Equal loads may be named by any host; a policy whose target load
+    depends on the order of the hosts, and a start beyond tol/2 of an
+    invariant one, take the full sweeps (the bits of the form switched off);
+    an infeasible action is reported from either kind of policy."""
+    import torch
+    p = _inst(K, C, J)
+    mdp = mdpvi.MDP.from_instance(p)
+    ll, ff = mdp.policy_greedy("least_loaded"), mdp.policy_greedy("first_fit")
+    n_occ, R = (C + 1) ** K, C + 1
+    o = torch.arange(n_occ, device="cuda")
+    digits = torch.stack([o // R ** k % R for k in range(K)])
+    # the highest-index host of the same load
+    other = ll.clone().reshape(J, n_occ).long()
+    for e in range(J):
+        want = torch.where(other[e] < K, digits.gather(0, other[e].clamp(max=K - 1)[None])[0], torch.full_like(o, -1))
+        for k in range(K):
+            other[e] = torch.where((other[e] < K) & (digits[k] == want), torch.full_like(other[e], k), other[e])
+    other = other.reshape(-1).to(torch.uint8)
+    assert not torch.equal(other, ll)
+    a, _, _ = _evaluate(mdpvi, p, True, ll)
+    b, _, _ = _evaluate(mdpvi, p, True, other)
+    assert torch.equal(a, b)   # the same orbit equations
+    c, _, _ = _evaluate(mdpvi, p, False, other)
+    assert float((a - c).abs().max()) <= _eval_tol(p) * float(a.abs().max())
+    one_off = ll.clone()
+    one_off[1] = K             # (1, 0, ..): the paid cloud there only, of its orbit
+    V1 = a + 1e-12 * torch.rand_like(a)
+    V2 = a.clone()
+    V2[p.num_states - 2] += 1e-9
+    for pi, V0 in ((ff, None), (one_off, None), (ll, V2)):
+        x, sx, _ = _evaluate(mdpvi, p, True, pi, V0)
+        y, sy, _ = _evaluate(mdpvi, p, False, pi, V0)
+        assert torch.equal(x, y) and sx["iterations"] == sy["iterations"]
+    x, _, _ = _evaluate(mdpvi, p, True, ll, V1)   # within tol/2: starts at the representatives' values
+    assert float((x - a).abs().max()) <= 2e-10 * p.gamma / (1 - p.gamma)
+    for pi in (ll, ff):
+        bad = pi.clone()
+        bad[-1] = 0            # every host full
+        assert _evaluate(mdpvi, p, True, bad)[2] == mdpvi.EINVAL
+        bad[-1] = K + 1
+        assert _evaluate(mdpvi, p, True, bad)[2] == mdpvi.EINVAL
+    V0 = torch.zeros_like(a)
+    V0[7] = float("nan")
+    assert _evaluate(mdpvi, p, True, ll, V0)[2] == mdpvi.ENAN
+
+
+@pytest.mark.parametrize("K,C,J", [(4, 9, 3), (5, 10, 2), (8, 3, 2)])
+def test_full_evaluation_forms_same_bits(mdpvi, K, C, J):
+    """The full sweeps of an evaluation in the direct and the tile forms give
+    the same bits, for a policy that depends on the order of the hosts and,
+    with the orbit form off, for one that does not."""
+    import torch
+    p = _inst(K, C, J)
+    mdp = mdpvi.MDP.from_instance(p)
+    for kind, orbits in (("first_fit", True), ("least_loaded", False)):
+        pi = mdp.policy_greedy(kind)
+        ref, sr, _ = _evaluate(mdpvi, p, orbits, pi, form=0)
+        for form in (mdpvi.FORM_TILE, mdpvi.FORM_TILE + 2, -1):
+            got, sg, _ = _evaluate(mdpvi, p, orbits, pi, form=form)
+            assert sg["iterations"] == sr["iterations"] and torch.equal(got, ref), (kind, form)
+
+
+# ------------------------------------------------------------------ batches
+
+
+def _batch_insts():
+    shapes = [(1, 6, 2), (2, 9, 2), (3, 5, 5), (4, 6, 3), (5, 6, 3), (5, 10, 3), (4, 12, 3), (5, 12, 1), (6, 4, 2),
+              (8, 2, 2), (9, 1, 1), (3, 12, 3), (5, 10, 2)]
+    return [_inst(*s, gamma=0.85 + 0.01 * k) for k, s in enumerate(shapes)]
+
+
+def test_batch_same_as_single(mdpvi):
+    """Batched value iteration, evaluation and policy iteration with some
+    instances on their orbits (LDS-resident ones and rounds, both kernels) and
+    some refused: per instance the single-instance bits and sweep counts."""
+    import torch
+    insts = _batch_insts()
+    b = mdpvi.Batch(insts)
+    off = b.offsets
+    V0 = torch.zeros(b.num_states, device="cuda")
+    for i in (2, 6, 11):   # starts that are not invariant
+        V0[off[i] + 1] = 0.25
+    for tol, most in ((1e-6, 1_000_000), (1e-30, 45)):
+        V = V0.clone()
+        try:
+            _, its, res = b.vi_solve(V, tol=tol, max_iter=most)
+        except mdpvi.MdpviError as e:
+            assert e.code == mdpvi.ENOCONV
+            its = None
+        for i, p in enumerate(insts):
+            one, st, _ = _solve(mdpvi, p, -1, V0[off[i]:off[i + 1]], tol, most)
+            assert torch.equal(one.view(torch.int32), V[off[i]:off[i + 1]].view(torch.int32)), (i, most)
+            assert its is None or (its[i] == st["iterations"] and res[i] == st["residual_inf"])
+    pi = b.policy_greedy("least_loaded")
+    ff = b.policy_greedy("first_fit")
+    for i in (0, 4, 5):
+        pi[off[i]:off[i + 1]] = ff[off[i]:off[i + 1]]
+    Ve, _, its, res = b.policy_eval(pi, tol=1e-10)
+    Vp, pp = Ve.clone(), pi.clone()
+    _, rounds = b.policy_iteration(pp, Vp, eval_tol=1e-10, improve_tol=1e-8)
+    for i, p in enumerate(insts):
+        sl = slice(off[i], off[i + 1])
+        one, st, _ = _evaluate(mdpvi, p, True, pi[sl].contiguous())
+        assert torch.equal(one, Ve[sl]) and its[i] == st["iterations"] and res[i] == st["residual_inf"], i
+        mdp = mdpvi.MDP.from_instance(p)
+        p1, V1 = pi[sl].clone(), Ve[sl].clone()
+        _, _, _, r1 = mdp.policy_iteration(p1, V1, eval_tol=1e-10, improve_tol=1e-8)
+        assert r1 == rounds[i] and torch.equal(p1, pp[sl]) and torch.equal(V1, Vp[sl]), i
+
+
+def test_batch_orbits_off_same_bits(mdpvi):
+    import torch
+    insts = _batch_insts()
+    b = mdpvi.Batch(insts)
+    outs = []
+    for on in (True, False):
+        b.set_orbits(on)
+        V = torch.zeros(b.num_states, device="cuda")
+        _, its, res = b.vi_solve(V, tol=1e-6)
+        outs.append((V, its, res))
+    assert torch.equal(outs[0][0].view(torch.int32), outs[1][0].view(torch.int32))
+    assert outs[0][1] == outs[1][1] and outs[0][2] == outs[1][2]
