@@ -132,6 +132,15 @@ hipError_t launch_extract_f32(const Model& M, const float* V, uint8_t* pi, float
 hipError_t launch_extract_f64(const Model& M, const double* V, uint8_t* pi, float* gap,
                               hipStream_t s);
 
+// The tile form of the extraction (extract_tile.hpp), taken by the two
+// launchers above where it applies.
+bool extract_tile_shape_f32(const Model& M, TileShape* S);
+bool extract_tile_shape_f64(const Model& M, TileShape* S);
+hipError_t launch_extract_tile_f32(const Model& M, const TileShape& S, const float* V, uint8_t* pi, float* gap,
+                                   hipStream_t s);
+hipError_t launch_extract_tile_f64(const Model& M, const TileShape& S, const double* V, uint8_t* pi, float* gap,
+                                   hipStream_t s);
+
 // ctl->flag := 1 if some pi entry is not a feasible action.
 hipError_t launch_policy_check(const Model& M, const uint8_t* pi, Ctl* ctl, hipStream_t s);
 // Policy improvement: pi_out = pi_in where no action beats the current one's

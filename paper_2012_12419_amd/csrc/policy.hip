@@ -8,6 +8,7 @@
 #include "device.hpp"
 #include "kernels.hpp"
 #include "policy_impl.hpp"
+#include "tile.hpp"
 
 #include <type_traits>
 
@@ -176,11 +177,15 @@ static hipError_t launch_extract_t(const Model& M, const T* V, uint8_t* pi, floa
 
 hipError_t launch_extract_f32(const Model& M, const float* V, uint8_t* pi, float* gap,
                               hipStream_t s) {
+  TileShape S{};
+  if (extract_tile_shape_f32(M, &S)) return launch_extract_tile_f32(M, S, V, pi, gap, s);
   return launch_extract_t<float>(M, V, pi, gap, s);
 }
 
 hipError_t launch_extract_f64(const Model& M, const double* V, uint8_t* pi, float* gap,
                               hipStream_t s) {
+  TileShape S{};
+  if (extract_tile_shape_f64(M, &S)) return launch_extract_tile_f64(M, S, V, pi, gap, s);
   return launch_extract_t<double>(M, V, pi, gap, s);
 }
 
