@@ -143,9 +143,11 @@ __device__ __forceinline__ void block_max_to(double v, Ctl* ctl, double* res, lo
 }
 
 // End of a 1-norm sweep: the workgroup's sum of |w' - w| is added to its
-// residual word.
+// residual word.  NB = kAnyBlock: of any number of wavefronts.
+constexpr int kAnyBlock = 1024;
+template <int NB = kBlock>
 __device__ __forceinline__ void block_sum_to(double v, double* res, long long j) {
-  __shared__ double part[kBlock / kWave];
+  __shared__ double part[NB / kWave];
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
   const int lane = threadIdx.x % kWave;
@@ -153,9 +155,10 @@ __device__ __forceinline__ void block_sum_to(double v, double* res, long long j)
   if (lane == 0) part[wid] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
+    const int waves = NB == kAnyBlock ? static_cast<int>(blockDim.x) / kWave : NB / kWave;
     double m = 0.0;
 #pragma unroll
-    for (int w = 0; w < kBlock / kWave; ++w) m += part[w];
+    for (int w = 0; w < waves; ++w) m += part[w];
     if (m != 0.0) atomicAdd(res + sum_word(j, blockIdx.x % kResLanes), m);
   }
 }

@@ -240,3 +240,34 @@ def test_adjoint_form_rejected_where_it_does_not_apply(mdpvi):
     assert big_c.adjoint_form() == mdpvi.ADJOINT_EXACT + 1
     with pytest.raises(mdpvi.MdpviError):
         big_c.set_adjoint_form(3)
+
+
+# the group form's edges: one group in all but one digit, the loads of a reset
+# line (5, 7, 9, 11 and 16 of them, none or some past C), teams of one
+# wavefront and of the most lanes, several zero high digits
+GROUP_SHAPES = [(3, 1, 1), (3, 2, 2), (4, 4, 3), (3, 5, 3), (4, 6, 2), (3, 7, 3), (4, 8, 3), (3, 9, 1), (3, 10, 3),
+                (3, 11, 3), (3, 15, 3), (7, 3, 3), (8, 2, 1)]
+
+
+@pytest.mark.parametrize("K,C,J", GROUP_SHAPES)
+def test_group_form_is_the_exact_form(mdpvi, K, C, J):
+    """Same w bit for bit at every stopping point."""
+    import torch
+    J = min(J, C)
+    inst = W.make(K, C, tuple(range(1, J + 1)), tuple(0.9 / (1 + j) for j in range(J)), 0.1, 0.03,
+                  tuple(1.1 * (1 + j) for j in range(J)), 0.95)
+    mdp = mdpvi.MDP.from_instance(inst)
+    pi = mdp.policy_greedy("first_fit")
+    Vp = torch.zeros(mdp.num_states, dtype=torch.float64, device="cuda")
+    for tol, most in ((1e-9, 100000), (1e-300, 1), (1e-300, 8), (1e-300, 9)):
+        got = []
+        for form in (mdpvi.ADJOINT_GROUP, mdpvi.ADJOINT_EXACT + 1):
+            mdp.set_adjoint_form(form)
+            w = torch.zeros(mdp.num_states, device="cuda")
+            try:
+                its = mdp.vi_adjoint(pi, Vp, w=w, tol=tol, max_iter=most)[3]["iterations"]
+            except mdpvi.MdpviError as err:
+                its = err.stats["iterations"]
+            got.append((its, w.cpu().numpy().view(np.uint32).copy()))
+        assert got[0][0] == got[1][0], (tol, most, got[0][0], got[1][0])
+        assert np.array_equal(got[0][1], got[1][1]), (tol, most)
