@@ -55,6 +55,7 @@ struct mdpvi_mdp {
   uint8_t* pbuf = nullptr;      // policy scratch (policy iteration), N + 16 bytes
   double* abuf = nullptr;       // two FP64 arrival-term arrays of n_occ + kSentinel doubles
                                 // (exact-shape direct and tile forms)
+  Model* d_model = nullptr;     // M in device memory
   Ctl* ctl = nullptr;           // device control words
   Ctl* ctl_host = nullptr;      // pinned mirror
   double* res = nullptr;        // residual words / per-workgroup partials
@@ -113,6 +114,13 @@ int ensure_scratch(mdpvi_mdp* h, size_t bytes) {
   if (h->device >= 0 && h->device != dev)
     return fail(MDPVI_EINVAL, "handle scratch lives on device %d, current device is %d", h->device,
                 dev);
+  if (!h->d_model) {
+    if (hipMalloc(reinterpret_cast<void**>(&h->d_model), sizeof(Model)) != hipSuccess) {
+      h->d_model = nullptr;
+      return fail(MDPVI_ENOMEM, "hipMalloc of %zu model bytes failed", sizeof(Model));
+    }
+    HIP_TRY(hipMemcpy(h->d_model, &h->M, sizeof(Model), hipMemcpyHostToDevice));
+  }
   if (!h->ctl) {
     if (hipMalloc(&h->ctl, sizeof(Ctl)) != hipSuccess) {
       h->ctl = nullptr;
@@ -1054,6 +1062,7 @@ void mdp_free(mdpvi_mdp_t h) {
   if (h->vbuf) (void)hipFree(h->vbuf);
   if (h->abuf) (void)hipFree(h->abuf);
   if (h->pbuf) (void)hipFree(h->pbuf);
+  if (h->d_model) (void)hipFree(h->d_model);
   if (h->ctl) (void)hipFree(h->ctl);
   if (h->ctl_host) (void)hipHostFree(h->ctl_host);
   if (h->res) (void)hipFree(h->res);
@@ -1271,9 +1280,9 @@ int mdp_autotune(mdpvi_mdp_t h, const float* V, int32_t trials, void* hip_stream
       auto sweep = [&]() -> hipError_t {
         if (is_tile_form(form)) {
           mdpvi::tile_set_walkers(&Se, form - MDPVI_FORM_TILE, cu_count());
-          return mdpvi::launch_eval_tile(M, Se, pol, ev[0], ev[1], Ae[0], Ae[1], h->ctl, h->res, 0, 1.0, s);
+          return mdpvi::launch_eval_tile(M, h->d_model, Se, pol, ev[0], ev[1], Ae[0], Ae[1], h->ctl, h->res, 0, 1.0, s);
         }
-        return mdpvi::launch_eval_sweep(M, pol, ev[0], ev[1], h->ctl, h->res, 0, 1.0, s);
+        return mdpvi::launch_eval_sweep(M, h->d_model, pol, ev[0], ev[1], h->ctl, h->res, 0, 1.0, s);
       };
       double us = 0.0;
       int trc = time_form(sweep, &us);
@@ -1292,7 +1301,7 @@ int mdp_autotune(mdpvi_mdp_t h, const float* V, int32_t trials, void* hip_stream
         int orc = set_tile_order(h, &Se, eval_working_set(M), "eval", code);
         if (orc) return orc;
         auto sweep = [&]() -> hipError_t {
-          return mdpvi::launch_eval_tile(M, Se, pol, ev[0], ev[1], Ae[0], Ae[1], h->ctl, h->res, 0, 1.0, s);
+          return mdpvi::launch_eval_tile(M, h->d_model, Se, pol, ev[0], ev[1], Ae[0], Ae[1], h->ctl, h->res, 0, 1.0, s);
         };
         double us = 0.0;
         int trc = time_form(sweep, &us);
@@ -1651,7 +1660,7 @@ int eval_run(mdpvi_mdp* h, const uint8_t* pi, double* V, double tol, int64_t max
     return run_loop<double>(h, V, tol, max_iter, s, st, 17.0 * M.n_states,
                             static_cast<double>(M.n_states),
                             [&](long long j, double* in, double* out) {
-                              return mdpvi::launch_eval_tile(M, S, pi, in, out, A[j & 1], A[(j + 1) & 1],
+                              return mdpvi::launch_eval_tile(M, h->d_model, S, pi, in, out, A[j & 1], A[(j + 1) & 1],
                                                              h->ctl, h->res, j, tol, s);
                             },
                             false, S.grid);
@@ -1659,7 +1668,7 @@ int eval_run(mdpvi_mdp* h, const uint8_t* pi, double* V, double tol, int64_t max
   return run_loop<double>(h, V, tol, max_iter, s, st, 17.0 * M.n_states,
                           static_cast<double>(M.n_states),
                           [&](long long j, double* in, double* out) {
-                            return mdpvi::launch_eval_sweep(M, pi, in, out, h->ctl, h->res, j, tol, s);
+                            return mdpvi::launch_eval_sweep(M, h->d_model, pi, in, out, h->ctl, h->res, j, tol, s);
                           },
                           false, mdpvi::eval_sweep_grid(M));
 }

@@ -208,4 +208,38 @@ __device__ __forceinline__ bool sweep_stopped(Ctl* ctl, double* res, long long j
   return false;
 }
 
+// The control of the max-norm sweeps that leave the test to workgroup 0, which
+// sets done_iter = j where sweep j-1 met it, at its end; sweep j still writes
+// V^{j+1}, into the buffer that the answer V^j is not in, and later sweeps
+// skip.  So no workgroup waits for the test's words before its first load.  A
+// done_iter below j is older than this launch: the same for every lane.
+struct SweepTest {
+  long long done;
+  bool mine;
+  unsigned int up, bad;
+};
+
+__device__ __forceinline__ SweepTest sweep_test_load(const Ctl* ctl, long long j) {
+  SweepTest t{load_agent(&ctl->done_iter), blockIdx.x == 0 && threadIdx.x < kWave, 0u, 0u};
+  if (t.mine && j > 0) {
+    const int r = static_cast<int>((j - 1) % kResSlots), x = threadIdx.x % kNumXcd;
+    t.up = load_agent(&ctl->go[r][x][0]);
+    t.bad = load_agent(&ctl->nan[r][x][0]);
+  }
+  return t;
+}
+
+__device__ __forceinline__ bool sweep_skipped(const SweepTest& t, long long j) { return t.done >= 0 && t.done < j; }
+
+__device__ __forceinline__ void sweep_test_record(const SweepTest& t, Ctl* ctl, long long j) {
+  if (!t.mine) return;
+  const bool met = __ballot(t.bad != 0u) != 0 || __ballot(t.up != 0u) == 0;
+  if (j > 0 && met && threadIdx.x == 0) store_agent(&ctl->done_iter, j);
+  if (threadIdx.x < kNumXcd) {
+    const int r = static_cast<int>((j + 1) % kResSlots);
+    store_agent(&ctl->go[r][threadIdx.x][0], 0u);
+    store_agent(&ctl->nan[r][threadIdx.x][0], 0u);
+  }
+}
+
 }  // namespace mdpvi

@@ -122,7 +122,7 @@ hipError_t launch_vi_row(const Model& M, const TileShape& S, const float* Vin, f
                          double* Aout, Ctl* ctl, double* res, long long j, double tol, hipStream_t s);
 bool eval_tile_shape(const Model& M, TileShape* S);
 hipError_t launch_eval_arrival_init(const Model& M, const double* V, double* A, hipStream_t s);
-hipError_t launch_eval_tile(const Model& M, const TileShape& S, const uint8_t* pi, const double* Vin,
+hipError_t launch_eval_tile(const Model& M, const Model* dM, const TileShape& S, const uint8_t* pi, const double* Vin,
                             double* Vout, const double* Ain, double* Aout, Ctl* ctl, double* res, long long j,
                             double tol, hipStream_t s);
 
@@ -151,7 +151,7 @@ hipError_t launch_improve(const Model& M, const double* V, const uint8_t* pi_in,
 hipError_t launch_policy_diff(uint64_t n, const uint8_t* a, const uint8_t* b, Ctl* ctl, hipStream_t s);
 
 // One fixed-policy FP64 sweep V^{j+1} = r_pi + gamma P_pi V^j.
-hipError_t launch_eval_sweep(const Model& M, const uint8_t* pi, const double* Vin, double* Vout,
+hipError_t launch_eval_sweep(const Model& M, const Model* dM, const uint8_t* pi, const double* Vin, double* Vout,
                              Ctl* ctl, double* res, long long j, double tol, hipStream_t s);
 // Workgroups of one generic-form evaluation or adjoint sweep (4 occupancies
 // per thread), and of the evaluation sweep actually launched.

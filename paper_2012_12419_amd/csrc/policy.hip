@@ -30,11 +30,13 @@ __global__ __launch_bounds__(kBlock) void policy_check_kernel(Model M, const uin
 }
 
 template <int KMAX, int JMAX, typename Idx>
-__global__ __launch_bounds__(kBlock) void eval_sweep_kernel(Model M, const uint8_t* __restrict__ pi,
+__global__ __launch_bounds__(kBlock) void eval_sweep_kernel(const Model* __restrict__ dM, const uint8_t* __restrict__ pi,
                                                              const double* __restrict__ Vin,
                                                              double* __restrict__ Vout, Ctl* ctl,
                                                              double* res, long long j, double tol) {
-  if (sweep_stopped<ResKind::kMax>(ctl, res, j, tol)) return;
+  const Model& M = *dM;
+  const SweepTest test = sweep_test_load(ctl, j);
+  if (sweep_skipped(test, j)) return;
   const uint32_t b = xcd_block(blockIdx.x, gridDim.x);
   double dmax = 0.0;
 #pragma unroll
@@ -47,6 +49,7 @@ __global__ __launch_bounds__(kBlock) void eval_sweep_kernel(Model M, const uint8
     }
   }
   block_max_to(dmax, ctl, res, j, tol);
+  sweep_test_record(test, ctl, j);
 }
 
 template <int KMAX, int JMAX, typename Idx>
@@ -55,12 +58,18 @@ __global__ __launch_bounds__(kBlock) void greedy_kernel(Model M, int kind, uint8
   if (o < static_cast<Idx>(M.n_occ)) greedy_occupancy<KMAX, JMAX>(M, kind, pi, o);
 }
 
+// The sweeps take the model from device memory: as a launch's argument its
+// 0.75 KB made the host's part of a launch longer than a small sweep (734
+// sweeps of 85,683 states, with the test left to workgroup 0: 4.54 -> 4.23 ms;
+// workgroups of one wavefront, which spread over more CUs, took 5.0).
 template <int K, int J>
-__global__ __launch_bounds__(kBlock) void eval_exact_kernel(Model M, const uint8_t* __restrict__ pi,
+__global__ __launch_bounds__(kBlock) void eval_exact_kernel(const Model* __restrict__ dM, const uint8_t* __restrict__ pi,
                                                              const double* __restrict__ Vin,
                                                              double* __restrict__ Vout, Ctl* ctl,
                                                              double* res, long long j, double tol) {
-  if (sweep_stopped<ResKind::kMax>(ctl, res, j, tol)) return;
+  const Model& M = *dM;
+  const SweepTest test = sweep_test_load(ctl, j);
+  if (sweep_skipped(test, j)) return;
   const uint32_t b = xcd_block(blockIdx.x, gridDim.x);
   const uint32_t o = b * kBlock + threadIdx.x;
   double dmax = 0.0;
@@ -68,6 +77,7 @@ __global__ __launch_bounds__(kBlock) void eval_exact_kernel(Model M, const uint8
   const BufView vin = make_view(Vin, static_cast<uint32_t>(M.n_states) * 8u);
   if (o < static_cast<uint32_t>(M.n_occ)) dmax = eval_exact<K, J>(M, pv, vin, Vout, o);
   block_max_to(dmax, ctl, res, j, tol);
+  sweep_test_record(test, ctl, j);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -81,41 +91,40 @@ static bool eval_exact_shape(const Model& M) {
 }
 
 template <int K, int J>
-static hipError_t launch_eval_exact_t(const Model& M, const uint8_t* pi, const double* Vin, double* Vout,
+static hipError_t launch_eval_exact_t(const Model& M, const Model* dM, const uint8_t* pi, const double* Vin, double* Vout,
                                       Ctl* ctl, double* res, long long j, double tol, hipStream_t s) {
-  const uint32_t grid = static_cast<uint32_t>((static_cast<uint64_t>(M.n_occ) + kBlock - 1) / kBlock);
-  hipLaunchKernelGGL((eval_exact_kernel<K, J>), dim3(grid), dim3(kBlock), 0, s, M, pi, Vin, Vout, ctl, res,
-                     j, tol);
+  const uint32_t grid = eval_sweep_grid(M);
+  hipLaunchKernelGGL((eval_exact_kernel<K, J>), dim3(grid), dim3(kBlock), 0, s, dM, pi, Vin, Vout, ctl, res, j, tol);
   return hipGetLastError();
 }
 
-static hipError_t launch_eval_exact(const Model& M, const uint8_t* pi, const double* Vin, double* Vout,
+static hipError_t launch_eval_exact(const Model& M, const Model* dM, const uint8_t* pi, const double* Vin, double* Vout,
                                     Ctl* ctl, double* res, long long j, double tol, hipStream_t s) {
   switch (M.K * 4 + M.J) {
-    case 5: return launch_eval_exact_t<1, 1>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 6: return launch_eval_exact_t<1, 2>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 7: return launch_eval_exact_t<1, 3>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 9: return launch_eval_exact_t<2, 1>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 10: return launch_eval_exact_t<2, 2>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 11: return launch_eval_exact_t<2, 3>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 13: return launch_eval_exact_t<3, 1>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 14: return launch_eval_exact_t<3, 2>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 15: return launch_eval_exact_t<3, 3>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 17: return launch_eval_exact_t<4, 1>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 18: return launch_eval_exact_t<4, 2>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 19: return launch_eval_exact_t<4, 3>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 21: return launch_eval_exact_t<5, 1>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 22: return launch_eval_exact_t<5, 2>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 23: return launch_eval_exact_t<5, 3>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 25: return launch_eval_exact_t<6, 1>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 26: return launch_eval_exact_t<6, 2>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 27: return launch_eval_exact_t<6, 3>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 29: return launch_eval_exact_t<7, 1>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 30: return launch_eval_exact_t<7, 2>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 31: return launch_eval_exact_t<7, 3>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 33: return launch_eval_exact_t<8, 1>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 34: return launch_eval_exact_t<8, 2>(M, pi, Vin, Vout, ctl, res, j, tol, s);
-    case 35: return launch_eval_exact_t<8, 3>(M, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 5: return launch_eval_exact_t<1, 1>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 6: return launch_eval_exact_t<1, 2>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 7: return launch_eval_exact_t<1, 3>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 9: return launch_eval_exact_t<2, 1>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 10: return launch_eval_exact_t<2, 2>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 11: return launch_eval_exact_t<2, 3>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 13: return launch_eval_exact_t<3, 1>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 14: return launch_eval_exact_t<3, 2>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 15: return launch_eval_exact_t<3, 3>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 17: return launch_eval_exact_t<4, 1>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 18: return launch_eval_exact_t<4, 2>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 19: return launch_eval_exact_t<4, 3>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 21: return launch_eval_exact_t<5, 1>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 22: return launch_eval_exact_t<5, 2>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 23: return launch_eval_exact_t<5, 3>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 25: return launch_eval_exact_t<6, 1>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 26: return launch_eval_exact_t<6, 2>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 27: return launch_eval_exact_t<6, 3>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 29: return launch_eval_exact_t<7, 1>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 30: return launch_eval_exact_t<7, 2>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 31: return launch_eval_exact_t<7, 3>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 33: return launch_eval_exact_t<8, 1>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 34: return launch_eval_exact_t<8, 2>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
+    case 35: return launch_eval_exact_t<8, 3>(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
     default:
       return hipErrorInvalidValue;
   }
@@ -256,21 +265,21 @@ hipError_t launch_policy_diff(uint64_t n, const uint8_t* a, const uint8_t* b, Ct
   return hipGetLastError();
 }
 
-hipError_t launch_eval_sweep(const Model& M, const uint8_t* pi, const double* Vin, double* Vout,
+hipError_t launch_eval_sweep(const Model& M, const Model* dM, const uint8_t* pi, const double* Vin, double* Vout,
                              Ctl* ctl, double* res, long long j, double tol, hipStream_t s) {
-  if (eval_exact_shape(M)) return launch_eval_exact(M, pi, Vin, Vout, ctl, res, j, tol, s);
+  if (eval_exact_shape(M)) return launch_eval_exact(M, dM, pi, Vin, Vout, ctl, res, j, tol, s);
   if (use_32bit_index(M)) {
     return dispatch_kj(M, [&](auto km, auto jm) {
       constexpr int KM = decltype(km)::value, JM = decltype(jm)::value;
       hipLaunchKernelGGL((eval_sweep_kernel<KM, JM, uint32_t>), sweep_grid(M),
-                                           dim3(kBlock), 0, s, M, pi, Vin, Vout, ctl, res, j, tol);
+                                           dim3(kBlock), 0, s, dM, pi, Vin, Vout, ctl, res, j, tol);
       return hipGetLastError();
     });
   } else {
     return dispatch_kj(M, [&](auto km, auto jm) {
       constexpr int KM = decltype(km)::value, JM = decltype(jm)::value;
       hipLaunchKernelGGL((eval_sweep_kernel<KM, JM, uint64_t>), sweep_grid(M),
-                                           dim3(kBlock), 0, s, M, pi, Vin, Vout, ctl, res, j, tol);
+                                           dim3(kBlock), 0, s, dM, pi, Vin, Vout, ctl, res, j, tol);
       return hipGetLastError();
     });
   }
