@@ -23,6 +23,12 @@ average launch duration: the timed solves' spans between the HIP events the
 library records on the solver's stream, over their working sweeps; one
 extra step with an event pair around every sweep is reported beside it) and
 the FP64 CPU oracle timed on a bounded sample of the same workload.
+
+The timed steps sweep every state (set_orbits(False)): a backup counts where
+it is computed.  By default the library sweeps one state per orbit of the
+host permutations where the problem allows it, with the same results; the
+field "automatic" holds the same steps timed so, and the batched and the
+beyond-cache figures carry both.
 """
 from __future__ import annotations
 
@@ -72,6 +78,7 @@ def batched_vs_per_instance(mdpvi, n: int, tol: float) -> dict:
     import workloads as W
     insts = W.batch(n, seed=3)
     b = mdpvi.Batch(insts)
+    b.set_orbits(False)                        # both sides sweep every state
     tuned = b.autotune(trials=3)               # untimed: round-kernel tile sizes for these shapes
     V = torch.zeros(b.num_states, device="cuda")
     b.vi_solve(V, tol=tol)                     # warm-up (first-use allocations)
@@ -81,7 +88,18 @@ def batched_vs_per_instance(mdpvi, n: int, tol: float) -> dict:
     st, its, _ = b.vi_solve(V, tol=tol)
     torch.cuda.synchronize()
     t_batch = time.perf_counter() - t0
+    b.set_orbits(True)
+    V.zero_()
+    b.vi_solve(V, tol=tol)                     # first-use tables of the orbit form
+    V.zero_()
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    b.vi_solve(V, tol=tol)
+    torch.cuda.synchronize()
+    t_auto = time.perf_counter() - t0
     mdps = [mdpvi.MDP.from_instance(p) for p in insts]
+    for m in mdps:
+        m.set_orbits(False)
     Vs = [torch.zeros(m.num_states, device="cuda") for m in mdps]
     for m, v in zip(mdps[:8], Vs[:8]):
         m.vi_solve(v, tol=tol)
@@ -94,7 +112,7 @@ def batched_vs_per_instance(mdpvi, n: int, tol: float) -> dict:
     torch.cuda.synchronize()
     t_single = time.perf_counter() - t0
     return {"instances": n, "states": b.num_states, "tol": tol,
-            "batched_seconds": t_batch, "batched_backups_per_s": st["backups"] / t_batch,
+            "batched_seconds": t_batch, "batched_seconds_automatic": t_auto, "batched_backups_per_s": st["backups"] / t_batch,
             "per_instance_seconds": t_single, "per_instance_backups_per_s": backups_single / t_single,
             "speedup": t_single / t_batch, "max_sweeps": max(its),
             "round_kernel_occupancies_per_thread": b.round_forms(),
@@ -135,6 +153,7 @@ def supplementary_k7(mdpvi, tol: float) -> dict:
     import torch
     inst, desc = workload("large_single_k7")
     mdp = mdpvi.MDP.from_instance(inst)
+    mdp.set_orbits(False)
     vi_form, _ = mdp.sweep_forms()
     V = torch.zeros(mdp.num_states, dtype=torch.float32, device="cuda")
     try:
@@ -143,6 +162,11 @@ def supplementary_k7(mdpvi, tol: float) -> dict:
         pass
     V.zero_()
     st = mdp.vi_solve(V, tol=tol)
+    mdp.set_orbits(True)
+    V.zero_()
+    mdp.vi_solve(V, tol=tol)   # first-use tables of the orbit form
+    V.zero_()
+    auto = mdp.vi_solve(V, tol=tol)
     N = mdp.num_states
     avg = st["seconds"] / st["iterations"]
     ach = VI_BYTES_PER_STATE * N / avg / 1e9
@@ -152,7 +176,7 @@ def supplementary_k7(mdpvi, tol: float) -> dict:
             "vi_tile_kernel": ["paper_2012_12419_amd/csrc/tile_vi.hip", "paper_2012_12419_amd/csrc/tile_vi.hpp",
                                "paper_2012_12419_amd/csrc/tile.hpp"]}
     return {"workload": f"large_single_k7: {desc}", "states": N, "form": vi_form, "kernel": impl,
-            "sweeps": st["iterations"], "seconds": st["seconds"],
+            "sweeps": st["iterations"], "seconds": st["seconds"], "seconds_automatic": auto["seconds"],
             "backups_per_s": st["backups"] / st["seconds"], "avg_us": avg * 1e6,
             "roofline": {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": ach / HBM_PEAK_GBS,
@@ -429,6 +453,7 @@ def main() -> int:
     inst, desc = workload(args.workload)
     mdp = mdpvi.MDP.from_instance(inst)
     mdp.set_sweep_form(args.sweep_form)
+    mdp.set_orbits(False)
     tuned = None
     if args.autotune and args.sweep_form == -1:
         # untimed: the autotuner records the fastest form of each sweep for
@@ -472,6 +497,19 @@ def main() -> int:
         recs.append(step())
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
+
+    # the same steps in the library's default mode
+    mdp.set_orbits(True)
+    step()
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    auto_recs = [step() for _ in range(args.steps)]
+    torch.cuda.synchronize()
+    automatic = {"ms_per_step": (time.perf_counter() - t0) / args.steps * 1e3,
+                 "time_to_tol_s": sum(r[0]["seconds"] for r in auto_recs) / len(auto_recs),
+                 "same_sweeps": all([x["iterations"] for x in r] == [x["iterations"] for x in recs[0]]
+                                    for r in auto_recs)}
+    mdp.set_orbits(False)
 
     t_tol = sum(r[0]["seconds"] for r in recs) / len(recs)
     tol_labels = tolerance_runs(mdp, V, args.tol, t_tol, recs[0][0]["iterations"] if recs else None)
@@ -579,6 +617,7 @@ def main() -> int:
                                         "state per FP64 evaluation sweep of pi* and of the least-loaded "
                                         "heuristic; divided by the steps' wall time"},
         "time_to_tol_s": t_tol,
+        "automatic": automatic,
         "time_to_tol": tol_labels,
         "vi_sweeps": vi_sweeps,
         "eval_sweeps": ev_sweeps,
