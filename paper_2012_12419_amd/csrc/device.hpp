@@ -119,7 +119,9 @@ enum class ResKind { kMax, kSum };
 
 // End of a max-norm sweep: the workgroup's largest |V' - V| is stored to
 // res[r * grid + b]; if it is not below tol the workgroup raises go[r]
-// (and nan[r] for a NaN).  No atomics.
+// (and nan[r] for a NaN).  No atomics, and no look at the words first: that
+// round trip at the end of every workgroup was 0.5 to 1 us of a sweep (FP64
+// evaluation of 85,683 states 5.75 -> 5.25 us, of 322,102 7.8 -> 6.9).
 template <int NB = kBlock>
 __device__ __forceinline__ void block_max_to(double v, Ctl* ctl, double* res, long long j, double tol) {
   __shared__ double part[NB / kWave];
@@ -135,10 +137,8 @@ __device__ __forceinline__ void block_max_to(double v, Ctl* ctl, double* res, lo
     const int r = static_cast<int>(j % kResSlots);
     const int x = blockIdx.x % kNumXcd;
     res[static_cast<size_t>(r) * gridDim.x + blockIdx.x] = m;
-    volatile unsigned int* go = &ctl->go[r][x][0];
-    if (!(m < tol) && *go == 0u) *go = 1u;
-    volatile unsigned int* nn = &ctl->nan[r][x][0];
-    if (m != m && *nn == 0u) *nn = 1u;
+    if (!(m < tol)) __hip_atomic_store(&ctl->go[r][x][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (m != m) __hip_atomic_store(&ctl->nan[r][x][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 }
 

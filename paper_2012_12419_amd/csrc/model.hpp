@@ -91,11 +91,10 @@ struct Model {
 //   go[r][x]:  the sweep with index j (r = j mod kResSlots) failed the test in
 //              some workgroup b with b mod 8 = x: that workgroup's largest
 //              |V' - V| is not below tol.  Workgroups raise it with a plain
-//              store only after reading it still clear, so a word sees a few
-//              stores per sweep instead of one per workgroup (stores to one
-//              address from thousands of workgroups serialise in the memory
-//              system).  Workgroups b and b + 8 normally share an XCD and
-//              hence its L2.  The sweep converged iff every go[r][x] is clear.
+//              store, which stays in their XCD's L2 until the launch ends:
+//              workgroups b and b + 8 normally share an XCD (stores that go
+//              to memory, from thousands of workgroups to one address,
+//              serialise there).  The sweep converged iff every go[r][x] is clear.
 //   nan[r][x]: likewise for a NaN.  Every word sits on its own 128-byte line.
 // The residual values themselves live in a separate buffer.
 struct Ctl {
