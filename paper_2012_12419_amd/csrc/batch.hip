@@ -254,41 +254,43 @@ __global__ __launch_bounds__(kBlock) void batch_line_sum_kernel(const BatchInst*
 }
 
 
-// Per-instance control of the round form: true (for the whole workgroup) when
-// the instance already stopped.  The leader workgroup of the instance (its
-// first tile) records done_iter, counts the instance off and clears the
-// residual words of the next round.
+// Per-instance control of the round form, as SweepTest of the single sweeps:
+// the instance's first workgroup (its leader) alone tests the residual of
+// round j-1, at its end; where that meets the test it records done_iter = j,
+// counts the instance off, and later rounds skip the instance.  Round j has
+// then written the buffer that the answer is not in.  The leader also clears
+// the residual words of round j+1.
+struct RoundTest {
+  long long done;
+  bool mine;
+  double v;
+};
+
+__device__ __forceinline__ RoundTest round_test_load(const BatchCtl* c, long long j, bool leader) {
+  RoundTest t{load_agent(&c->done_iter), leader && threadIdx.x < kWave, 0.0};
+  if (t.mine && j > 0 && threadIdx.x < kBatchLanes)
+    t.v = __longlong_as_double(static_cast<long long>(load_agent(&c->res[(j - 1) % kResSlots][threadIdx.x][0])));
+  return t;
+}
+
+__device__ __forceinline__ bool round_skipped(const RoundTest& t, long long j) { return t.done >= 0 && t.done < j; }
+
 template <ResKind RK>
-__device__ __forceinline__ bool inst_stopped(BatchCtl* c, long long j, double tol, int* remaining,
-                                             bool leader) {
-  __shared__ int stop;
-  if (threadIdx.x < kWave) {
-    bool s = load_agent(&c->done_iter) >= 0;
-    if (!s && j > 0) {
-      double v = 0.0;
-      if (threadIdx.x < kBatchLanes)
-        v = __longlong_as_double(static_cast<long long>(
-            load_agent(&c->res[(j - 1) % kResSlots][threadIdx.x][0])));
-      if constexpr (RK == ResKind::kMax) {
-        v = wave_max(v);
-      } else {
+__device__ __forceinline__ void round_test_record(const RoundTest& t, BatchCtl* c, long long j, double tol,
+                                                  int* remaining) {
+  if (!t.mine) return;
+  double v = t.v;
+  if constexpr (RK == ResKind::kMax) {
+    v = wave_max(v);
+  } else {
 #pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-      }
-      if (!(v >= tol)) {
-        s = true;
-        if (leader && threadIdx.x == 0) {
-          store_agent(&c->done_iter, j);
-          atomicSub(remaining, 1);
-        }
-      }
-    }
-    if (threadIdx.x == 0) stop = s ? 1 : 0;
+    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
   }
-  __syncthreads();
-  if (stop) return true;
-  if (leader && threadIdx.x < kBatchLanes) store_agent(&c->res[(j + 1) % kResSlots][threadIdx.x][0], 0ull);
-  return false;
+  if (j > 0 && !(v >= tol) && threadIdx.x == 0) {
+    store_agent(&c->done_iter, j);
+    atomicSub(remaining, 1);
+  }
+  if (threadIdx.x < kBatchLanes) store_agent(&c->res[(j + 1) % kResSlots][threadIdx.x][0], 0ull);
 }
 
 // The workgroup's part of round j's residual of its instance: the largest
@@ -361,7 +363,8 @@ __device__ __forceinline__ void round_body(const BatchInst* __restrict__ insts, 
   const BatchInst& I = insts[tile.inst];
   const Model& M = I.M;
   BatchCtl* c = ctl + tile.inst;
-  if (inst_stopped<Op::RK>(c, j, tol, remaining, tile.first == 0)) return;
+  const RoundTest test = round_test_load(c, j, tile.first == 0);
+  if (round_skipped(test, j)) return;
   const T* Vin = ((j & 1) ? W : V) + I.offset;
   T* Vout = ((j & 1) ? V : W) + I.offset;
   const uint8_t* p = pi ? pi + I.offset : nullptr;
@@ -401,6 +404,7 @@ __device__ __forceinline__ void round_body(const BatchInst* __restrict__ insts, 
     }
   }
   round_residual<Op::RK>(acc, c, j, (tile.first / kBlock) % kBatchLanes);
+  round_test_record<Op::RK>(test, c, j, tol, remaining);
 }
 
 template <class Op, int KMAX, int JMAX, int FORM>
@@ -469,7 +473,8 @@ __global__ __launch_bounds__(kBlock) void batch_vi_tile_kernel(const BatchInst* 
   const BatchInst& I = insts[tile.inst];
   const Model& M = I.M;
   BatchCtl* c = ctl + tile.inst;
-  if (inst_stopped<ResKind::kMax>(c, j, tol, remaining, tile.first == 0)) return;
+  const RoundTest test = round_test_load(c, j, tile.first == 0);
+  if (round_skipped(test, j)) return;
   const float* Vin = ((j & 1) ? W : V) + I.offset;
   float* Vout = ((j & 1) ? V : W) + I.offset;
   const double* Ain = ((j & 1) ? A1 : A0) + I.aoff;
@@ -485,6 +490,7 @@ __global__ __launch_bounds__(kBlock) void batch_vi_tile_kernel(const BatchInst* 
     default: acc = NAN;   // not a tile-form shape: the host never lists such a tile
   }
   round_residual<ResKind::kMax>(acc, c, j, tile.first % kBatchLanes);
+  round_test_record<ResKind::kMax>(test, c, j, tol, remaining);
 }
 
 // FP64 evaluation round in the tile form (tile_eval.hpp) for the instances
@@ -502,7 +508,8 @@ __device__ __forceinline__ void eval_tile_round(const BatchInst* __restrict__ in
   const BatchInst& I = insts[tile.inst];
   const Model& M = I.M;
   BatchCtl* c = ctl + tile.inst;
-  if (inst_stopped<ResKind::kMax>(c, j, tol, remaining, tile.first == 0)) return;
+  const RoundTest test = round_test_load(c, j, tile.first == 0);
+  if (round_skipped(test, j)) return;
   const uint32_t nocc = static_cast<uint32_t>(M.n_occ);
   const uint32_t ns = static_cast<uint32_t>(M.n_states);
   const BufView pv = make_view(pi + I.offset, ns);
@@ -521,6 +528,7 @@ __device__ __forceinline__ void eval_tile_round(const BatchInst* __restrict__ in
     default: acc = NAN;   // not a tile-form shape: the host never lists such a tile
   }
   round_residual<ResKind::kMax>(acc, c, j, tile.first % kBatchLanes);
+  round_test_record<ResKind::kMax>(test, c, j, tol, remaining);
 }
 
 __global__ __launch_bounds__(kBlock) void batch_eval_tile_kernel(const BatchInst* __restrict__ insts,
