@@ -1,12 +1,12 @@
 // adjoint_group.hpp -- the group form of the transposed (adjoint) backup as
-// a device function of a team of lanes, shared by the single-instance group
-// kernel (adjoint_group.hip) and the batched round kernel (adjoint_batch.hip).
+// a workgroup-level device function of the single-instance group kernel
+// (adjoint_group.hip).
 //
-// A group is the G = (C+1)^2 occupancies that share digits 2..K-1; a team
-// takes one, an (occupancy, class) per lane (slot l = e G + r).  The high
-// digits are then the team's, so the neighbours along them are loads at the
-// lane's own offset plus a scalar one.  A lane loads its state's action and
-// weight, its class's neighbours along the high digits and, where one is
+// A group is the G = (C+1)^2 occupancies that share digits 2..K-1; a
+// workgroup takes one, an (occupancy, class) per lane (slot l = e G + r).  The
+// high digits are then the workgroup's, so the neighbours along them are loads
+// at the lane's own offset plus a scalar one.  A lane loads its state's action
+// and weight, its class's neighbours along the high digits and, where one is
 // zero, the reset line along the first such digit, all in one round trip
 // (further lines, which few groups have, later: loading them ahead too took
 // 100 registers and 22 us at 786,432 states, 13 us so).  It publishes in LDS
@@ -15,12 +15,15 @@
 // form the arrival inflows, 2 J (C+1) others the reset lines along digits 0
 // and 1, once each instead of in every wavefront that holds a lane of n_0 = 0
 // or n_1 = 0, and each lane finishes its state.  Bound by instruction issue
-// (about 300 vector and 250 scalar instructions a wavefront) for large
+// (about 330 vector and 250 scalar instructions a wavefront) for large
 // instances, by the round trips for small ones: a sweep of K = 5, C = 8, J = 3
 // (177,147 states) 11.9 -> 6.2 us, of K = 6, C = 7, J = 3 24.6 -> 13.1 us
-// against one occupancy of all classes per lane.  Terms are added in the order
-// of adjoint_occupancy (zeros between them change nothing), so w is
-// bit-identical to the other adjoint forms.
+// against one occupancy of all classes per lane.  Two groups per lane (20 us)
+// and workgroups of 512 and 1,024 lanes (22.8 and 23.3 us) were slower there.
+// In the rounds of a batch, which fill the chip, a lane per occupancy with all
+// its classes needs fewer instructions: the form took 94 against 63 ms.
+// Terms are added in the order of adjoint_occupancy (zeros between them change
+// nothing), so w is bit-identical to the other adjoint forms.
 #pragma once
 
 #include "adjoint_impl.hpp"
@@ -40,12 +43,12 @@ struct AdjointArgs {
   double up[kLineLoads];   // mu_L (x + 1), 0 at x = C
 };
 
-// Lanes of a group's team.
+// Lanes of a group's workgroup.
 __host__ __device__ constexpr uint32_t adjoint_group_threads(uint32_t R, uint32_t J) {
   return (J * R * R + kWave - 1) / kWave * kWave;
 }
 
-// LDS bytes of a team: the line sums along digits 0 and 1, the arrival inflows,
+// LDS bytes of a workgroup: the line sums along digits 0 and 1, the arrival inflows,
 // the weights, K + 1 arrival terms per slot.
 __host__ __device__ constexpr uint32_t adjoint_group_lds(uint32_t K, uint32_t R, uint32_t J) {
   return 8 * (2 * J * R + R * R) + 4 * J * R * R * (K + 2);
@@ -54,17 +57,14 @@ __host__ __device__ constexpr uint32_t adjoint_group_lds(uint32_t K, uint32_t R,
 // stop(): called by every lane once its loads are issued; true makes the
 // function return false at once (before any LDS write or barrier: the answer
 // must be the same for the whole workgroup).  Otherwise the new weight is
-// stored and *dsum_out receives the lane's |w' - w|; returns true.  tid: the
-// lane's number in its team of `threads` lanes; g: the team's group, the same
-// for each wavefront; active: whether the team stores; lds:
-// adjoint_group_lds bytes of the team's own.  LMIN <= C + 1 <= L: the loads of
-// a reset line, those past C (of the state itself) weighted with zero.
+// stored and *dsum_out receives the lane's |w' - w|; returns true.  g: the
+// group; lds: adjoint_group_lds bytes.  LMIN <= C + 1 <= L: the loads of a reset
+// line, those past C (of the state itself) weighted with zero.
 template <int K, int J, int LMIN, int L, typename Stop>
 __device__ __forceinline__ bool adjoint_group_block(const AdjointArgs& M, const uint8_t* __restrict__ pi,
                                                     const float* __restrict__ win, float* __restrict__ wout,
-                                                    uint32_t tid, uint32_t threads, uint32_t g, bool active,
-                                                    double* lds, Stop&& stop, double* dsum_out) {
-  constexpr int NH = K - 2, NA = NH > 0 ? NH : 1;
+                                                    uint32_t g, double* lds, Stop&& stop, double* dsum_out) {
+  constexpr int NH = K - 2;
   const uint32_t R = static_cast<uint32_t>(M.R), G = R * R, C = static_cast<uint32_t>(M.C);
   const uint32_t nocc = M.n_occ;
   const uint32_t slots = J * G, nl = J * R;
@@ -73,11 +73,12 @@ __device__ __forceinline__ bool adjoint_group_block(const AdjointArgs& M, const 
   float* ws = reinterpret_cast<float*>(Bs + G);         // [J][G] weights
   float* in = ws + slots;   // [K+1][J][G]: cloud, hosts 0 and 1 (at the source), high hosts (at the target)
   // lanes past the slots stand in for the last one and store nothing
+  const uint32_t tid = threadIdx.x, threads = blockDim.x;
   const uint32_t l = tid < slots ? tid : slots - 1;
   const uint32_t q1 = fast_div(l, M.divR), e = J == 1 ? 0u : fast_div(q1, M.divR);
   const int n0 = static_cast<int>(l - q1 * R), n1 = static_cast<int>(q1 - e * R);
   // high digits, the same for the workgroup
-  int nh[NA], load_high = 0;
+  int nh[NH], load_high = 0;
   {
     uint32_t q = g;
 #pragma unroll
@@ -96,9 +97,9 @@ __device__ __forceinline__ bool adjoint_group_block(const AdjointArgs& M, const 
   const uint32_t s4 = 4u * s;
   const int p_own = ld_u8(vp, s, 0);
   const float w_own = ld_f32(vw, s4, 0);
-  int p_k[NA];
-  uint32_t d_k[NA];   // distance of the arrival predecessor; 0: none
-  float w_k[NA], w_rel[NA], h[L];
+  int p_k[NH];
+  uint32_t d_k[NH];   // distance of the arrival predecessor; 0: none
+  float w_k[NH], w_rel[NH], h[L];
 #pragma unroll
   for (int x = 0; x < NH; ++x) {
     const uint32_t st = M.stride[2 + x];
@@ -142,7 +143,7 @@ __device__ __forceinline__ bool adjoint_group_block(const AdjointArgs& M, const 
   for (int x = 0; x < NH; ++x) il[(3 + x) * slots] = d_k[x] != 0 && p_k[x] == 2 + x ? w_k[x] : 0.0f;
   __syncthreads();
 
-  // the team's last lanes: the reset lines along digits 0 and 1, each summed
+  // the last lanes: the reset lines along digits 0 and 1, each summed
   // from zero in the order 0..C
   if (tid >= threads - 2 * nl) {
     const uint32_t t = tid - (threads - 2 * nl);
@@ -155,7 +156,7 @@ __device__ __forceinline__ bool adjoint_group_block(const AdjointArgs& M, const 
     for (uint32_t y = 0; y < L; ++y) x[y] = ws[y <= C ? base + y * st : base];
     lines[t] = sum_line(x);
   }
-  // its first: the arrival inflow, the paid cloud at n', then placements on
+  // the first: the arrival inflow, the paid cloud at n', then placements on
   // host k from n' - size_e 1_k, k = 0..K-1, e = 0..J-1
   if (tid < G) {
     const float* iu = in + tid;
@@ -201,7 +202,7 @@ __device__ __forceinline__ bool adjoint_group_block(const AdjointArgs& M, const 
   const double c = g == 0 && l == e * G ? pick(M.c_obj[0], M.c_obj[1], M.c_obj[2]) : 0.0;
   const float wn = static_cast<float>(fma(M.gamma, acc, c));
   *dsum_out = 0.0;
-  if (active && tid < slots) {
+  if (tid < slots) {
     st_f32(vo, wn, s4, 0);
     *dsum_out = fabs(static_cast<double>(wn) - static_cast<double>(w_own));
   }

@@ -496,6 +496,7 @@ int run_loop(mdpvi_mdp* h, T* buf0, double tol, int64_t max_iter, hipStream_t s,
 
 constexpr int kOrbitRefused = 1;      // the start or the policy is not invariant under host permutations
 constexpr int kOrbitInfeasible = 2;   // the policy has an infeasible action
+constexpr int kOrbitNoMemory = 3;     // no memory for the tables: nothing was done
 constexpr char kInfeasiblePolicy[] = "policy has an action that is not feasible in its state";
 constexpr int64_t kOrbitLdsSweeps = 8192;   // most sweeps of one LDS-resident launch
 
@@ -643,6 +644,10 @@ template <class Op>
 int orbit_solve(mdpvi_mdp* h, const uint8_t* pi, typename Op::T* V, double tol, int64_t max_iter, hipStream_t s,
                 mdpvi_stats* st) {
   int rc = orbit_ensure(h, s);
+  if (rc == MDPVI_ENOMEM) {   // the full sweeps need none of it
+    (void)hipGetLastError();
+    return kOrbitNoMemory;
+  }
   if (rc) return rc;
   OrbitPlan& O = h->orbit;
   const Model& M = h->M;
@@ -1363,7 +1368,7 @@ int vi_solve(mdpvi_mdp_t h, float* V, double tol, int64_t max_iter, void* hip_st
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   if (h->slab_t == -1 && orbit_applies<mdpvi::OrbitVi>(h, max_iter)) {
     const int orc = orbit_solve<mdpvi::OrbitVi>(h, nullptr, V, tol, max_iter, s, st);
-    if (orc != kOrbitRefused) return orc;
+    if (orc != kOrbitRefused && orc != kOrbitNoMemory) return orc;
   }
   int rc = ensure_scratch(h, static_cast<size_t>(h->M.n_states) * sizeof(float));
   if (rc) return rc;
@@ -1617,15 +1622,16 @@ int policy_eval(mdpvi_mdp_t h, const uint8_t* pi, double* V, double tol, int64_t
   if (max_iter < 1) return fail(MDPVI_EINVAL, "max_iter=%lld must be >= 1", (long long)max_iter);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const Model& M = h->M;
-  const bool tried = orbit_applies<mdpvi::OrbitEval>(h, max_iter);
-  if (tried) {   // its check also covers feasibility
+  bool checked = false;
+  if (orbit_applies<mdpvi::OrbitEval>(h, max_iter)) {
     const int orc = orbit_solve<mdpvi::OrbitEval>(h, pi, V, tol, max_iter, s, st);
     if (orc == kOrbitInfeasible) return fail(MDPVI_EINVAL, "%s", kInfeasiblePolicy);
-    if (orc != kOrbitRefused) return orc;
+    if (orc != kOrbitRefused && orc != kOrbitNoMemory) return orc;
+    checked = orc == kOrbitRefused;   // its check covers feasibility
   }
   int rc = ensure_scratch(h, static_cast<size_t>(M.n_states) * sizeof(double));
   if (rc) return rc;
-  if (!tried) {
+  if (!checked) {
     HIP_TRY(mdpvi::launch_ctl_init(h->ctl, h->res, s));
     HIP_TRY(mdpvi::launch_policy_check(M, pi, h->ctl, s));
     HIP_TRY(hipMemcpyAsync(h->ctl_host, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
@@ -1714,7 +1720,7 @@ int policy_iteration(mdpvi_mdp_t h, uint8_t* pi, double* V, double eval_tol, int
     rc = kOrbitRefused;
     if (orbit_applies<mdpvi::OrbitEval>(h, eval_max_iter))
       rc = orbit_solve<mdpvi::OrbitEval>(h, pi, V, eval_tol, eval_max_iter, s, &e);
-    if (rc == kOrbitRefused) rc = eval_run(h, pi, V, eval_tol, eval_max_iter, s, &e);
+    if (rc == kOrbitRefused || rc == kOrbitNoMemory) rc = eval_run(h, pi, V, eval_tol, eval_max_iter, s, &e);
     tot.iterations += e.iterations;
     tot.residual_inf = e.residual_inf;
     tot.bound_inf = e.bound_inf;
@@ -2478,6 +2484,10 @@ template <class Op>
 int orbit_batch_solve(mdpvi_batch* b, const uint8_t* pi, typename Op::T* V, double tol, int64_t max_iter,
                       hipStream_t s, const int* active, std::vector<mdpvi::BatchOut>& done, int* n_left) {
   int rc = orbit_batch_ensure(b, s);
+  if (rc == MDPVI_ENOMEM) {   // the full forms need none of it
+    (void)hipGetLastError();
+    return MDPVI_OK;
+  }
   if (rc) return rc;
   OrbitBatch& O = b->orbit;
   const int n = static_cast<int>(O.inst.size()), nt = static_cast<int>(b->tiles_all.size());
