@@ -149,6 +149,7 @@ def run_sweeps(kernel: str, workload: str, sweeps: int, copy_mb: int, form: int,
     inst = {"large_single": W.large_single(), "large_single_k7": W.large_single(K=7),
             "gradient": W.gradient_instance()}[workload]
     mdp = mdpvi.MDP.from_instance(inst)
+    mdp.set_orbits(False)
     mdp.set_sweep_form(form)
     mdp.set_adjoint_form(adjoint_form)
     try:
