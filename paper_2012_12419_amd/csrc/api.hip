@@ -114,13 +114,6 @@ int ensure_scratch(mdpvi_mdp* h, size_t bytes) {
   if (h->device >= 0 && h->device != dev)
     return fail(MDPVI_EINVAL, "handle scratch lives on device %d, current device is %d", h->device,
                 dev);
-  if (!h->d_model) {
-    if (hipMalloc(reinterpret_cast<void**>(&h->d_model), sizeof(Model)) != hipSuccess) {
-      h->d_model = nullptr;
-      return fail(MDPVI_ENOMEM, "hipMalloc of %zu model bytes failed", sizeof(Model));
-    }
-    HIP_TRY(hipMemcpy(h->d_model, &h->M, sizeof(Model), hipMemcpyHostToDevice));
-  }
   if (!h->ctl) {
     if (hipMalloc(&h->ctl, sizeof(Ctl)) != hipSuccess) {
       h->ctl = nullptr;
@@ -150,6 +143,13 @@ int ensure_scratch(mdpvi_mdp* h, size_t bytes) {
       return fail(MDPVI_ENOMEM, "hipHostMalloc of the residual mirror failed");
     }
     h->device = dev;
+  }
+  if (!h->d_model) {
+    if (hipMalloc(reinterpret_cast<void**>(&h->d_model), sizeof(Model)) != hipSuccess) {
+      h->d_model = nullptr;
+      return fail(MDPVI_ENOMEM, "hipMalloc of %zu model bytes failed", sizeof(Model));
+    }
+    HIP_TRY(hipMemcpy(h->d_model, &h->M, sizeof(Model), hipMemcpyHostToDevice));
   }
   if (bytes > h->vbuf_bytes) {
     if (h->vbuf) {
