@@ -186,9 +186,9 @@ int policy_extract_f64(mdpvi_mdp_t h, const double *V, uint8_t *pi, float *gap,
  * A policy whose target load (the occupancy of the host it places on, or
  * none) is the same in all states that differ by a host permutation, such as
  * the least-loaded heuristic, has an invariant value.  When V^0 is invariant
- * too, to within tol/2, the sweeps run on one state per orbit, from its
- * representative's V^0, in every sweep form (mdp_set_orbits); the result
- * differs from that of the full sweeps in the rounding of FP64 sums.
+ * too (the same value in all states of an orbit), the sweeps run on one state
+ * per orbit, in every sweep form (mdp_set_orbits); the result differs from that
+ * of the full sweeps in the rounding of FP64 sums.
  * Errors as vi_solve.                                                       */
 int policy_eval(mdpvi_mdp_t h, const uint8_t *pi, double *V, double tol,
                 int64_t max_iter, void *hip_stream, mdpvi_stats *st);

@@ -53,14 +53,13 @@ __global__ __launch_bounds__(256) void orbit_begin_kernel(OrbitShape S, OrbitPar
 template <class Op, int KX>
 __global__ __launch_bounds__(256) void orbit_check_kernel(OrbitShape S, OrbitParams P, OrbitWork W,
                                                           const typename Op::T* __restrict__ V,
-                                                          const uint8_t* __restrict__ pi, double delta,
-                                                          OrbitCtl* mirror) {
+                                                          const uint8_t* __restrict__ pi, OrbitCtl* mirror) {
   __shared__ uint32_t B[kOrbitBinom];
   orbit_stage_binom(S, B);
   bool bad = false, infeasible = false;
   const uint64_t step = static_cast<uint64_t>(gridDim.x) * blockDim.x;
   for (uint64_t o = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; o < S.n_occ; o += step)
-    bad = orbit_differs<Op, KX>(S, P, W, B, V, pi, delta, static_cast<uint32_t>(o), infeasible) || bad;
+    bad = orbit_differs<Op, KX>(S, P, W, B, V, pi, static_cast<uint32_t>(o), infeasible) || bad;
   const bool any = __ballot(bad || infeasible) != 0, inf = __ballot(infeasible) != 0;
   if (any && threadIdx.x % kWave == 0) orbit_refuse(W.ctl, mirror, inf);
 }
@@ -188,10 +187,8 @@ template <class Op>
 hipError_t launch_orbit_begin(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, const typename Op::T* V,
                               const uint8_t* pi, double tol, OrbitCtl* mirror, hipStream_t s) {
   hipLaunchKernelGGL((orbit_begin_kernel<Op>), dim3((S.n + 255) / 256), dim3(256), 0, s, S, P, W, V, pi, tol);
-  const double delta = 0.5 * tol;
-#define MDPVI_CALL(KX_)                                                                                      \
-  hipLaunchKernelGGL((orbit_check_kernel<Op, KX_>), dim3(full_grid(S)), dim3(256), 0, s, S, P, W, V, pi, delta, \
-                     mirror)
+#define MDPVI_CALL(KX_) \
+  hipLaunchKernelGGL((orbit_check_kernel<Op, KX_>), dim3(full_grid(S)), dim3(256), 0, s, S, P, W, V, pi, mirror)
   MDPVI_ORBIT_K(S.K, MDPVI_CALL)
 #undef MDPVI_CALL
   return hipGetLastError();

@@ -103,11 +103,11 @@ __global__ __launch_bounds__(256) void orbit_batch_begin_kernel(const OrbitInst*
 // instance against their orbits.
 template <class Op, int KX>
 __device__ __forceinline__ bool batch_differs(const OrbitInst& I, const uint32_t* B, const typename Op::T* V,
-                                              const uint8_t* pi, double delta, uint32_t first, bool& infeasible) {
+                                              const uint8_t* pi, uint32_t first, bool& infeasible) {
   bool bad = false;
   for (int k = 0; k < kOccPerThread; ++k) {
     const uint32_t o = first + threadIdx.x + static_cast<uint32_t>(k * kBlock);
-    if (o < I.S.n_occ) bad = orbit_differs<Op, KX>(I.S, I.P, I.W, B, V, pi, delta, o, infeasible) || bad;
+    if (o < I.S.n_occ) bad = orbit_differs<Op, KX>(I.S, I.P, I.W, B, V, pi, o, infeasible) || bad;
   }
   return bad;
 }
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kBlock) void orbit_batch_check_kernel(const OrbitIn
                                                                    const int32_t* __restrict__ slot,
                                                                    const Tile* __restrict__ tiles,
                                                                    const typename Op::T* __restrict__ V,
-                                                                   const uint8_t* __restrict__ pi, double delta) {
+                                                                   const uint8_t* __restrict__ pi) {
   __shared__ uint32_t B[kOrbitBinom];
   const Tile t = tiles[blockIdx.x];
   const int at = slot[t.inst];
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kBlock) void orbit_batch_check_kernel(const OrbitIn
   const typename Op::T* Vi = V + I.offset;
   const uint8_t* p = pi ? pi + I.offset : nullptr;
   bool bad = false, infeasible = false;
-#define MDPVI_BODY(KX_) bad = batch_differs<Op, KX_>(I, B, Vi, p, delta, t.first, infeasible)
+#define MDPVI_BODY(KX_) bad = batch_differs<Op, KX_>(I, B, Vi, p, t.first, infeasible)
   MDPVI_OB_K(MDPVI_BODY)
 #undef MDPVI_BODY
   const bool any = __ballot(bad || infeasible) != 0, inf = __ballot(infeasible) != 0;
@@ -289,8 +289,7 @@ hipError_t launch_orbit_batch_begin(const OrbitInst* insts, const int32_t* slot,
                                     const int* active, double tol, int* remaining, int n_remaining, hipStream_t s) {
   hipLaunchKernelGGL((orbit_batch_begin_kernel<Op>), dim3(n_otiles), dim3(256), 0, s, insts, otiles, V, pi, active,
                      tol, remaining, n_remaining);
-  hipLaunchKernelGGL((orbit_batch_check_kernel<Op>), dim3(n_tiles), dim3(kBlock), 0, s, insts, slot, tiles, V, pi,
-                     0.5 * tol);
+  hipLaunchKernelGGL((orbit_batch_check_kernel<Op>), dim3(n_tiles), dim3(kBlock), 0, s, insts, slot, tiles, V, pi);
   return hipGetLastError();
 }
 

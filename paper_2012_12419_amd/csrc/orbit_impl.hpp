@@ -119,14 +119,12 @@ __device__ __forceinline__ void orbit_begin(const OrbitShape& S, const OrbitPara
   W.A[0][r] = a;
 }
 
-// Occupancy o against its orbit: value iteration's start bit for bit; an
-// evaluation's start to within delta (it then begins at the representative's
-// value, which moves the start by less than the tolerance) and its policy's
-// target load; `infeasible` for an action without room.
+// Occupancy o against its orbit: the start (value iteration's bit for bit) and
+// an evaluation's target load; `infeasible` for an action without room.
 template <class Op, int KX>
 __device__ __forceinline__ bool orbit_differs(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W,
                                               const uint32_t* B, const typename Op::T* __restrict__ V,
-                                              const uint8_t* __restrict__ pi, double delta, uint32_t o,
+                                              const uint8_t* __restrict__ pi, uint32_t o,
                                               bool& infeasible) {
   using T = typename Op::T;
   const T* Vr = static_cast<const T*>(W.V[0]);
@@ -145,8 +143,7 @@ __device__ __forceinline__ bool orbit_differs(const OrbitShape& S, const OrbitPa
 #pragma unroll
       for (int k = 0; k < KX; ++k) load = (KX <= 8 || k < S.K) && k == x ? d[k] : load;
       if (x > S.K || (x < S.K && load + P.size[e] > S.C)) infeasible = true;
-      const double dv = fabs(V[s] - Vr[at]);
-      bad = bad || load != W.load[at] || !(dv <= delta);
+      bad = bad || load != W.load[at] || V[s] != Vr[at];
     } else {
       bad = bad || __float_as_uint(V[s]) != __float_as_uint(Vr[at]);
     }
