@@ -187,8 +187,8 @@ int policy_extract_f64(mdpvi_mdp_t h, const double *V, uint8_t *pi, float *gap,
  * none) is the same in all states that differ by a host permutation, such as
  * the least-loaded heuristic, has an invariant value.  When V^0 is invariant
  * too (the same value in all states of an orbit), the sweeps run on one state
- * per orbit, in every sweep form (mdp_set_orbits); the result differs from that
- * of the full sweeps in the rounding of FP64 sums.
+ * per orbit, unless the caller chose a sweep form (mdp_set_orbits); the result
+ * differs from that of the full sweeps in the rounding of FP64 sums.
  * Errors as vi_solve.                                                       */
 int policy_eval(mdpvi_mdp_t h, const uint8_t *pi, double *V, double tol,
                 int64_t max_iter, void *hip_stream, mdpvi_stats *st);
@@ -304,7 +304,8 @@ int vi_solve_bsdi(mdpvi_mdp_t h, float *V, double tol, int64_t max_iter, int32_t
                   void *hip_stream, mdpvi_stats *st);
 
 /* Choice of the sweep kernels for this handle (a tuning knob; every form
- * computes bit-identical iterates).  slab_digits = -1: automatic (the
+ * computes bit-identical iterates: a handle on which it was called evaluates
+ * policies by full sweeps, mdp_set_orbits).  slab_digits = -1: automatic (the
  * default); 0: the direct forms (every neighbour read from global memory);
  * t in 1..K-1: the LDS slab form of value iteration, each workgroup staging
  * the (C+1)^t occupancies that share the high digits (evaluation: direct);
@@ -392,10 +393,12 @@ int batch_set_round_form(mdpvi_batch_t b, int32_t op, int32_t opt);
 int batch_round_forms(mdpvi_batch_t b, int32_t *opt);
 
 /* Whether the batch's instances may be solved on the orbits of the host
- * permutations: 1 (the default) where an instance's start, and policy, are
- * invariant (vi_solve_batch with automatic round and tile forms,
- * policy_eval_batch and the evaluations of policy_iteration_batch; as
- * mdp_set_orbits, per instance); 0 never.  Errors: MDPVI_EINVAL (NULL).     */
+ * permutations where an instance's start, and policy, are invariant
+ * (vi_solve_batch with automatic round and tile forms, policy_eval_batch and
+ * the evaluations of policy_iteration_batch; as mdp_set_orbits, per instance).
+ * -1 (the default): evaluations until batch_set_round_form or
+ * batch_set_tile_form is called for them; 1: evaluations in every form;
+ * 0: never.  Errors: MDPVI_EINVAL (NULL).                                   */
 int batch_set_orbits(mdpvi_batch_t b, int32_t on);
 
 /* Tile form of the round kernels of operation op (0 value iteration, 1 FP64
@@ -473,9 +476,11 @@ int mdp_autotune(mdpvi_mdp_t h, const float *V, int32_t trials, void *hip_stream
 int32_t mdp_adjoint_form(mdpvi_mdp_t h);
 
 /* Whether solves of this handle may run on the orbits of the host
- * permutations (vi_solve in automatic mode, policy_eval and the evaluations of
- * policy_iteration): 1 (the default) where the start, and the policy, are
- * invariant; 0 never (a measurement aid: every state is then swept).
+ * permutations where the start, and the policy, are invariant (vi_solve in
+ * automatic mode, policy_eval and the evaluations of policy_iteration).
+ * -1 (the default): evaluations until mdp_set_sweep_form is called, whose
+ * forms, the automatic one included, share other bits; 1: evaluations in every
+ * form; 0: never (a measurement aid: every state is then swept).
  * Errors: MDPVI_EINVAL (NULL handle).                                       */
 int mdp_set_orbits(mdpvi_mdp_t h, int32_t on);
 

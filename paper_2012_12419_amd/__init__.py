@@ -235,7 +235,7 @@ class MDP:
 
     def set_orbits(self, on: bool = True):
         """Whether solves may run on the orbits of the host permutations
-        (mdp_set_orbits); off: every state is swept."""
+        (mdp_set_orbits): on, in every sweep form; off: every state is swept."""
         _check(load().mdp_set_orbits(self._h, 1 if on else 0))
 
     def sweep_forms(self):
@@ -430,7 +430,8 @@ class Batch:
 
     def set_orbits(self, on: bool = True):
         """Whether instances may be solved on the orbits of the host
-        permutations (batch_set_orbits); off: every state is swept."""
+        permutations (batch_set_orbits): on, in every evaluation form; off:
+        every state is swept."""
         _check(load().batch_set_orbits(self._h, 1 if on else 0))
 
     def tile_form_instances(self, op: str) -> int:

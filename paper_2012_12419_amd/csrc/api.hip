@@ -67,7 +67,8 @@ struct mdpvi_mdp {
   double* out_host = nullptr;   // pinned, 2 * kMaxJ + 3 doubles
   bool timing = false;          // bracket every sweep with events
   int adjoint_form = 0;         // adjoint sweep form: 0 automatic, else a valid form
-  bool orbits = true;           // solve invariant problems on their orbits
+  int orbits = -1;              // orbit form: 0 off, 1 on in every form, -1 automatic
+  bool form_chosen = false;     // mdp_set_sweep_form was called: evaluations in that form
   int slab_t = -1;              // sweep form: -1 automatic, 0 direct, t > 0 slab of t digits,
                                 // MDPVI_FORM_TILE the tile form
   hipEvent_t* sweep_ev = nullptr;   // 2 * kMaxChunk events (created on demand)
@@ -560,6 +561,16 @@ bool orbit_in_lds(const mdpvi::OrbitShape& S) {
          static_cast<uint64_t>(S.n) * S.L * reads <= 56000;
 }
 
+// Whether the handle's settings allow the form.  Value iteration: in the
+// automatic sweep form (its bits are the same in all).  Evaluation: its orbit
+// sums round otherwise than the full sweeps', so a caller who chose a sweep
+// form, the automatic one included, gets the bits that those share.
+template <class Op>
+bool orbit_allowed(const mdpvi_mdp* h) {
+  if (Op::kEval) return h->orbits > 0 || (h->orbits < 0 && !h->form_chosen);
+  return h->orbits != 0 && h->slab_t == -1;
+}
+
 // Whether a solve tries the form.  Launched sweeps need at least four times
 // fewer orbits than occupancies (K = 2 has two: its full sweep is as fast);
 // a handful of sweeps does not pay for the check and the expansion.
@@ -567,7 +578,7 @@ template <class Op>
 bool orbit_applies(mdpvi_mdp* h, int64_t max_iter) {
   OrbitPlan& O = h->orbit;
   if (O.covered < 0) O.covered = orbit_shape(h->M, &O.S) ? 1 : 0;
-  return h->orbits && O.covered == 1 && max_iter >= mdpvi::kOrbitChunk &&
+  return orbit_allowed<Op>(h) && O.covered == 1 && max_iter >= mdpvi::kOrbitChunk &&
          (orbit_in_lds<Op>(O.S) || O.S.n_occ >= 4ull * O.S.n);
 }
 
@@ -967,7 +978,8 @@ constexpr int kOrbitWords = 8;
 
 struct mdpvi_batch {
   OrbitBatch orbit;
-  bool orbits = true;                // solve invariant instances on their orbits
+  int orbits = -1;                   // orbit form: 0 off, 1 on, -1 automatic
+  bool eval_form_chosen = false;     // a form of the evaluation's rounds was set
   int n = 0;
   std::vector<Model> models;
   std::vector<int64_t> offsets;      // n + 1 state offsets
@@ -1103,7 +1115,7 @@ int mdp_sweep_forms(mdpvi_mdp_t h, int32_t* vi, int32_t* eval) {
 
 int mdp_set_orbits(mdpvi_mdp_t h, int32_t on) {
   if (!h) return fail(MDPVI_EINVAL, "NULL handle");
-  h->orbits = on != 0;
+  h->orbits = on < 0 ? -1 : on != 0;
   return MDPVI_OK;
 }
 
@@ -1120,6 +1132,7 @@ int mdp_set_sweep_form(mdpvi_mdp_t h, int32_t slab_digits) {
     if (!mdpvi::vi_tile_shape(h->M, &S))
       return fail(MDPVI_EINVAL, "the tile form does not apply to this instance");
     h->slab_t = slab_digits;
+    h->form_chosen = true;
     return MDPVI_OK;
   }
   if (is_row_form(slab_digits)) {
@@ -1127,6 +1140,7 @@ int mdp_set_sweep_form(mdpvi_mdp_t h, int32_t slab_digits) {
     if (!mdpvi::vi_row_shape(h->M, &S))
       return fail(MDPVI_EINVAL, "the row form does not apply to this instance");
     h->slab_t = slab_digits;
+    h->form_chosen = true;
     return MDPVI_OK;
   }
   if (slab_digits < -1 || slab_digits >= h->M.K)
@@ -1138,6 +1152,7 @@ int mdp_set_sweep_form(mdpvi_mdp_t h, int32_t slab_digits) {
       return fail(MDPVI_EINVAL, "a slab of %d digits does not fit the LDS budget", slab_digits);
   }
   h->slab_t = slab_digits;
+  h->form_chosen = true;
   return MDPVI_OK;
 }
 
@@ -1366,7 +1381,7 @@ int vi_solve(mdpvi_mdp_t h, float* V, double tol, int64_t max_iter, void* hip_st
   if (!(tol > 0)) return fail(MDPVI_EINVAL, "tol=%g must be > 0", tol);
   if (max_iter < 1) return fail(MDPVI_EINVAL, "max_iter=%lld must be >= 1", (long long)max_iter);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  if (h->slab_t == -1 && orbit_applies<mdpvi::OrbitVi>(h, max_iter)) {
+  if (orbit_applies<mdpvi::OrbitVi>(h, max_iter)) {
     const int orc = orbit_solve<mdpvi::OrbitVi>(h, nullptr, V, tol, max_iter, s, st);
     if (orc != kOrbitRefused && orc != kOrbitNoMemory) return orc;
   }
@@ -2470,9 +2485,14 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
   return MDPVI_OK;
 }
 
-// Whether a call tries the orbit form at all.
+// Whether a call tries the orbit form at all (orbit_allowed, for the batch's
+// forms: value iteration's have the same bits, the evaluation's only among
+// themselves).
+template <class Op>
 bool orbit_batch_applies(const mdpvi_batch* b, int64_t max_iter) {
-  return b->orbits && max_iter >= mdpvi::kOrbitChunk && !(b->orbit.built && b->orbit.inst.empty());
+  const bool allowed = Op::kEval ? b->orbits > 0 || (b->orbits < 0 && !b->eval_form_chosen)
+                                 : b->orbits != 0 && b->round_opt[0] == 0 && b->tile_mode[0] < 0;
+  return allowed && max_iter >= mdpvi::kOrbitChunk && !(b->orbit.built && b->orbit.inst.empty());
 }
 
 // Value iteration (pi NULL) or evaluation of pi on the orbits, for the
@@ -2688,7 +2708,7 @@ int vi_solve_batch(mdpvi_batch_t b, float* V, double tol, int64_t max_iter, void
   HIP_TRY(hipEventRecord(b->ev0, s));
   std::vector<mdpvi::BatchOut> done(b->n, mdpvi::BatchOut{0, 0.0});
   int n_left = b->n;
-  if (b->round_opt[0] == 0 && b->tile_mode[0] < 0 && orbit_batch_applies(b, max_iter)) {
+  if (orbit_batch_applies<mdpvi::OrbitVi>(b, max_iter)) {
     rc = orbit_batch_solve<mdpvi::OrbitVi>(b, nullptr, V, tol, max_iter, s, nullptr, done, &n_left);
     if (rc) return rc;
   }
@@ -2909,7 +2929,7 @@ int policy_eval_batch(mdpvi_batch_t b, const uint8_t* pi, double* V, double tol,
   std::vector<mdpvi::BatchOut> done(b->n, mdpvi::BatchOut{0, 0.0});
   int n_left = b->n;
   HIP_TRY(hipEventRecord(b->ev0, s));
-  if (orbit_batch_applies(b, max_iter) &&
+  if (orbit_batch_applies<mdpvi::OrbitEval>(b, max_iter) &&
       (rc = orbit_batch_solve<mdpvi::OrbitEval>(b, pi, V, tol, max_iter, s, nullptr, done, &n_left)))
     return rc;
   if (n_left < b->n) {
@@ -2971,7 +2991,7 @@ int policy_iteration_batch(mdpvi_batch_t b, uint8_t* pi, double* V, double eval_
     std::vector<mdpvi::BatchOut> done(n, mdpvi::BatchOut{0, 0.0});
     int n_left = n_active;
     HIP_TRY(hipEventRecord(b->ev0, s));
-    if (orbit_batch_applies(b, eval_max_iter) &&
+    if (orbit_batch_applies<mdpvi::OrbitEval>(b, eval_max_iter) &&
         (rc = orbit_batch_solve<mdpvi::OrbitEval>(b, pi, V, eval_tol, eval_max_iter, s, b->d_active[a], done, &n_left)))
       break;
     const int* left = b->d_active[a];   // the instances evaluated by full sweeps
@@ -3067,6 +3087,7 @@ int batch_set_round_form(mdpvi_batch_t b, int32_t op, int32_t opt) {
   if (opt != 0 && opt != 1 && opt != 2 && opt != 4)
     return fail(MDPVI_EINVAL, "occupancies per thread %d not in {0, 1, 2, 4}", opt);
   b->round_opt[op] = opt;
+  if (op == 1) b->eval_form_chosen = true;
   return MDPVI_OK;
 }
 
@@ -3078,7 +3099,7 @@ int batch_round_forms(mdpvi_batch_t b, int32_t* opt) {
 
 int batch_set_orbits(mdpvi_batch_t b, int32_t on) {
   if (!b) return fail(MDPVI_EINVAL, "NULL batch");
-  b->orbits = on != 0;
+  b->orbits = on < 0 ? -1 : on != 0;
   return MDPVI_OK;
 }
 
@@ -3087,6 +3108,7 @@ int batch_set_tile_form(mdpvi_batch_t b, int32_t op, int32_t mode) {
   if (op < 0 || op > 1) return fail(MDPVI_EINVAL, "operation %d outside 0..1", op);
   if (mode < -1 || mode > 1) return fail(MDPVI_EINVAL, "mode=%d not in {-1, 0, 1}", mode);
   b->tile_mode[op] = mode;
+  if (op == 1) b->eval_form_chosen = true;
   return MDPVI_OK;
 }
 

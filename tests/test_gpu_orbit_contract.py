@@ -59,3 +59,65 @@ def test_batch_evaluation_keeps_its_start(mdpvi):
         V, _, its, res = b.policy_eval(b.policy_greedy("least_loaded"), V, tol=0.1)
         outs.append((V, its, res))
     assert outs[0][1:] == outs[1][1:] and torch.equal(outs[0][0], outs[1][0])
+
+
+# A chosen form evaluates by full sweeps: the bits of the form with orbits off.
+# first and last: the forms of one instance with and without orbit LDS solves.
+@pytest.mark.parametrize("K,C,J", [(3, 8, 2), (5, 10, 2)])
+def test_chosen_sweep_forms_are_run(mdpvi, K, C, J):
+    import torch
+    p = _inst(K, C, J)
+    pi = mdpvi.MDP.from_instance(p).policy_greedy("least_loaded")
+    forms = [0, -1] + ([mdpvi.FORM_TILE] if K >= 4 else [])
+
+    def run(form=None, orbits=None):
+        mdp = mdpvi.MDP.from_instance(p)
+        if orbits is not None:
+            mdp.set_orbits(orbits)
+        if form is not None:
+            mdp.set_sweep_form(form)
+        V, _ = mdp.policy_eval(pi, tol=1e-10)
+        q = pi.clone()
+        V2 = torch.zeros_like(V)
+        mdp.policy_iteration(q, V2, eval_tol=1e-10, improve_tol=1e-8, max_rounds=20)
+        return V, V2
+
+    full = run(0, False)
+    free = run()
+    assert not torch.equal(free[0], full[0])   # the orbit sums round otherwise at these shapes
+    for f in forms:
+        for x, y in zip(run(f), full):
+            assert torch.equal(x, y), f
+        for x, y in zip(run(f, True), free):   # asked for by name: on in every form
+            assert torch.equal(x, y), f
+
+
+def test_chosen_batch_forms_are_run(mdpvi):
+    import torch
+    insts = [_inst(3, 8, 2), _inst(5, 10, 2), _inst(4, 12, 3)]
+
+    def run(choose=lambda b: None):
+        b = mdpvi.Batch(insts)
+        choose(b)
+        pi = b.policy_greedy("least_loaded")
+        V = b.policy_eval(pi, tol=1e-10)[0]
+        V2 = torch.zeros_like(V)
+        b.policy_iteration(pi, V2, eval_tol=1e-10, improve_tol=1e-8)
+        return V, V2
+
+    full = run(lambda b: b.set_orbits(False))
+    free = run()
+    assert not torch.equal(free[0], full[0])
+    for choose in (lambda b: b.set_round_form("eval", 2), lambda b: b.set_round_form("eval", 0),
+                   lambda b: b.set_tile_form("eval", 1), lambda b: b.set_tile_form("eval", 0)):
+        for x, y in zip(run(choose), full):
+            assert torch.equal(x, y)
+
+        def both(b):
+            b.set_orbits(True)
+            choose(b)
+        for x, y in zip(run(both), free):
+            assert torch.equal(x, y)
+    for op in ("vi", "adjoint"):   # of another operation: nothing to the evaluation
+        for x, y in zip(run(lambda b: b.set_round_form(op, 2)), free):
+            assert torch.equal(x, y)
