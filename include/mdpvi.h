@@ -135,8 +135,8 @@ int64_t mdp_feasible_pairs(mdpvi_mdp_t h);
  * solution) stays so.  In automatic mode (mdp_set_sweep_form) the call checks
  * V^0 on the device and, when it is invariant, sweeps one state per orbit of
  * the permutations and writes the result to every state: the iterates of the
- * full sweeps, bit for bit (for values within a factor of 2^21 of each other
- * or zero, whose sums the sweeps form exactly; beyond that two forms may
+ * full sweeps, bit for bit (for values within a factor of 2^29 / (K C) of each
+ * other or zero, whose sums the sweeps form exactly; beyond that two forms may
  * round a sum differently in its last FP64 place).  Otherwise every state is
  * swept.  st->backups and st->bytes count the full state space either way.
  * Errors: MDPVI_EINVAL (NULL, tol <= 0 or NaN, max_iter < 1), MDPVI_ENOCONV

@@ -47,11 +47,11 @@ __device__ __forceinline__ void st_f64(BufView v, double x, uint32_t lane_off, u
 
 // The part of a backup that no action changes: releases and idling
 // S = sum_k n_k V(n - 1_k) + (KC - |n|) V(n) and host resets rs = sum_k
-// V(n^{k<-0}), weighted.  S and rs have small whole-number weights, so for
-// FP32 values they are exact in FP64 (values within a factor of 2^22 of each
-// other: 24 bits, at most 8 of weight and 21 of range) and do not depend on
-// the order of the hosts: a sweep maps an iterate that is invariant under
-// host permutations to one that is, bit for bit.
+// V(n^{k<-0}), weighted.  S and rs have whole-number weights of KC and K in
+// all, so for FP32 values within a factor of 2^29 / KC of each other they are
+// exact in FP64 (24 bits of a value, log2(KC) of weight, the rest of the 53 of
+// range) and do not depend on the order of the hosts: a sweep maps an iterate
+// that is invariant under host permutations to one that is, bit for bit.
 __device__ __forceinline__ double stay_sum(const Model& M, double S, double rs) {
   return fma(M.nu_L, rs, M.mu_L * S);
 }

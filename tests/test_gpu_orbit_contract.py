@@ -121,3 +121,32 @@ def test_chosen_batch_forms_are_run(mdpvi):
     for op in ("vi", "adjoint"):   # of another operation: nothing to the evaluation
         for x, y in zip(run(lambda b: b.set_round_form(op, 2)), free):
             assert torch.equal(x, y)
+
+
+# More units than the exact sums' 2^21 range of values has room for (K C > 256):
+# 300, 540 and 264 of them, launched sweeps with 16- and 32-bit tables.
+@pytest.mark.parametrize("K,C", [(3, 100), (3, 180), (4, 66)])
+def test_same_bits_over_the_stated_range(mdpvi, K, C):
+    """Value iteration from an invariant start whose values spread over the
+    factor 2^29 / (K C) that the header states: the full sweeps' bits."""
+    import math
+    import torch
+    p = _inst(K, C, 1, gamma=0.95)
+    g = torch.Generator(device="cuda").manual_seed(K * C)
+    per_digit = torch.rand(C + 1, generator=g, device="cuda", dtype=torch.float64)
+    o = torch.arange(p.num_states, device="cuda")
+    u = torch.zeros(p.num_states, dtype=torch.float64, device="cuda")
+    digits = torch.stack([o // (C + 1) ** k % (C + 1) for k in range(K)]).sort(dim=0).values
+    for d in digits:                       # in the order of the sorted digits: the same bits over an orbit
+        u = (u + 7 * per_digit[d]) % 1.0
+    V0 = torch.exp2(u * math.log2(2 ** 29 / (K * C))).float()
+    outs = []
+    for orbits in (True, False):
+        mdp = mdpvi.MDP.from_instance(p)
+        mdp.set_orbits(orbits)
+        V = V0.clone()
+        with pytest.raises(mdpvi.MdpviError) as e:
+            mdp.vi_solve(V, tol=1e-30, max_iter=40)
+        assert e.value.code == mdpvi.ENOCONV
+        outs.append((V, e.value.stats["residual_inf"]))
+    assert outs[0][1] == outs[1][1] and torch.equal(outs[0][0].view(torch.int32), outs[1][0].view(torch.int32))
