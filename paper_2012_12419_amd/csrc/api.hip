@@ -95,6 +95,7 @@ int fail(int code, const char* fmt, ...) {
 }
 
 int fail_hip(hipError_t e, const char* what) {
+  (void)hipGetLastError();   // reported here, not again by the next launch
   return fail(MDPVI_EDEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
@@ -106,51 +107,63 @@ int fail_hip(hipError_t e, const char* what) {
 
 bool is_finite(double x) { return std::isfinite(x); }
 
+// Device memory of a handle; false when there is none.  A failed attempt
+// leaves no error behind for the next launch to report.
+template <typename T>
+bool handle_malloc(mdpvi_mdp* h, T** p, size_t bytes) {
+  (void)h;
+  if (hipMalloc(reinterpret_cast<void**>(p), bytes) == hipSuccess) return true;
+  *p = nullptr;
+  (void)hipGetLastError();
+  return false;
+}
+
+template <typename T>
+bool pinned_malloc(T** p, size_t bytes) {
+  if (hipHostMalloc(reinterpret_cast<void**>(p), bytes, hipHostMallocDefault) == hipSuccess) return true;
+  *p = nullptr;
+  (void)hipGetLastError();
+  return false;
+}
+
 // Device scratch of a handle: control words, pinned mirror, events and a
 // ping-pong partner of at least `bytes`.  Bound to the device current at
-// first use.
+// first use.  Each piece is there or NULL, so that a call after a failed one
+// goes on from what is missing.
 int ensure_scratch(mdpvi_mdp* h, size_t bytes) {
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
   if (h->device >= 0 && h->device != dev)
     return fail(MDPVI_EINVAL, "handle scratch lives on device %d, current device is %d", h->device,
                 dev);
-  if (!h->ctl) {
-    if (hipMalloc(&h->ctl, sizeof(Ctl)) != hipSuccess) {
-      h->ctl = nullptr;
-      return fail(MDPVI_ENOMEM, "hipMalloc of %zu control bytes failed", sizeof(Ctl));
-    }
-    if (hipHostMalloc(reinterpret_cast<void**>(&h->ctl_host), sizeof(Ctl), hipHostMallocDefault) !=
-        hipSuccess) {
-      h->ctl_host = nullptr;
-      return fail(MDPVI_ENOMEM, "hipHostMalloc of the control mirror failed");
-    }
-    HIP_TRY(hipEventCreate(&h->ev0));
-    HIP_TRY(hipEventCreate(&h->ev1));
-    // the largest grid of any sweep form: the direct form, or the slab form
-    // with one low digit (n_occ / (C+1) workgroups)
-    const uint64_t g1 = static_cast<uint64_t>(h->M.n_occ) / static_cast<uint64_t>(h->M.R);
-    const uint32_t gmax = std::max<uint32_t>(
-        std::max(std::max(mdpvi::occ_sweep_grid(h->M), mdpvi::eval_sweep_grid(h->M)), mdpvi::vi_sweep_grid(h->M, 0)),
-        static_cast<uint32_t>(g1));
-    h->res_n = mdpvi::res_doubles(gmax);
-    if (hipMalloc(reinterpret_cast<void**>(&h->res), h->res_n * sizeof(double)) != hipSuccess) {
-      h->res = nullptr;
-      return fail(MDPVI_ENOMEM, "hipMalloc of %zu residual words failed", h->res_n);
-    }
-    if (hipHostMalloc(reinterpret_cast<void**>(&h->res_host), h->res_n * sizeof(double),
-                      hipHostMallocDefault) != hipSuccess) {
-      h->res_host = nullptr;
-      return fail(MDPVI_ENOMEM, "hipHostMalloc of the residual mirror failed");
-    }
-    h->device = dev;
-  }
+  if (!h->ctl && !handle_malloc(h, &h->ctl, sizeof(Ctl)))
+    return fail(MDPVI_ENOMEM, "hipMalloc of %zu control bytes failed", sizeof(Ctl));
+  h->device = dev;
+  if (!h->ctl_host && !pinned_malloc(&h->ctl_host, sizeof(Ctl)))
+    return fail(MDPVI_ENOMEM, "hipHostMalloc of the control mirror failed");
+  for (hipEvent_t* e : {&h->ev0, &h->ev1})
+    if (!*e) HIP_TRY(hipEventCreate(e));
+  // the largest grid of any sweep form: the direct form, or the slab form
+  // with one low digit (n_occ / (C+1) workgroups)
+  const uint64_t g1 = static_cast<uint64_t>(h->M.n_occ) / static_cast<uint64_t>(h->M.R);
+  const uint32_t gmax = std::max<uint32_t>(
+      std::max(std::max(mdpvi::occ_sweep_grid(h->M), mdpvi::eval_sweep_grid(h->M)), mdpvi::vi_sweep_grid(h->M, 0)),
+      static_cast<uint32_t>(g1));
+  h->res_n = mdpvi::res_doubles(gmax);
+  if (!h->res && !handle_malloc(h, &h->res, h->res_n * sizeof(double)))
+    return fail(MDPVI_ENOMEM, "hipMalloc of %zu residual words failed", h->res_n);
+  if (!h->res_host && !pinned_malloc(&h->res_host, h->res_n * sizeof(double)))
+    return fail(MDPVI_ENOMEM, "hipHostMalloc of the residual mirror failed");
   if (!h->d_model) {
-    if (hipMalloc(reinterpret_cast<void**>(&h->d_model), sizeof(Model)) != hipSuccess) {
-      h->d_model = nullptr;
+    Model* d = nullptr;
+    if (!handle_malloc(h, &d, sizeof(Model)))
       return fail(MDPVI_ENOMEM, "hipMalloc of %zu model bytes failed", sizeof(Model));
+    const hipError_t e = hipMemcpy(d, &h->M, sizeof(Model), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      (void)hipFree(d);
+      return fail_hip(e, "hipMemcpy(model)");
     }
-    HIP_TRY(hipMemcpy(h->d_model, &h->M, sizeof(Model), hipMemcpyHostToDevice));
+    h->d_model = d;
   }
   if (bytes > h->vbuf_bytes) {
     if (h->vbuf) {
@@ -159,10 +172,8 @@ int ensure_scratch(mdpvi_mdp* h, size_t bytes) {
       h->vbuf = nullptr;
       h->vbuf_bytes = 0;
     }
-    if (hipMalloc(&h->vbuf, bytes) != hipSuccess) {
-      h->vbuf = nullptr;
+    if (!handle_malloc(h, &h->vbuf, bytes))
       return fail(MDPVI_ENOMEM, "hipMalloc of a %zu-byte value buffer failed", bytes);
-    }
     h->vbuf_bytes = bytes;
   }
   return MDPVI_OK;
@@ -186,10 +197,8 @@ int ensure_aux(mdpvi_mdp* h, size_t doubles) {
       h->aux = nullptr;
       h->aux_bytes = 0;
     }
-    if (hipMalloc(reinterpret_cast<void**>(&h->aux), bytes) != hipSuccess) {
-      h->aux = nullptr;
+    if (!handle_malloc(h, &h->aux, bytes))
       return fail(MDPVI_ENOMEM, "hipMalloc of %zu auxiliary bytes failed", bytes);
-    }
     h->aux_bytes = bytes;
   }
   return MDPVI_OK;
@@ -203,10 +212,8 @@ int tune_lookup(const Model& M, const char* op);
 int arrival_arrays(mdpvi_mdp* h, const float* V, hipStream_t s, double* A[2]) {
   const Model& M = h->M;
   const size_t per = static_cast<size_t>(M.n_occ) + mdpvi::kSentinel;
-  if (!h->abuf && hipMalloc(reinterpret_cast<void**>(&h->abuf), 2 * per * sizeof(double)) != hipSuccess) {
-    h->abuf = nullptr;
+  if (!h->abuf && !handle_malloc(h, &h->abuf, 2 * per * sizeof(double)))
     return fail(MDPVI_ENOMEM, "hipMalloc of the arrival-term arrays failed");
-  }
   A[0] = h->abuf;
   A[1] = h->abuf + per;
   HIP_TRY(mdpvi::launch_arrival_init(M, V, A[0], A[1], s));
@@ -359,10 +366,8 @@ int set_tile_order(mdpvi_mdp* h, mdpvi::TileShape* S, double ws, const char* op,
       mdpvi::tile_deal(*S, run, &order);
     else
       mdpvi::tile_partition(h->M.K, h->M.R, *S, &order);
-    if (hipMalloc(reinterpret_cast<void**>(&d), order.size() * sizeof(uint32_t)) != hipSuccess) {
-      d = nullptr;
+    if (!handle_malloc(h, &d, order.size() * sizeof(uint32_t)))
       return fail(MDPVI_ENOMEM, "hipMalloc of the tile order failed");
-    }
     const hipError_t e = hipMemcpy(d, order.data(), order.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
       (void)hipFree(d);
@@ -608,20 +613,14 @@ int orbit_ensure(mdpvi_mdp* h, hipStream_t s) {
   size_t o_v[2], o_a[2];
   for (size_t& o : o_v) o = take(n * O.S.L * sizeof(double));
   for (size_t& o : o_a) o = take((n + 1) * sizeof(double));
-  if (!O.mirror) {
-    if (hipHostMalloc(reinterpret_cast<void**>(&O.mirror), sizeof(mdpvi::OrbitCtl), hipHostMallocDefault) !=
-        hipSuccess) {
-      O.mirror = nullptr;
-      return fail(MDPVI_ENOMEM, "hipHostMalloc of the control mirror failed");
-    }
-  }
+  if (!O.mirror && !pinned_malloc(&O.mirror, sizeof(mdpvi::OrbitCtl)))
+    return fail(MDPVI_ENOMEM, "hipHostMalloc of the control mirror failed");
   for (hipEvent_t* e : {&O.ev0, &O.ev1})
     if (!*e) HIP_TRY(hipEventCreate(e));
   for (hipEvent_t& e : O.step)
     if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   unsigned char* d = nullptr;
-  if (hipMalloc(reinterpret_cast<void**>(&d), at) != hipSuccess)
-    return fail(MDPVI_ENOMEM, "hipMalloc of %zu orbit bytes failed", at);
+  if (!handle_malloc(h, &d, at)) return fail(MDPVI_ENOMEM, "hipMalloc of %zu orbit bytes failed", at);
   O.S.binom = reinterpret_cast<uint32_t*>(d + o_bin);
   O.S.dig = reinterpret_cast<uint64_t*>(d + o_dig);
   O.S.rep = reinterpret_cast<uint32_t*>(d + o_rep);
@@ -655,10 +654,7 @@ template <class Op>
 int orbit_solve(mdpvi_mdp* h, const uint8_t* pi, typename Op::T* V, double tol, int64_t max_iter, hipStream_t s,
                 mdpvi_stats* st) {
   int rc = orbit_ensure(h, s);
-  if (rc == MDPVI_ENOMEM) {   // the full sweeps need none of it
-    (void)hipGetLastError();
-    return kOrbitNoMemory;
-  }
+  if (rc == MDPVI_ENOMEM) return kOrbitNoMemory;   // the full sweeps need none of it
   if (rc) return rc;
   OrbitPlan& O = h->orbit;
   const Model& M = h->M;
@@ -1264,8 +1260,7 @@ int mdp_autotune(mdpvi_mdp_t h, const float* V, int32_t trials, void* hip_stream
   // buffers only
   uint8_t* pol = nullptr;
   double* ev[2] = {nullptr, nullptr};
-  if (hipMalloc(reinterpret_cast<void**>(&pol), N + 16) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void**>(&ev[0]), 2 * N * sizeof(double)) != hipSuccess) {
+  if (!handle_malloc(h, &pol, N + 16) || !handle_malloc(h, &ev[0], 2 * N * sizeof(double))) {
     if (pol) (void)hipFree(pol);
     return fail(MDPVI_ENOMEM, "hipMalloc of the tuning buffers failed");
   }
@@ -1284,10 +1279,8 @@ int mdp_autotune(mdpvi_mdp_t h, const float* V, int32_t trials, void* hip_stream
     if (mdpvi::eval_tile_shape(M, &Se)) {
       for (int w = 0; w <= 5; ++w) eforms.push_back(MDPVI_FORM_TILE + w);
       const size_t per = static_cast<size_t>(M.n_occ) + mdpvi::kSentinel;
-      if (!h->abuf && hipMalloc(reinterpret_cast<void**>(&h->abuf), 2 * per * sizeof(double)) != hipSuccess) {
-        h->abuf = nullptr;
+      if (!h->abuf && !handle_malloc(h, &h->abuf, 2 * per * sizeof(double)))
         return fail(MDPVI_ENOMEM, "hipMalloc of the arrival-term arrays failed");
-      }
       Ae[0] = h->abuf;
       Ae[1] = h->abuf + per;
       int orc = set_tile_order(h, &Se, eval_working_set(M), "eval");
@@ -1670,10 +1663,8 @@ int eval_run(mdpvi_mdp* h, const uint8_t* pi, double* V, double tol, int64_t max
   mdpvi::TileShape S{};
   if (eval_form(h, &S) != 0) {
     const size_t per = static_cast<size_t>(M.n_occ) + mdpvi::kSentinel;
-    if (!h->abuf && hipMalloc(reinterpret_cast<void**>(&h->abuf), 2 * per * sizeof(double)) != hipSuccess) {
-      h->abuf = nullptr;
+    if (!h->abuf && !handle_malloc(h, &h->abuf, 2 * per * sizeof(double)))
       return fail(MDPVI_ENOMEM, "hipMalloc of the arrival-term arrays failed");
-    }
     double* A[2] = {h->abuf, h->abuf + per};
     int orc = set_tile_order(h, &S, eval_working_set(M), "eval");
     if (orc) return orc;
@@ -1712,12 +1703,8 @@ int policy_iteration(mdpvi_mdp_t h, uint8_t* pi, double* V, double eval_tol, int
   const size_t N = static_cast<size_t>(M.n_states);
   int rc = ensure_scratch(h, N * sizeof(double));
   if (rc) return rc;
-  if (!h->pbuf) {
-    if (hipMalloc(reinterpret_cast<void**>(&h->pbuf), N + 16) != hipSuccess) {
-      h->pbuf = nullptr;
-      return fail(MDPVI_ENOMEM, "hipMalloc of the policy scratch failed");
-    }
-  }
+  if (!h->pbuf && !handle_malloc(h, &h->pbuf, N + 16))
+    return fail(MDPVI_ENOMEM, "hipMalloc of the policy scratch failed");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   HIP_TRY(mdpvi::launch_ctl_init(h->ctl, h->res, s));
   HIP_TRY(mdpvi::launch_policy_check(M, pi, h->ctl, s));

@@ -1,0 +1,126 @@
+"""Scratch memory at its limits, on the host: the library runs in a process of
+its own against a stand-in HIP runtime (fake_hip.c) whose allocations and
+copies fail on demand.  Kernels do not run, so solves end with ENOCONV or ENAN;
+what counts is the code, the kernels that would have been launched and the
+memory held."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, sys
+sys.path.insert(0, {root!r})
+f = ctypes.CDLL({fake!r}, mode=ctypes.RTLD_GLOBAL)
+f.fake_log.restype = ctypes.c_char_p
+f.fake_first_arg.restype = ctypes.c_void_p
+for n in ("fake_live", "fake_peak"):
+    getattr(f, n).restype = ctypes.c_size_t
+f.fake_set_budget.argtypes = [ctypes.c_size_t]
+import paper_2012_12419_amd as m
+assert "torch" not in sys.modules
+lib = m.load()
+def params(K, C, J):
+    return m.make_params(K, C, [1 + j for j in range(J)], [0.5] * J, 0.1, 0.02, [1.0 + j for j in range(J)], 0.9)
+def handle(K, C, J):
+    p, keep = params(K, C, J)
+    h = ctypes.c_void_p()
+    assert lib.mdp_build(ctypes.byref(p), ctypes.byref(h)) == m.OK
+    return h
+def batch(shapes):
+    ps = [params(*s) for s in shapes]
+    a = (m.Params * len(ps))(*[p for p, _ in ps])
+    b = ctypes.c_void_p()
+    assert lib.mdp_build_batch(a, len(ps), ctypes.byref(b)) == m.OK
+    return b
+V = ctypes.create_string_buffer(8 << 22)      # stands for every device array of a caller
+pi = ctypes.create_string_buffer(1 << 22)
+def log():
+    return f.fake_log().decode()
+def vi(h, it=40):
+    return lib.vi_solve(h, V, 1e-6, it, None, None)
+def ev(h, it=40):
+    return lib.policy_eval(h, pi, V, 1e-6, it, None, None)
+def vib(b, it=40):
+    return lib.vi_solve_batch(b, V, 1e-6, it, None, None, None, None)
+def evb(b, it=40):
+    return lib.policy_eval_batch(b, pi, V, 1e-6, it, None, None, None, None)
+RAN = (m.ENOCONV, m.ENAN)
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    if not shutil.which("gcc"):
+        pytest.skip("no host compiler")
+    d = tmp_path_factory.mktemp("fake_hip")
+    fake = str(d / "libamdhip64.so.7")
+    vers = d / "versions"
+    vers.write_text("hip_4.2 { *; };\nhip_4.3 { hipGraph*; };\nhip_6.0 { hipGetDeviceProperties*; };\n")
+    subprocess.run(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-Wl,-soname,libamdhip64.so.7",
+                    f"-Wl,--version-script={vers}", os.path.join(HERE, "fake_hip.c"), "-o", fake], check=True)
+
+    def go(body):
+        code = PRELUDE.format(root=ROOT, fake=fake) + body
+        r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+    return go
+
+
+def test_every_failed_allocation_of_a_handle_is_made_up_for(run):
+    """Each allocation of the full sweeps fails once: ENOMEM, and the next call
+    on the handle runs; nothing is left allocated."""
+    run("""
+before = f.fake_live()
+for call in (vi, ev):
+    for fail in (f.fake_fail_malloc, f.fake_fail_host):
+        for n in range(20):
+            f.fake_reset()
+            h = handle(5, 10, 2)
+            lib.mdp_set_orbits(h, 0)
+            fail(n)
+            rc = call(h)
+            if rc in RAN:
+                assert n >= 2
+                break
+            assert rc == m.ENOMEM, (n, rc, lib.mdpvi_last_error())
+            assert call(h) in RAN, (n, lib.mdpvi_last_error())
+            lib.mdp_free(h)
+        else:
+            raise AssertionError("never ran")
+        lib.mdp_free(h)
+assert f.fake_live() == before
+""")
+
+
+def test_a_failed_copy_of_the_model_is_made_again(run):
+    """The evaluation sweeps read the model from device memory: after a failed
+    copy the next call copies it again."""
+    run("""
+h = handle(4, 6, 2)
+lib.mdp_set_orbits(h, 0)
+f.fake_fail_copy(0)
+assert ev(h) == m.EDEVICE
+rc = ev(h)
+assert rc in RAN, (rc, lib.mdpvi_last_error())
+at = f.fake_first_arg(b"eval_exact_kernel")
+K, C, J = ctypes.cast(at, ctypes.POINTER(ctypes.c_int32 * 3)).contents
+assert (K, C, J) == (4, 6, 2)
+""")
+
+
+def test_a_solve_without_memory_for_the_tables_takes_the_full_sweeps(run):
+    run("""
+for fail in (f.fake_fail_malloc, f.fake_fail_host):
+    f.fake_reset()
+    h = handle(6, 7, 2)
+    fail(0)
+    assert vi(h) in RAN
+    assert "vi_" in log() or "sweep" in log()
+    lib.mdp_free(h)
+""")
