@@ -107,15 +107,29 @@ int fail_hip(hipError_t e, const char* what) {
 
 bool is_finite(double x) { return std::isfinite(x); }
 
-// Device memory of a handle; false when there is none.  A failed attempt
-// leaves no error behind for the next launch to report.
+// Gives the orbit form's device memory back (the next solve that wants it
+// allocates it again).  No orbit kernel may be running.
+void orbit_release(mdpvi_mdp* h) {
+  for (hipGraphExec_t& g : h->orbit.chunk) {
+    if (g) (void)hipGraphExecDestroy(g);
+    g = nullptr;
+  }
+  if (h->orbit.dev) (void)hipFree(h->orbit.dev);
+  h->orbit.dev = nullptr;
+}
+
+// Device memory of a handle; false when there is none.  The orbit form's
+// tables, which only save time, make room for it.  A failed attempt leaves no
+// error behind for the next launch to report.
 template <typename T>
 bool handle_malloc(mdpvi_mdp* h, T** p, size_t bytes) {
-  (void)h;
-  if (hipMalloc(reinterpret_cast<void**>(p), bytes) == hipSuccess) return true;
-  *p = nullptr;
-  (void)hipGetLastError();
-  return false;
+  for (;;) {
+    if (hipMalloc(reinterpret_cast<void**>(p), bytes) == hipSuccess) return true;
+    *p = nullptr;
+    (void)hipGetLastError();
+    if (!h->orbit.dev) return false;
+    orbit_release(h);
+  }
 }
 
 template <typename T>
@@ -956,6 +970,7 @@ struct OrbitBatch {
     std::vector<Rounds> rounds;
   };
   bool built = false;
+  bool no_memory = false;         // there was none for it, or other scratch needed it: not tried again
   std::vector<int32_t> inst;      // entry -> instance
   Operation op[2];
   unsigned char* dev = nullptr;
@@ -1087,9 +1102,7 @@ void mdp_free(mdpvi_mdp_t h) {
     for (uint32_t* o : per_t)
       if (o) (void)hipFree(o);
   if (h->out_host) (void)hipHostFree(h->out_host);
-  for (hipGraphExec_t g : h->orbit.chunk)
-    if (g) (void)hipGraphExecDestroy(g);
-  if (h->orbit.dev) (void)hipFree(h->orbit.dev);
+  orbit_release(h);
   if (h->orbit.mirror) (void)hipHostFree(h->orbit.mirror);
   for (hipEvent_t e : {h->orbit.ev0, h->orbit.ev1, h->orbit.step[0], h->orbit.step[1]})
     if (e) (void)hipEventDestroy(e);
@@ -2271,6 +2284,23 @@ int batch_offsets(mdpvi_batch_t b, int64_t* offsets) {
 
 namespace {
 
+// handle_malloc for a batch, whose plan takes long to rebuild: once it had to
+// make room, the batch does without.
+template <typename T>
+bool batch_malloc(mdpvi_batch* b, T** p, size_t bytes) {
+  for (;;) {
+    if (hipMalloc(reinterpret_cast<void**>(p), bytes) == hipSuccess) return true;
+    *p = nullptr;
+    (void)hipGetLastError();
+    OrbitBatch& O = b->orbit;
+    if (!O.dev) return false;
+    (void)hipFree(O.dev);
+    O.dev = nullptr;
+    O.built = false;
+    O.no_memory = true;
+  }
+}
+
 // The entries and lists of the batch's orbit form, and their device block.
 int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
   OrbitBatch& O = b->orbit;
@@ -2419,8 +2449,7 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
     for (auto& r : L.rounds)
       for (int k = 0; k < 2; ++k) o_act.push_back(take(r.tiles.size() * sizeof(mdpvi::Tile)));
   unsigned char* d = nullptr;
-  if (hipMalloc(reinterpret_cast<void**>(&d), at) != hipSuccess)
-    return fail(MDPVI_ENOMEM, "hipMalloc of %zu orbit bytes failed", at);
+  if (!batch_malloc(b, &d, at)) return fail(MDPVI_ENOMEM, "hipMalloc of %zu orbit bytes failed", at);
   for (int e = 0; e < n; ++e) {
     mdpvi::OrbitInst& I = inst[e];
     I.S.binom = reinterpret_cast<uint32_t*>(d + o_bin[e]);
@@ -2479,7 +2508,7 @@ template <class Op>
 bool orbit_batch_applies(const mdpvi_batch* b, int64_t max_iter) {
   const bool allowed = Op::kEval ? b->orbits > 0 || (b->orbits < 0 && !b->eval_form_chosen)
                                  : b->orbits != 0 && b->round_opt[0] == 0 && b->tile_mode[0] < 0;
-  return allowed && max_iter >= mdpvi::kOrbitChunk && !(b->orbit.built && b->orbit.inst.empty());
+  return allowed && !b->orbit.no_memory && max_iter >= mdpvi::kOrbitChunk && !(b->orbit.built && b->orbit.inst.empty());
 }
 
 // Value iteration (pi NULL) or evaluation of pi on the orbits, for the
@@ -2491,10 +2520,7 @@ template <class Op>
 int orbit_batch_solve(mdpvi_batch* b, const uint8_t* pi, typename Op::T* V, double tol, int64_t max_iter,
                       hipStream_t s, const int* active, std::vector<mdpvi::BatchOut>& done, int* n_left) {
   int rc = orbit_batch_ensure(b, s);
-  if (rc == MDPVI_ENOMEM) {   // the full forms need none of it
-    (void)hipGetLastError();
-    return MDPVI_OK;
-  }
+  if (rc == MDPVI_ENOMEM) return MDPVI_OK;   // the full forms need none of it
   if (rc) return rc;
   OrbitBatch& O = b->orbit;
   const int n = static_cast<int>(O.inst.size()), nt = static_cast<int>(b->tiles_all.size());
@@ -2603,10 +2629,8 @@ int batch_vi_full(mdpvi_batch* b, float* V, double tol, int64_t max_iter, hipStr
     std::vector<int32_t> sub;
     for (int32_t i : b->lds_list)
       if (on[i]) sub.push_back(i);
-    if (!b->d_sub && hipMalloc(reinterpret_cast<void**>(&b->d_sub), b->n * sizeof(int32_t)) != hipSuccess) {
-      b->d_sub = nullptr;
+    if (!b->d_sub && !batch_malloc(b, &b->d_sub, b->n * sizeof(int32_t)))
       return fail(MDPVI_ENOMEM, "hipMalloc of a batch list failed");
-    }
     n_lds = static_cast<int>(sub.size());
     if (n_lds) HIP_TRY(hipMemcpyAsync(b->d_sub, sub.data(), n_lds * sizeof(int32_t), hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));   // the list above is this call's own
@@ -2903,12 +2927,8 @@ int policy_eval_batch(mdpvi_batch_t b, const uint8_t* pi, double* V, double tol,
   if (!b || !pi || !V) return fail(MDPVI_EINVAL, "NULL batch, policy or value array");
   int rc = batch_args(b, tol, max_iter);
   if (rc) return rc;
-  if (!b->W2) {
-    if (hipMalloc(&b->W2, std::max<int64_t>(b->offsets[b->n], 1) * sizeof(double)) != hipSuccess) {
-      b->W2 = nullptr;
-      return fail(MDPVI_ENOMEM, "hipMalloc of the FP64 batch scratch failed");
-    }
-  }
+  if (!b->W2 && !batch_malloc(b, &b->W2, std::max<int64_t>(b->offsets[b->n], 1) * sizeof(double)))
+    return fail(MDPVI_ENOMEM, "hipMalloc of the FP64 batch scratch failed");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   int bad = -1;
   if ((rc = batch_check_policy(b, pi, s, &bad))) return rc;
@@ -2949,12 +2969,8 @@ int policy_iteration_batch(mdpvi_batch_t b, uint8_t* pi, double* V, double eval_
   if (max_rounds < 1) return fail(MDPVI_EINVAL, "max_rounds=%lld must be >= 1", (long long)max_rounds);
   int rc = batch_args(b, eval_tol, eval_max_iter);
   if (rc) return rc;
-  if (!b->W2) {
-    if (hipMalloc(&b->W2, std::max<int64_t>(b->offsets[b->n], 1) * sizeof(double)) != hipSuccess) {
-      b->W2 = nullptr;
-      return fail(MDPVI_ENOMEM, "hipMalloc of the FP64 batch scratch failed");
-    }
-  }
+  if (!b->W2 && !batch_malloc(b, &b->W2, std::max<int64_t>(b->offsets[b->n], 1) * sizeof(double)))
+    return fail(MDPVI_ENOMEM, "hipMalloc of the FP64 batch scratch failed");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   int bad = -1;
   if ((rc = batch_check_policy(b, pi, s, &bad))) return rc;
@@ -3126,8 +3142,8 @@ int batch_autotune(mdpvi_batch_t b, int32_t trials, void* hip_stream, int32_t* o
     (void)hipFree(w64);
     (void)hipFree(pol);
   };
-  if (hipMalloc(&v32, N * sizeof(float)) != hipSuccess || hipMalloc(&v64, N * sizeof(double)) != hipSuccess ||
-      hipMalloc(&w64, N * sizeof(double)) != hipSuccess || hipMalloc(&pol, N) != hipSuccess) {
+  if (!batch_malloc(b, &v32, N * sizeof(float)) || !batch_malloc(b, &v64, N * sizeof(double)) ||
+      !batch_malloc(b, &w64, N * sizeof(double)) || !batch_malloc(b, &pol, N)) {
     release();
     return fail(MDPVI_ENOMEM, "hipMalloc of the tuning buffers failed");
   }

@@ -114,6 +114,32 @@ assert (K, C, J) == (4, 6, 2)
 """)
 
 
+@pytest.mark.parametrize("call", ["vi", "ev"])
+@pytest.mark.parametrize("shape", [(6, 7, 2), (8, 9, 1), (3, 8, 2)])
+def test_orbit_tables_make_room_for_the_full_sweeps(run, call, shape):
+    """A call that the orbit form refuses, on a device with just the memory
+    that the full sweeps need, runs them."""
+    run(f"""
+shape, call = {shape}, {call}
+V = ctypes.create_string_buffer(16 * shape[2] * (shape[1] + 1) ** shape[0])
+pi = ctypes.create_string_buffer(shape[2] * (shape[1] + 1) ** shape[0])
+h = handle(*shape)
+lib.mdp_set_orbits(h, 0)
+assert call(h) in RAN
+need = f.fake_live()
+lib.mdp_free(h)
+for spare in (0, 4096, 1 << 16, 1 << 20):
+    f.fake_reset()
+    f.fake_refuse(1)
+    f.fake_set_budget(need + spare)
+    h = handle(*shape)
+    for _ in range(3):
+        assert call(h) in RAN, (spare, lib.mdpvi_last_error())
+    lib.mdp_free(h)
+    assert f.fake_live() == 0
+""")
+
+
 def test_a_solve_without_memory_for_the_tables_takes_the_full_sweeps(run):
     run("""
 for fail in (f.fake_fail_malloc, f.fake_fail_host):
@@ -123,4 +149,31 @@ for fail in (f.fake_fail_malloc, f.fake_fail_host):
     assert vi(h) in RAN
     assert "vi_" in log() or "sweep" in log()
     lib.mdp_free(h)
+""")
+
+
+SHAPES = "[(3, 8, 2), (4, 6, 3), (5, 9, 2), (6, 4, 2)]"
+
+
+def test_batch_plan_makes_room_for_later_scratch(run):
+    """The evaluation's FP64 scratch, allocated after a value iteration on
+    orbits, on a device with just the memory that the full forms need."""
+    run(f"""
+shapes = {SHAPES}
+b = batch(shapes)
+lib.batch_set_orbits(b, 0)
+vib(b)
+rc = evb(b)
+need = f.fake_live()
+lib.mdp_free_batch(b)
+f.fake_reset()
+b = batch(shapes)
+vib(b)
+assert "orbit_batch" in log()
+with_plan = f.fake_live()
+f.fake_set_budget(max(need, with_plan))
+assert with_plan + 8 * lib.batch_num_states(b, -1) > max(need, with_plan)
+assert evb(b) == rc, lib.mdpvi_last_error()
+lib.mdp_free_batch(b)
+assert f.fake_live() == 0
 """)
