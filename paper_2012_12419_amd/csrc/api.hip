@@ -2449,7 +2449,11 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
     for (auto& r : L.rounds)
       for (int k = 0; k < 2; ++k) o_act.push_back(take(r.tiles.size() * sizeof(mdpvi::Tile)));
   unsigned char* d = nullptr;
-  if (!batch_malloc(b, &d, at)) return fail(MDPVI_ENOMEM, "hipMalloc of %zu orbit bytes failed", at);
+  if ((!O.h_ctl && !pinned_malloc(&O.h_ctl, n * sizeof(mdpvi::OrbitCtl))) ||
+      (!O.h_words && !pinned_malloc(&O.h_words, 2 * kOrbitWords * sizeof(int))) || !batch_malloc(b, &d, at)) {
+    O.no_memory = true;
+    return fail(MDPVI_ENOMEM, "allocation of %zu orbit bytes failed", at);
+  }
   for (int e = 0; e < n; ++e) {
     mdpvi::OrbitInst& I = inst[e];
     I.S.binom = reinterpret_cast<uint32_t*>(d + o_bin[e]);
@@ -2471,10 +2475,6 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
   if (e == hipSuccess)
     e = mdpvi::launch_orbit_batch_table(O.d_inst, reinterpret_cast<mdpvi::Tile*>(d + o_tt),
                                         static_cast<int>(ttiles.size()), s);
-  if (e == hipSuccess && !O.h_ctl)
-    e = hipHostMalloc(reinterpret_cast<void**>(&O.h_ctl), n * sizeof(mdpvi::OrbitCtl), hipHostMallocDefault);
-  if (e == hipSuccess && !O.h_words)
-    e = hipHostMalloc(reinterpret_cast<void**>(&O.h_words), 2 * kOrbitWords * sizeof(int), hipHostMallocDefault);
   if (e == hipSuccess && !O.small) e = hipStreamCreateWithFlags(&O.small, hipStreamNonBlocking);
   for (hipEvent_t* ev : {&O.fork, &O.join[0], &O.join[1], &O.step[0], &O.step[1]})
     if (e == hipSuccess && !*ev) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);

@@ -155,6 +155,30 @@ for fail in (f.fake_fail_malloc, f.fake_fail_host):
 SHAPES = "[(3, 8, 2), (4, 6, 3), (5, 9, 2), (6, 4, 2)]"
 
 
+def test_batch_without_memory_for_its_plan_takes_the_full_forms(run):
+    """A failed device or pinned allocation of the batch's orbit plan: the full
+    forms run, and the plan is not tried again."""
+    run(f"""
+shapes = {SHAPES}
+b = batch(shapes)
+assert vib(b) != m.EDEVICE and "orbit_batch" in log()   # the plan's allocations: two pinned ones, one of the device
+lib.mdp_free_batch(b)
+for which, at in ((f.fake_fail_host, 0), (f.fake_fail_host, 1), (f.fake_fail_malloc, 0)):
+    f.fake_reset()
+    b = batch(shapes)
+    lib.batch_set_orbits(b, 0)
+    rc = vib(b)                      # the batch's own scratch
+    lib.batch_set_orbits(b, -1)
+    f.fake_reset()
+    which(at)
+    assert vib(b) == rc, lib.mdpvi_last_error()
+    assert "orbit" not in log() and "batch_lds" in log()
+    assert vib(b) == rc and "orbit" not in log()
+    lib.mdp_free_batch(b)
+assert f.fake_live() == 0
+""")
+
+
 def test_batch_plan_makes_room_for_later_scratch(run):
     """The evaluation's FP64 scratch, allocated after a value iteration on
     orbits, on a device with just the memory that the full forms need."""
