@@ -377,15 +377,28 @@ dim3 static_grid(long long B) { return dim3(static_cast<uint32_t>((B + kStaticWa
 // 59 and 63 against 32 and 107 us (40, 80).
 constexpr long long kLaneScenarios = 32768;
 
-#define MDPVI_STATIC_K(K_, CALL)  \
-  if ((K_) <= 4) CALL(4);         \
-  else if ((K_) <= 8) CALL(8);    \
-  else if ((K_) <= 12) CALL(12);  \
-  else if ((K_) <= 16) CALL(16);  \
-  else if ((K_) <= 24) CALL(24);  \
-  else if ((K_) <= 32) CALL(32);  \
-  else if ((K_) <= 48) CALL(48);  \
-  else CALL(64)
+// ... and for placing, whose lanes scan every VC for every task: from 25 VCs on
+// the wavefronts' time passes the other form's for 32,768 scenarios (1.06 of
+// it at 32 VCs and 200 tasks, 0.8 at 49,152); from 33 on it does so wherever the
+// last of the 1,280 wavefronts that LDS holds at a time are few (40 VCs, 200
+// tasks: 0.84 of it at 65,536, 1.26 at 98,304, 0.86 at 262,144), which the
+// line bounds to a third of them; beyond 48 it is never faster (64 VCs, 200
+// tasks: 1.9 at 32,768, 1.14 at 262,144).
+bool lane_first_fit(long long B, int K) {
+  const long long from = K <= 24 ? kLaneScenarios : K <= 32 ? 49152 : K <= 48 ? 163840 : (1ll << 62);
+  return B >= from;
+}
+
+// CALL(most VCs of the kernel); LAST for those beyond 32, or 48.
+#define MDPVI_STATIC_K(K_, CALL, LAST) \
+  if ((K_) <= 4) CALL(4);              \
+  else if ((K_) <= 8) CALL(8);         \
+  else if ((K_) <= 12) CALL(12);       \
+  else if ((K_) <= 16) CALL(16);       \
+  else if ((K_) <= 24) CALL(24);       \
+  else if ((K_) <= 32) CALL(32);       \
+  else if ((K_) <= 48) CALL(48);       \
+  else CALL(LAST)
 
 }  // namespace
 
@@ -393,11 +406,11 @@ hipError_t launch_static_first_fit(long long B, int K, long long T, const int32_
                                    double bvc, double btc, double gvc, int32_t* place, int32_t* used,
                                    long long* totals, double* reward, int32_t* status, hipStream_t s) {
   if (B == 0) return hipSuccess;
-  if (B >= kLaneScenarios) {
+  if (lane_first_fit(B, K)) {
 #define MDPVI_CALL(KB_)                                                                                             \
   hipLaunchKernelGGL((static_lane_first_fit_kernel<KB_>), dim3(static_cast<uint32_t>((B + kWave - 1) / kWave)),     \
                      dim3(kWave), 0, s, B, K, T, caps, need, bvc, btc, gvc, place, used, totals, reward, status)
-    MDPVI_STATIC_K(K, MDPVI_CALL);
+    MDPVI_STATIC_K(K, MDPVI_CALL, 48);
 #undef MDPVI_CALL
     return hipGetLastError();
   }
@@ -414,7 +427,7 @@ hipError_t launch_static_score(long long B, int K, long long T, const int32_t* c
 #define MDPVI_CALL(KB_)                                                                                         \
   hipLaunchKernelGGL((static_lane_score_kernel<KB_>), dim3(static_cast<uint32_t>((B + kWave - 1) / kWave)),     \
                      dim3(kWave), 0, s, B, K, T, caps, need, place, bvc, btc, gvc, used, totals, reward, status)
-    MDPVI_STATIC_K(K, MDPVI_CALL);
+    MDPVI_STATIC_K(K, MDPVI_CALL, 64);
 #undef MDPVI_CALL
     return hipGetLastError();
   }
