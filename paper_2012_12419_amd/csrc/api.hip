@@ -1306,7 +1306,7 @@ int mdp_autotune(mdpvi_mdp_t h, const float* V, int32_t trials, void* hip_stream
       auto sweep = [&]() -> hipError_t {
         if (is_tile_form(form)) {
           mdpvi::tile_set_walkers(&Se, form - MDPVI_FORM_TILE, cu_count());
-          return mdpvi::launch_eval_tile(M, h->d_model, Se, pol, ev[0], ev[1], Ae[0], Ae[1], h->ctl, h->res, 0, 1.0, s);
+          return mdpvi::launch_eval_tile(M, Se, pol, ev[0], ev[1], Ae[0], Ae[1], h->ctl, h->res, 0, 1.0, s);
         }
         return mdpvi::launch_eval_sweep(M, h->d_model, pol, ev[0], ev[1], h->ctl, h->res, 0, 1.0, s);
       };
@@ -1327,7 +1327,7 @@ int mdp_autotune(mdpvi_mdp_t h, const float* V, int32_t trials, void* hip_stream
         int orc = set_tile_order(h, &Se, eval_working_set(M), "eval", code);
         if (orc) return orc;
         auto sweep = [&]() -> hipError_t {
-          return mdpvi::launch_eval_tile(M, h->d_model, Se, pol, ev[0], ev[1], Ae[0], Ae[1], h->ctl, h->res, 0, 1.0, s);
+          return mdpvi::launch_eval_tile(M, Se, pol, ev[0], ev[1], Ae[0], Ae[1], h->ctl, h->res, 0, 1.0, s);
         };
         double us = 0.0;
         int trc = time_form(sweep, &us);
@@ -1685,7 +1685,7 @@ int eval_run(mdpvi_mdp* h, const uint8_t* pi, double* V, double tol, int64_t max
     return run_loop<double>(h, V, tol, max_iter, s, st, 17.0 * M.n_states,
                             static_cast<double>(M.n_states),
                             [&](long long j, double* in, double* out) {
-                              return mdpvi::launch_eval_tile(M, h->d_model, S, pi, in, out, A[j & 1], A[(j + 1) & 1],
+                              return mdpvi::launch_eval_tile(M, S, pi, in, out, A[j & 1], A[(j + 1) & 1],
                                                              h->ctl, h->res, j, tol, s);
                             },
                             false, S.grid);

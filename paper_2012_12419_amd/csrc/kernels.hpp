@@ -122,7 +122,7 @@ hipError_t launch_vi_row(const Model& M, const TileShape& S, const float* Vin, f
                          double* Aout, Ctl* ctl, double* res, long long j, double tol, hipStream_t s);
 bool eval_tile_shape(const Model& M, TileShape* S);
 hipError_t launch_eval_arrival_init(const Model& M, const double* V, double* A, hipStream_t s);
-hipError_t launch_eval_tile(const Model& M, const Model* dM, const TileShape& S, const uint8_t* pi, const double* Vin,
+hipError_t launch_eval_tile(const Model& M, const TileShape& S, const uint8_t* pi, const double* Vin,
                             double* Vout, const double* Ain, double* Aout, Ctl* ctl, double* res, long long j,
                             double tol, hipStream_t s);
 

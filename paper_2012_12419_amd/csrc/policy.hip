@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kBlock) void greedy_kernel(Model M, int kind, uint8
   if (o < static_cast<Idx>(M.n_occ)) greedy_occupancy<KMAX, JMAX>(M, kind, pi, o);
 }
 
-// The sweeps take the model from device memory: as a launch's argument its
+// These sweeps take the model from device memory: as a launch's argument its
 // 0.75 KB made the host's part of a launch longer than a small sweep (734
 // sweeps of 85,683 states, with the test left to workgroup 0: 4.54 -> 4.23 ms;
 // workgroups of one wavefront, which spread over more CUs, took 5.0).

@@ -17,14 +17,16 @@
 
 namespace mdpvi {
 
+// The model as an argument, whose loads the compiler may repeat after any
+// barrier: from device memory the sweeps took 44.0 instead of 41.6 us at K = 6,
+// C = 10, J = 3 and 236 instead of 228 at K = 7, J = 1.
 template <int K, int J, int T>
-__global__ __launch_bounds__(kTileBlock, kTileMinWaves) void eval_tile_kernel(const Model* __restrict__ dM, TileShape S, const uint8_t* __restrict__ pi,
+__global__ __launch_bounds__(kTileBlock, kTileMinWaves) void eval_tile_kernel(Model M, TileShape S, const uint8_t* __restrict__ pi,
                                                             const double* __restrict__ Vin,
                                                             double* __restrict__ Vout,
                                                             const double* __restrict__ Ain,
                                                             double* __restrict__ Aout, Ctl* ctl, double* res,
                                                             long long j, double tol) {
-  const Model& M = *dM;
   const SweepTest test = sweep_test_load(ctl, j);
   if (sweep_skipped(test, j)) return;
   extern __shared__ double tile_lds[];
@@ -68,13 +70,13 @@ hipError_t launch_eval_arrival_init(const Model& M, const double* V, double* A, 
   return hipGetLastError();
 }
 
-hipError_t launch_eval_tile(const Model& M, const Model* dM, const TileShape& S, const uint8_t* pi, const double* Vin,
+hipError_t launch_eval_tile(const Model& M, const TileShape& S, const uint8_t* pi, const double* Vin,
                             double* Vout, const double* Ain, double* Aout, Ctl* ctl, double* res, long long j,
                             double tol, hipStream_t s) {
   const size_t lds = static_cast<size_t>(S.occ) * 8 * M.J;
   return tile_dispatch(M.K, M.J, S.T, [&](auto kc, auto jc, auto tc) {
     constexpr int Kc = decltype(kc)::value, Jc = decltype(jc)::value, Tc = decltype(tc)::value;
-    hipLaunchKernelGGL((eval_tile_kernel<Kc, Jc, Tc>), dim3(S.grid), dim3(kTileBlock), lds, s, dM, S, pi, Vin, Vout,
+    hipLaunchKernelGGL((eval_tile_kernel<Kc, Jc, Tc>), dim3(S.grid), dim3(kTileBlock), lds, s, M, S, pi, Vin, Vout,
                        Ain, Aout, ctl, res, j, tol);
     return hipGetLastError();
   });
