@@ -255,41 +255,57 @@ __global__ __launch_bounds__(kBlock) void batch_line_sum_kernel(const BatchInst*
 
 
 // Per-instance control of the round form, as SweepTest of the single sweeps:
-// the instance's first workgroup (its leader) alone tests the residual of
-// round j-1, at its end; where that meets the test it records done_iter = j,
-// counts the instance off, and later rounds skip the instance.  Round j has
-// then written the buffer that the answer is not in.  The leader also clears
-// the residual words of round j+1.
+// from round kTestFirst on the instance's first workgroup (its leader) alone
+// tests the residual of round j-1, at its end; where that meets the test it
+// records done_iter = j, counts the instance off, and later rounds skip the
+// instance.  Round j has then written the buffer that the answer is not in.
+// The first rounds test at their start, in every workgroup.  The leader also
+// clears the residual words of round j+1.
 struct RoundTest {
-  long long done;
   bool mine;
   double v;
 };
 
-__device__ __forceinline__ RoundTest round_test_load(const BatchCtl* c, long long j, bool leader) {
-  RoundTest t{load_agent(&c->done_iter), leader && threadIdx.x < kWave, 0.0};
-  if (t.mine && j > 0 && threadIdx.x < kBatchLanes)
-    t.v = __longlong_as_double(static_cast<long long>(load_agent(&c->res[(j - 1) % kResSlots][threadIdx.x][0])));
-  return t;
-}
-
-__device__ __forceinline__ bool round_skipped(const RoundTest& t, long long j) { return t.done >= 0 && t.done < j; }
-
+// Whether the residual whose words the wavefront's first lanes hold meets the
+// test.
 template <ResKind RK>
-__device__ __forceinline__ void round_test_record(const RoundTest& t, BatchCtl* c, long long j, double tol,
-                                                  int* remaining) {
-  if (!t.mine) return;
-  double v = t.v;
+__device__ __forceinline__ bool round_met(double v, double tol) {
   if constexpr (RK == ResKind::kMax) {
     v = wave_max(v);
   } else {
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
   }
-  if (j > 0 && !(v >= tol) && threadIdx.x == 0) {
-    store_agent(&c->done_iter, j);
-    atomicSub(remaining, 1);
-  }
+  return !(v >= tol);
+}
+
+__device__ __forceinline__ void round_done(BatchCtl* c, long long j, int* remaining) {
+  store_agent(&c->done_iter, j);
+  atomicSub(remaining, 1);
+}
+
+// True (the same in every wavefront of the instance): skip the round.
+template <ResKind RK>
+__device__ __forceinline__ bool round_test_begin(BatchCtl* c, long long j, double tol, int* remaining, bool leader,
+                                                 RoundTest& t) {
+  const bool early = j < kTestFirst;
+  const long long done = load_agent(&c->done_iter);
+  t = RoundTest{leader && threadIdx.x < kWave, 0.0};
+  const int lane = threadIdx.x % kWave;
+  if ((early || t.mine) && j > 0 && lane < kBatchLanes)
+    t.v = __longlong_as_double(static_cast<long long>(load_agent(&c->res[(j - 1) % kResSlots][lane][0])));
+  if (!early) return done >= 0 && done < j;
+  if (done >= 0) return true;
+  if (j == 0 || !round_met<RK>(t.v, tol)) return false;
+  if (leader && threadIdx.x == 0) round_done(c, j, remaining);
+  return true;
+}
+
+template <ResKind RK>
+__device__ __forceinline__ void round_test_record(const RoundTest& t, BatchCtl* c, long long j, double tol,
+                                                  int* remaining) {
+  if (!t.mine) return;
+  if (j >= kTestFirst && round_met<RK>(t.v, tol) && threadIdx.x == 0) round_done(c, j, remaining);
   if (threadIdx.x < kBatchLanes) store_agent(&c->res[(j + 1) % kResSlots][threadIdx.x][0], 0ull);
 }
 
@@ -363,8 +379,8 @@ __device__ __forceinline__ void round_body(const BatchInst* __restrict__ insts, 
   const BatchInst& I = insts[tile.inst];
   const Model& M = I.M;
   BatchCtl* c = ctl + tile.inst;
-  const RoundTest test = round_test_load(c, j, tile.first == 0);
-  if (round_skipped(test, j)) return;
+  RoundTest test;
+  if (round_test_begin<Op::RK>(c, j, tol, remaining, tile.first == 0, test)) return;
   const T* Vin = ((j & 1) ? W : V) + I.offset;
   T* Vout = ((j & 1) ? V : W) + I.offset;
   const uint8_t* p = pi ? pi + I.offset : nullptr;
@@ -473,8 +489,8 @@ __global__ __launch_bounds__(kBlock) void batch_vi_tile_kernel(const BatchInst* 
   const BatchInst& I = insts[tile.inst];
   const Model& M = I.M;
   BatchCtl* c = ctl + tile.inst;
-  const RoundTest test = round_test_load(c, j, tile.first == 0);
-  if (round_skipped(test, j)) return;
+  RoundTest test;
+  if (round_test_begin<ResKind::kMax>(c, j, tol, remaining, tile.first == 0, test)) return;
   const float* Vin = ((j & 1) ? W : V) + I.offset;
   float* Vout = ((j & 1) ? V : W) + I.offset;
   const double* Ain = ((j & 1) ? A1 : A0) + I.aoff;
@@ -508,8 +524,8 @@ __device__ __forceinline__ void eval_tile_round(const BatchInst* __restrict__ in
   const BatchInst& I = insts[tile.inst];
   const Model& M = I.M;
   BatchCtl* c = ctl + tile.inst;
-  const RoundTest test = round_test_load(c, j, tile.first == 0);
-  if (round_skipped(test, j)) return;
+  RoundTest test;
+  if (round_test_begin<ResKind::kMax>(c, j, tol, remaining, tile.first == 0, test)) return;
   const uint32_t nocc = static_cast<uint32_t>(M.n_occ);
   const uint32_t ns = static_cast<uint32_t>(M.n_states);
   const BufView pv = make_view(pi + I.offset, ns);

@@ -35,8 +35,8 @@ __global__ __launch_bounds__(kBlock) void eval_sweep_kernel(const Model* __restr
                                                              double* __restrict__ Vout, Ctl* ctl,
                                                              double* res, long long j, double tol) {
   const Model& M = *dM;
-  const SweepTest test = sweep_test_load(ctl, j);
-  if (sweep_skipped(test, j)) return;
+  SweepTest test;
+  if (sweep_test_begin(ctl, j, test)) return;
   const uint32_t b = xcd_block(blockIdx.x, gridDim.x);
   double dmax = 0.0;
 #pragma unroll
@@ -68,8 +68,8 @@ __global__ __launch_bounds__(kBlock) void eval_exact_kernel(const Model* __restr
                                                              double* __restrict__ Vout, Ctl* ctl,
                                                              double* res, long long j, double tol) {
   const Model& M = *dM;
-  const SweepTest test = sweep_test_load(ctl, j);
-  if (sweep_skipped(test, j)) return;
+  SweepTest test;
+  if (sweep_test_begin(ctl, j, test)) return;
   const uint32_t b = xcd_block(blockIdx.x, gridDim.x);
   const uint32_t o = b * kBlock + threadIdx.x;
   double dmax = 0.0;

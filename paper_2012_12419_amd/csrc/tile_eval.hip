@@ -27,8 +27,8 @@ __global__ __launch_bounds__(kTileBlock, kTileMinWaves) void eval_tile_kernel(Mo
                                                             const double* __restrict__ Ain,
                                                             double* __restrict__ Aout, Ctl* ctl, double* res,
                                                             long long j, double tol) {
-  const SweepTest test = sweep_test_load(ctl, j);
-  if (sweep_skipped(test, j)) return;
+  SweepTest test;
+  if (sweep_test_begin(ctl, j, test)) return;
   extern __shared__ double tile_lds[];
   const uint32_t occ = S.occ;
   double* Vl = tile_lds;            // [J][occ]
