@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <cstddef>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -32,22 +33,29 @@ using mdpvi::Ctl;
 using mdpvi::Model;
 
 // Scratch of a handle's orbit form: one device block (control and residual
-// words, rank table, orbit table, two iterates and their arrival terms) and
-// the pinned mirror of the control words.
+// words, rank table, orbit table, two iterates and their arrival terms).
 struct OrbitPlan {
   int covered = -1;             // -1: not yet asked
   mdpvi::OrbitShape S{};
   mdpvi::OrbitParams P{};
   mdpvi::OrbitWork W{};
   unsigned char* dev = nullptr;
-  mdpvi::OrbitCtl* mirror = nullptr;
-  hipEvent_t ev0 = nullptr, ev1 = nullptr, step[2] = {};
+  hipEvent_t step[2] = {};
   hipGraphExec_t chunk[2] = {};   // kOrbitChunk sweeps of value iteration, of evaluation
+};
+
+// Pinned host words of a handle, in one allocation (each takes tens of
+// microseconds of a handle's first call).
+struct HandleWords {
+  Ctl ctl;                      // mirror of the control words
+  mdpvi::OrbitCtl orbit;        // mirror of the orbit form's
+  uint32_t binom[mdpvi::kOrbitBinom];   // the rank table on its way to the device
 };
 
 struct mdpvi_mdp {
   Model M;
   OrbitPlan orbit;
+  HandleWords* words = nullptr;
   int64_t feasible_pairs = 0;
   int device = -1;              // device of the scratch below (-1: none yet)
   void* vbuf = nullptr;         // second value buffer (ping-pong partner)
@@ -57,7 +65,6 @@ struct mdpvi_mdp {
                                 // (exact-shape direct and tile forms)
   Model* d_model = nullptr;     // M in device memory
   Ctl* ctl = nullptr;           // device control words
-  Ctl* ctl_host = nullptr;      // pinned mirror
   double* res = nullptr;        // residual words / per-workgroup partials
   double* res_host = nullptr;   // pinned, res_n doubles
   size_t res_n = 0;
@@ -140,23 +147,30 @@ bool pinned_malloc(T** p, size_t bytes) {
   return false;
 }
 
-// Device scratch of a handle: control words, pinned mirror, events and a
-// ping-pong partner of at least `bytes`.  Bound to the device current at
-// first use.  Each piece is there or NULL, so that a call after a failed one
-// goes on from what is missing.
-int ensure_scratch(mdpvi_mdp* h, size_t bytes) {
+// What every solve of a handle needs: the device (that current at first use),
+// pinned words and timing events.
+int ensure_words(mdpvi_mdp* h) {
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
   if (h->device >= 0 && h->device != dev)
     return fail(MDPVI_EINVAL, "handle scratch lives on device %d, current device is %d", h->device,
                 dev);
-  if (!h->ctl && !handle_malloc(h, &h->ctl, sizeof(Ctl)))
-    return fail(MDPVI_ENOMEM, "hipMalloc of %zu control bytes failed", sizeof(Ctl));
-  h->device = dev;
-  if (!h->ctl_host && !pinned_malloc(&h->ctl_host, sizeof(Ctl)))
+  if (!h->words && !pinned_malloc(&h->words, sizeof(HandleWords)))
     return fail(MDPVI_ENOMEM, "hipHostMalloc of the control mirror failed");
+  h->device = dev;
   for (hipEvent_t* e : {&h->ev0, &h->ev1})
     if (!*e) HIP_TRY(hipEventCreate(e));
+  return MDPVI_OK;
+}
+
+// Device scratch of the full sweeps: control and residual words, the model and
+// a ping-pong partner of at least `bytes`.  Each piece is there or NULL, so
+// that a call after a failed one goes on from what is missing.
+int ensure_scratch(mdpvi_mdp* h, size_t bytes) {
+  const int rc = ensure_words(h);
+  if (rc) return rc;
+  if (!h->ctl && !handle_malloc(h, &h->ctl, sizeof(Ctl)))
+    return fail(MDPVI_ENOMEM, "hipMalloc of %zu control bytes failed", sizeof(Ctl));
   // the largest grid of any sweep form: the direct form, or the slab form
   // with one low digit (n_occ / (C+1) workgroups)
   const uint64_t g1 = static_cast<uint64_t>(h->M.n_occ) / static_cast<uint64_t>(h->M.R);
@@ -437,13 +451,35 @@ int timing_events(mdpvi_mdp* h) {
   return MDPVI_OK;
 }
 
+// Value iteration's way from the full sweeps to the orbit form (vi_solve):
+// after kSwitchSweeps sweeps, the first two chunks, that have not met the test.
+constexpr int kSwitchSweeps = 24;
+constexpr int kSwitched = 4;   // run_loop: the iterate is in buf0, the solve goes on on its orbits
+struct OrbitSwitch {
+  bool on = false;
+  double sweep_ms = 0.0;       // out: of the sweeps done
+};
+int orbit_switch_start(mdpvi_mdp* h, const void* V, double tol, hipStream_t s, bool* started);
+int orbit_verdict(const mdpvi_mdp* h);
+
+// Whether sweep j met the stopping test, from the mirror of the control words.
+bool sweep_met(const mdpvi_mdp* h, long long j) {
+  const int r = static_cast<int>(j % mdpvi::kResSlots);
+  bool up = false, bad = false;
+  for (int x = 0; x < mdpvi::kNumXcd; ++x) {
+    up = up || h->words->ctl.go[r][x][0] != 0u;
+    bad = bad || h->words->ctl.nan[r][x][0] != 0u;
+  }
+  return bad || !up;
+}
+
 // Enqueue sweeps j = 0, 1, ... in chunks until the device reports the test
 // met or max_iter sweeps were issued; leaves the final iterate in buf0.
 // `sweep(j, in, out)` enqueues sweep j.
 template <typename T, typename Sweep>
 int run_loop(mdpvi_mdp* h, T* buf0, double tol, int64_t max_iter, hipStream_t s,
              mdpvi_stats* st, double bytes_per_sweep, double backups_per_sweep, Sweep sweep,
-             bool sum_residual, uint32_t grid) {
+             bool sum_residual, uint32_t grid, OrbitSwitch* sw = nullptr) {
   T* buf[2] = {buf0, static_cast<T*>(h->vbuf)};
   HIP_TRY(mdpvi::launch_ctl_init(h->ctl, h->res, s));
   HIP_TRY(hipEventRecord(h->ev0, s));
@@ -463,9 +499,14 @@ int run_loop(mdpvi_mdp* h, T* buf0, double tol, int64_t max_iter, hipStream_t s,
       HIP_TRY(sweep(static_cast<long long>(j), buf[j & 1], buf[(j + 1) & 1]));
       if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[2 * i + 1], s));
     }
-    HIP_TRY(hipMemcpyAsync(h->ctl_host, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+    bool started = false;
+    if (sw && sw->on && issued + n == kSwitchSweeps) {   // an even number: the iterate is in buf0
+      const int orc = orbit_switch_start(h, buf0, tol, s, &started);
+      if (orc) return orc;
+    }
+    HIP_TRY(hipMemcpyAsync(&h->words->ctl, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    done = h->ctl_host->done_iter;
+    done = h->words->ctl.done_iter;
     if (h->timing) {
       for (int64_t i = 0; i < n; ++i) {
         if (done >= 0 && issued + i >= done) break;   // sweeps from `done` on did no work
@@ -476,6 +517,10 @@ int run_loop(mdpvi_mdp* h, T* buf0, double tol, int64_t max_iter, hipStream_t s,
     }
     issued += n;
     if (done >= 0) break;
+    if (started && orbit_verdict(h) == 0 && !sweep_met(h, issued - 1)) {
+      sw->sweep_ms = sweep_ms;
+      return kSwitched;
+    }
     if (chunk < kMaxChunk) chunk *= 2;
   }
   int64_t final_iter;
@@ -603,10 +648,9 @@ bool orbit_applies(mdpvi_mdp* h, int64_t max_iter) {
 
 int orbit_ensure(mdpvi_mdp* h, hipStream_t s) {
   OrbitPlan& O = h->orbit;
-  int dev = 0;
-  HIP_TRY(hipGetDevice(&dev));
-  if (h->device >= 0 && h->device != dev)
-    return fail(MDPVI_EINVAL, "handle scratch lives on device %d, current device is %d", h->device, dev);
+  int rc = ensure_words(h);
+  if (rc) return rc;
+  if (h->timing && (rc = timing_events(h))) return rc;
   if (O.dev) return MDPVI_OK;
   const size_t n = O.S.n, rows = static_cast<size_t>(2 + O.S.J) * O.S.K;
   size_t at = 0;
@@ -617,24 +661,20 @@ int orbit_ensure(mdpvi_mdp* h, hipStream_t s) {
   };
   const std::vector<uint32_t> binom = orbit_binom(O.S);
   const size_t o_ctl = take(sizeof(mdpvi::OrbitCtl));
-  const size_t o_res = take(static_cast<size_t>(mdpvi::kResSlots) * mdpvi::kOrbitGrid * sizeof(double));
   const size_t o_bin = take(binom.size() * sizeof(uint32_t));
+  const size_t o_found = take(mdpvi::kOrbitCheckGrid * sizeof(uint32_t));
+  const size_t o_res = take(static_cast<size_t>(mdpvi::kResSlots) * mdpvi::kOrbitGrid * sizeof(double));
   const size_t o_dig = take(n * sizeof(uint64_t));
   const size_t o_rep = take(n * sizeof(uint32_t));
   const size_t o_tab = take(rows * n * (O.S.wide ? 4 : 2));
   const size_t o_act = take(n * O.S.L * sizeof(uint32_t));
-  const size_t o_load = take(n * O.S.L * sizeof(int32_t));
   size_t o_v[2], o_a[2];
   for (size_t& o : o_v) o = take(n * O.S.L * sizeof(double));
   for (size_t& o : o_a) o = take((n + 1) * sizeof(double));
-  if (!O.mirror && !pinned_malloc(&O.mirror, sizeof(mdpvi::OrbitCtl)))
-    return fail(MDPVI_ENOMEM, "hipHostMalloc of the control mirror failed");
-  for (hipEvent_t* e : {&O.ev0, &O.ev1})
-    if (!*e) HIP_TRY(hipEventCreate(e));
-  for (hipEvent_t& e : O.step)
-    if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   unsigned char* d = nullptr;
   if (!handle_malloc(h, &d, at)) return fail(MDPVI_ENOMEM, "hipMalloc of %zu orbit bytes failed", at);
+  O.W.ctl = reinterpret_cast<mdpvi::OrbitCtl*>(d + o_ctl);
+  O.W.found = reinterpret_cast<uint32_t*>(d + o_found);
   O.S.binom = reinterpret_cast<uint32_t*>(d + o_bin);
   O.S.dig = reinterpret_cast<uint64_t*>(d + o_dig);
   O.S.rep = reinterpret_cast<uint32_t*>(d + o_rep);
@@ -645,102 +685,51 @@ int orbit_ensure(mdpvi_mdp* h, hipStream_t s) {
     O.W.A[b] = reinterpret_cast<double*>(d + o_a[b]);
   }
   O.W.act = reinterpret_cast<uint32_t*>(d + o_act);
-  O.W.load = reinterpret_cast<int32_t*>(d + o_load);
   O.W.res = reinterpret_cast<double*>(d + o_res);
-  O.W.ctl = reinterpret_cast<mdpvi::OrbitCtl*>(d + o_ctl);
-  hipError_t e = hipMemcpy(d + o_bin, binom.data(), binom.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
+  std::copy(binom.begin(), binom.end(), h->words->binom);
+  hipError_t e = hipMemcpyAsync(d + o_bin, h->words->binom, binom.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s);
   if (e == hipSuccess)
     e = mdpvi::launch_orbit_table(O.S, O.P, reinterpret_cast<uint64_t*>(d + o_dig),
                                   reinterpret_cast<uint32_t*>(d + o_rep), d + o_tab, s);
   if (e != hipSuccess) {
+    (void)hipStreamSynchronize(s);
     (void)hipFree(d);
     return fail_hip(e, "orbit table");
   }
   O.dev = d;
-  h->device = dev;
   return MDPVI_OK;
 }
 
-// Value iteration (pi NULL) or evaluation of pi on the orbits; kOrbitRefused
-// or kOrbitInfeasible (V untouched) when V or pi is not invariant under host
-// permutations, or pi has an infeasible action.
+// Starts a solve on the orbits at V, after it0 sweeps, with the check that V
+// (and pi) is invariant.
 template <class Op>
-int orbit_solve(mdpvi_mdp* h, const uint8_t* pi, typename Op::T* V, double tol, int64_t max_iter, hipStream_t s,
-                mdpvi_stats* st) {
-  int rc = orbit_ensure(h, s);
-  if (rc == MDPVI_ENOMEM) return kOrbitNoMemory;   // the full sweeps need none of it
-  if (rc) return rc;
+int orbit_start(mdpvi_mdp* h, const uint8_t* pi, const typename Op::T* V, double tol, int64_t it0, hipStream_t s) {
   OrbitPlan& O = h->orbit;
-  const Model& M = h->M;
-  volatile mdpvi::OrbitCtl* w = O.mirror;
-  if (h->timing && (rc = timing_events(h))) return rc;
+  volatile mdpvi::OrbitCtl* w = &h->words->orbit;
   w->done = -1;
-  w->flag = 0;
-  w->bad = 0;
-  HIP_TRY(hipEventRecord(O.ev0, s));
-  HIP_TRY(mdpvi::launch_orbit_begin<Op>(O.S, O.P, O.W, V, pi, tol, O.mirror, s));
-  int64_t issued = 0;
-  double sweep_ms = 0.0;
-  if (orbit_in_lds<Op>(O.S)) {
-    while (w->done < 0 && issued < max_iter) {
-      const int64_t n = std::min(kOrbitLdsSweeps, max_iter - issued);
-      if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[0], s));
-      HIP_TRY(mdpvi::launch_orbit_lds<Op>(O.S, O.P, O.W, O.mirror, issued, n, tol, s));
-      if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[1], s));
-      issued += n;
-      HIP_TRY(mdpvi::launch_orbit_expand<Op>(O.S, O.W, V, issued, s));
-      HIP_TRY(hipEventRecord(O.ev1, s));
-      HIP_TRY(hipEventSynchronize(O.ev1));
-      if (w->flag) return w->bad ? kOrbitInfeasible : kOrbitRefused;
-      if (h->timing) {
-        float ms = 0.f;
-        HIP_TRY(hipEventElapsedTime(&ms, h->sweep_ev[0], h->sweep_ev[1]));
-        sweep_ms += ms;
-      }
-    }
-  } else {
-    // chunks of sweeps, one in flight while the host waits for the other; the
-    // first only after the check, so that a refused call sweeps nothing
-    hipGraphExec_t& chunk = O.chunk[Op::kEval ? 1 : 0];
-    HIP_TRY(hipEventRecord(O.step[0], s));
-    HIP_TRY(hipEventSynchronize(O.step[0]));
-    if (w->flag) return w->bad ? kOrbitInfeasible : kOrbitRefused;
-    if (!chunk && !h->timing) HIP_TRY(mdpvi::build_orbit_chunk<Op>(O.S, O.P, O.W, O.mirror, &chunk));
-    for (int k = 0; w->done < 0 && issued < max_iter; ++k) {
-      const int n = static_cast<int>(std::min<int64_t>(mdpvi::kOrbitChunk, max_iter - issued));
-      if (n == mdpvi::kOrbitChunk && !h->timing) {
-        HIP_TRY(hipGraphLaunch(chunk, s));
-      } else {
-        for (int i = 0; i < n; ++i) {
-          if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[2 * i], s));
-          HIP_TRY(mdpvi::launch_orbit_sweep<Op>(O.S, O.P, O.W, O.mirror, i, s));
-          if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[2 * i + 1], s));
-        }
-        HIP_TRY(mdpvi::launch_orbit_next(O.W.ctl, n, s));
-      }
-      HIP_TRY(hipEventRecord(O.step[k & 1], s));
-      issued += n;
-      if (h->timing) {
-        HIP_TRY(hipEventSynchronize(O.step[k & 1]));
-        for (int i = 0; i < n; ++i) {
-          if (w->done >= 0 && issued - n + i >= w->done) break;   // sweeps that did no work
-          float ms = 0.f;
-          HIP_TRY(hipEventElapsedTime(&ms, h->sweep_ev[2 * i], h->sweep_ev[2 * i + 1]));
-          sweep_ms += ms;
-        }
-      } else if (k > 0) {
-        HIP_TRY(hipEventSynchronize(O.step[(k - 1) & 1]));
-      }
-    }
-    HIP_TRY(mdpvi::launch_orbit_last_residual(O.S, O.W, issued, O.mirror, s));
-    HIP_TRY(mdpvi::launch_orbit_expand<Op>(O.S, O.W, V, issued, s));
-    HIP_TRY(hipEventRecord(O.ev1, s));
-    HIP_TRY(hipEventSynchronize(O.ev1));
-  }
+  HIP_TRY(mdpvi::launch_orbit_check<Op>(O.S, O.P, O.W, V, pi, tol, it0, s));
+  return MDPVI_OK;
+}
+
+// The check's verdict, once the stream is past launch_orbit_verdict or a
+// LDS-resident solve: 0, kOrbitRefused or kOrbitInfeasible.
+int orbit_verdict(const mdpvi_mdp* h) {
+  const volatile mdpvi::OrbitCtl* w = &h->words->orbit;
+  return w->done == mdpvi::kOrbitDoneInfeasible ? kOrbitInfeasible
+         : w->done == mdpvi::kOrbitDoneRefused  ? kOrbitRefused
+                                                : 0;
+}
+
+// The stats and the code of a solve whose iterate V holds after `issued`
+// sweeps or the ones at which it stopped.
+template <class Op>
+int orbit_result(mdpvi_mdp* h, double tol, int64_t issued, double sweep_ms, mdpvi_stats* st) {
+  const Model& M = h->M;
+  const volatile mdpvi::OrbitCtl* w = &h->words->orbit;
   const int64_t final_iter = w->done >= 0 ? w->done : issued;
   const double res = w->residual;
   float ms = 0.f;
-  HIP_TRY(hipEventElapsedTime(&ms, O.ev0, O.ev1));
+  HIP_TRY(hipEventElapsedTime(&ms, h->ev0, h->ev1));
   if (st) {
     const double states = static_cast<double>(M.n_states);
     st->iterations = final_iter;
@@ -757,6 +746,120 @@ int orbit_solve(mdpvi_mdp* h, const uint8_t* pi, typename Op::T* V, double tol, 
     return fail(MDPVI_ENOCONV, "residual %.3e >= tol %.3e after %lld sweeps (max_iter)", res, tol,
                 (long long)final_iter);
   return MDPVI_OK;
+}
+
+// Value iteration of fewer states than this begins with full sweeps and goes to
+// the orbits only when kSwitchSweeps of them have not met the test: a call that
+// ends earlier (a warm start) then costs what it does without the form (100 us
+// at K = 4, C = 12, J = 3), where the check and its round trip add 15 to 20 us
+// and the tables 20 us of a handle's first call; a long one takes 24 sweeps of
+// 5 to 10 us in full (its 351 sweeps 1.52 ms, 1.37 without them, 2.48 all in
+// full).  Beyond, a full sweep takes as long as the check: 12 us at a million
+// states, 30 at 5.3 million.
+constexpr int64_t kSwitchStates = int64_t{1} << 20;
+
+int orbit_switch_start(mdpvi_mdp* h, const void* V, double tol, hipStream_t s, bool* started) {
+  int rc = orbit_ensure(h, s);
+  if (rc == MDPVI_ENOMEM) return MDPVI_OK;   // the full sweeps go on
+  if (rc) return rc;
+  *started = true;
+  if ((rc = orbit_start<mdpvi::OrbitVi>(h, nullptr, static_cast<const float*>(V), tol, kSwitchSweeps, s))) return rc;
+  HIP_TRY(mdpvi::launch_orbit_verdict(h->orbit.S, h->orbit.W, &h->words->orbit, s));
+  return MDPVI_OK;
+}
+
+// Launched sweeps of a started solve that was not refused, it0 having been
+// done (in sweep_ms): chunks of sweeps, one in flight while the host waits for
+// the other.  The first is waited for by itself, and is short where nothing
+// was swept before it: a warm start ends there (K = 4, C = 12, J = 3: 162 us
+// with two full chunks always in flight, against 100 us of full sweeps).
+template <class Op>
+int orbit_sweeps(mdpvi_mdp* h, typename Op::T* V, double tol, int64_t max_iter, int64_t it0, double sweep_ms,
+                 hipStream_t s, mdpvi_stats* st) {
+  OrbitPlan& O = h->orbit;
+  mdpvi::OrbitCtl* mirror = &h->words->orbit;
+  const volatile mdpvi::OrbitCtl* w = mirror;
+  for (hipEvent_t& e : O.step)
+    if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  hipGraphExec_t& chunk = O.chunk[Op::kEval ? 1 : 0];
+  int64_t issued = it0;
+  for (int k = 0; w->done < 0 && issued < max_iter; ++k) {
+    // the recording of a chunk, 0.1 ms of a handle's first long solve, waits for
+    // the solve to be one
+    const int most = issued == 0 ? mdpvi::kOrbitFirst
+                     : k == 1 && !chunk ? 2 * mdpvi::kOrbitFirst
+                                        : mdpvi::kOrbitChunk;
+    const int n = static_cast<int>(std::min<int64_t>(most, max_iter - issued));
+    if (n == mdpvi::kOrbitChunk && !h->timing) {
+      if (!chunk) HIP_TRY(mdpvi::build_orbit_chunk<Op>(O.S, O.P, O.W, mirror, &chunk));
+      HIP_TRY(hipGraphLaunch(chunk, s));
+    } else {
+      for (int i = 0; i < n; ++i) {
+        if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[2 * i], s));
+        HIP_TRY(mdpvi::launch_orbit_sweep<Op>(O.S, O.P, O.W, mirror, i, s));
+        if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[2 * i + 1], s));
+      }
+      HIP_TRY(mdpvi::launch_orbit_next(O.W.ctl, n, s));
+    }
+    HIP_TRY(hipEventRecord(O.step[k & 1], s));
+    issued += n;
+    if (h->timing) {
+      HIP_TRY(hipEventSynchronize(O.step[k & 1]));
+      for (int i = 0; i < n; ++i) {
+        if (w->done >= 0 && issued - n + i >= w->done) break;   // sweeps that did no work
+        float ms = 0.f;
+        HIP_TRY(hipEventElapsedTime(&ms, h->sweep_ev[2 * i], h->sweep_ev[2 * i + 1]));
+        sweep_ms += ms;
+      }
+    } else {
+      HIP_TRY(hipEventSynchronize(O.step[k == 0 ? 0 : (k - 1) & 1]));
+    }
+  }
+  if (w->done < 0) HIP_TRY(mdpvi::launch_orbit_last_residual(O.S, O.W, issued, mirror, s));
+  HIP_TRY(mdpvi::launch_orbit_expand<Op>(O.S, O.W, V, issued, s));
+  HIP_TRY(hipEventRecord(h->ev1, s));
+  HIP_TRY(hipEventSynchronize(h->ev1));
+  return orbit_result<Op>(h, tol, issued, sweep_ms, st);
+}
+
+// Value iteration (pi NULL) or evaluation of pi on the orbits; kOrbitRefused
+// or kOrbitInfeasible (V untouched) when V or pi is not invariant under host
+// permutations, or pi has an infeasible action.
+template <class Op>
+int orbit_solve(mdpvi_mdp* h, const uint8_t* pi, typename Op::T* V, double tol, int64_t max_iter, hipStream_t s,
+                mdpvi_stats* st) {
+  int rc = orbit_ensure(h, s);
+  if (rc == MDPVI_ENOMEM) return kOrbitNoMemory;   // the full sweeps need none of it
+  if (rc) return rc;
+  OrbitPlan& O = h->orbit;
+  const volatile mdpvi::OrbitCtl* w = &h->words->orbit;
+  HIP_TRY(hipEventRecord(h->ev0, s));
+  if ((rc = orbit_start<Op>(h, pi, V, tol, 0, s))) return rc;
+  if (!orbit_in_lds<Op>(O.S)) {   // a refused call sweeps nothing
+    HIP_TRY(mdpvi::launch_orbit_verdict(O.S, O.W, &h->words->orbit, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    if ((rc = orbit_verdict(h))) return rc;
+    return orbit_sweeps<Op>(h, V, tol, max_iter, 0, 0.0, s, st);
+  }
+  int64_t issued = 0;
+  double sweep_ms = 0.0;
+  while (w->done < 0 && issued < max_iter) {
+    const int64_t n = std::min(kOrbitLdsSweeps, max_iter - issued);
+    if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[0], s));
+    HIP_TRY(mdpvi::launch_orbit_lds<Op>(O.S, O.P, O.W, &h->words->orbit, issued, n, tol, s));
+    if (h->timing) HIP_TRY(hipEventRecord(h->sweep_ev[1], s));
+    issued += n;
+    HIP_TRY(mdpvi::launch_orbit_expand<Op>(O.S, O.W, V, issued, s));
+    HIP_TRY(hipEventRecord(h->ev1, s));
+    HIP_TRY(hipEventSynchronize(h->ev1));
+    if ((rc = orbit_verdict(h))) return rc;
+    if (h->timing) {
+      float ms = 0.f;
+      HIP_TRY(hipEventElapsedTime(&ms, h->sweep_ev[0], h->sweep_ev[1]));
+      sweep_ms += ms;
+    }
+  }
+  return orbit_result<Op>(h, tol, issued, sweep_ms, st);
 }
 
 // ---------------------------------------------------------------- tuning cache
@@ -976,12 +1079,11 @@ struct OrbitBatch {
   unsigned char* dev = nullptr;
   mdpvi::OrbitInst* d_inst = nullptr;
   const int32_t* d_slot = nullptr;
-  const mdpvi::Tile* d_otiles = nullptr;
-  int n_otiles = 0;
   mdpvi::OrbitCtl* d_ctl = nullptr;   // [entries]
+  uint32_t* d_found = nullptr;        // [tiles]
   int* d_words = nullptr;             // [0] round instances running, then per rounds list: all tiles, [2] active
   mdpvi::OrbitCtl* h_ctl = nullptr;   // pinned
-  int* h_words = nullptr;             // pinned, two copies
+  int* h_words = nullptr;             // behind h_ctl, two copies
   hipStream_t small = nullptr;
   hipEvent_t fork = nullptr, join[2] = {}, step[2] = {};
 };
@@ -1092,7 +1194,7 @@ void mdp_free(mdpvi_mdp_t h) {
   if (h->pbuf) (void)hipFree(h->pbuf);
   if (h->d_model) (void)hipFree(h->d_model);
   if (h->ctl) (void)hipFree(h->ctl);
-  if (h->ctl_host) (void)hipHostFree(h->ctl_host);
+  if (h->words) (void)hipHostFree(h->words);
   if (h->res) (void)hipFree(h->res);
   if (h->res_host) (void)hipHostFree(h->res_host);
   if (h->ev0) (void)hipEventDestroy(h->ev0);
@@ -1103,8 +1205,7 @@ void mdp_free(mdpvi_mdp_t h) {
       if (o) (void)hipFree(o);
   if (h->out_host) (void)hipHostFree(h->out_host);
   orbit_release(h);
-  if (h->orbit.mirror) (void)hipHostFree(h->orbit.mirror);
-  for (hipEvent_t e : {h->orbit.ev0, h->orbit.ev1, h->orbit.step[0], h->orbit.step[1]})
+  for (hipEvent_t e : h->orbit.step)
     if (e) (void)hipEventDestroy(e);
   if (h->sweep_ev) {
     for (int64_t i = 0; i < 2 * kMaxChunk; ++i)
@@ -1387,7 +1488,10 @@ int vi_solve(mdpvi_mdp_t h, float* V, double tol, int64_t max_iter, void* hip_st
   if (!(tol > 0)) return fail(MDPVI_EINVAL, "tol=%g must be > 0", tol);
   if (max_iter < 1) return fail(MDPVI_EINVAL, "max_iter=%lld must be >= 1", (long long)max_iter);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  if (orbit_applies<mdpvi::OrbitVi>(h, max_iter)) {
+  const bool orbits = orbit_applies<mdpvi::OrbitVi>(h, max_iter);
+  OrbitSwitch sw;
+  sw.on = orbits && !orbit_in_lds<mdpvi::OrbitVi>(h->orbit.S) && h->M.n_states < kSwitchStates;
+  if (orbits && !sw.on) {
     const int orc = orbit_solve<mdpvi::OrbitVi>(h, nullptr, V, tol, max_iter, s, st);
     if (orc != kOrbitRefused && orc != kOrbitNoMemory) return orc;
   }
@@ -1406,29 +1510,34 @@ int vi_solve(mdpvi_mdp_t h, float* V, double tol, int64_t max_iter, void* hip_st
     int orc = set_tile_order(h, &S, vi_working_set(M), "vi");
     if (orc) return orc;
   }
+  auto rest = [&](int lrc) {
+    return lrc == kSwitched
+               ? orbit_sweeps<mdpvi::OrbitVi>(h, V, tol, max_iter, kSwitchSweeps, sw.sweep_ms, s, st)
+               : lrc;
+  };
   if (is_row_form(form))
-    return run_loop<float>(h, V, tol, max_iter, s, st, 8.0 * M.n_states,
+    return rest(run_loop<float>(h, V, tol, max_iter, s, st, 8.0 * M.n_states,
                            static_cast<double>(h->feasible_pairs),
                            [&](long long j, float* in, float* out) {
                              return mdpvi::launch_vi_row(M, S, in, out, A[j & 1], A[(j + 1) & 1], h->ctl, h->res,
                                                          j, tol, s);
                            },
-                           false, S.grid);
+                           false, S.grid, &sw));
   if (is_tile_form(form))
-    return run_loop<float>(h, V, tol, max_iter, s, st, 8.0 * M.n_states,
+    return rest(run_loop<float>(h, V, tol, max_iter, s, st, 8.0 * M.n_states,
                            static_cast<double>(h->feasible_pairs),
                            [&](long long j, float* in, float* out) {
                              return mdpvi::launch_vi_tile(M, S, in, out, A[j & 1], A[(j + 1) & 1], h->ctl,
                                                           h->res, j, tol, s);
                            },
-                           false, S.grid);
-  return run_loop<float>(h, V, tol, max_iter, s, st, 8.0 * M.n_states,
+                           false, S.grid, &sw));
+  return rest(run_loop<float>(h, V, tol, max_iter, s, st, 8.0 * M.n_states,
                          static_cast<double>(h->feasible_pairs),
                          [&](long long j, float* in, float* out) {
                            return mdpvi::launch_vi_sweep(M, in, out, h->ctl, h->res, j, tol, s, form,
                                                          A[0] ? A : nullptr);
                          },
-                         false, mdpvi::vi_sweep_grid(M, form));
+                         false, mdpvi::vi_sweep_grid(M, form), &sw));
 }
 
 }  // extern "C"
@@ -1655,9 +1764,9 @@ int policy_eval(mdpvi_mdp_t h, const uint8_t* pi, double* V, double tol, int64_t
   if (!checked) {
     HIP_TRY(mdpvi::launch_ctl_init(h->ctl, h->res, s));
     HIP_TRY(mdpvi::launch_policy_check(M, pi, h->ctl, s));
-    HIP_TRY(hipMemcpyAsync(h->ctl_host, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(&h->words->ctl, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    if (h->ctl_host->flag) return fail(MDPVI_EINVAL, "%s", kInfeasiblePolicy);
+    if (h->words->ctl.flag) return fail(MDPVI_EINVAL, "%s", kInfeasiblePolicy);
   }
   return eval_run(h, pi, V, tol, max_iter, s, st);
 }
@@ -1721,9 +1830,9 @@ int policy_iteration(mdpvi_mdp_t h, uint8_t* pi, double* V, double eval_tol, int
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   HIP_TRY(mdpvi::launch_ctl_init(h->ctl, h->res, s));
   HIP_TRY(mdpvi::launch_policy_check(M, pi, h->ctl, s));
-  HIP_TRY(hipMemcpyAsync(h->ctl_host, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(&h->words->ctl, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  if (h->ctl_host->flag)
+  if (h->words->ctl.flag)
     return fail(MDPVI_EINVAL, "%s", kInfeasiblePolicy);
   const auto t0 = std::chrono::steady_clock::now();
   mdpvi_stats tot{};
@@ -1748,9 +1857,9 @@ int policy_iteration(mdpvi_mdp_t h, uint8_t* pi, double* V, double eval_tol, int
     HIP_TRY(mdpvi::launch_improve(M, V, pi, h->pbuf, improve_tol, s));
     HIP_TRY(mdpvi::launch_ctl_init(h->ctl, nullptr, s));
     HIP_TRY(mdpvi::launch_policy_diff(N, pi, h->pbuf, h->ctl, s));
-    HIP_TRY(hipMemcpyAsync(h->ctl_host, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(&h->words->ctl, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    stable = h->ctl_host->flag == 0;
+    stable = h->words->ctl.flag == 0;
     if (!stable) HIP_TRY(hipMemcpyAsync(pi, h->pbuf, N, hipMemcpyDeviceToDevice, s));
   }
   HIP_TRY(hipStreamSynchronize(s));
@@ -1779,9 +1888,9 @@ int vi_adjoint(mdpvi_mdp_t h, const uint8_t* pi, const double* V_pi, float* w, d
   const Model& M = h->M;
   HIP_TRY(mdpvi::launch_ctl_init(h->ctl, h->res, s));
   HIP_TRY(mdpvi::launch_policy_check(M, pi, h->ctl, s));
-  HIP_TRY(hipMemcpyAsync(h->ctl_host, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(&h->words->ctl, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  if (h->ctl_host->flag)
+  if (h->words->ctl.flag)
     return fail(MDPVI_EINVAL, "%s", kInfeasiblePolicy);
   const int aform = adjoint_form(h);
   rc = run_loop<float>(
@@ -2206,7 +2315,6 @@ void mdp_free_batch(mdpvi_batch_t b) {
   (void)hipFree(b->orbit.dev);
   (void)hipFree(b->d_sub);
   if (b->orbit.h_ctl) (void)hipHostFree(b->orbit.h_ctl);
-  if (b->orbit.h_words) (void)hipHostFree(b->orbit.h_words);
   if (b->orbit.small) (void)hipStreamDestroy(b->orbit.small);
   for (hipEvent_t e : {b->orbit.fork, b->orbit.join[0], b->orbit.join[1], b->orbit.step[0], b->orbit.step[1]})
     if (e) (void)hipEventDestroy(e);
@@ -2307,7 +2415,7 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
   if (O.built) return MDPVI_OK;
   std::vector<mdpvi::OrbitInst> inst;
   std::vector<int32_t> slot(b->n, -1);
-  std::vector<mdpvi::Tile> otiles, ttiles;
+  std::vector<mdpvi::Tile> ttiles;
   O.inst.clear();
   for (auto& op : O.op) op = OrbitBatch::Operation();
   for (int i = 0; i < b->n; ++i) {
@@ -2322,7 +2430,6 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
     I.inst = i;
     slot[i] = static_cast<int32_t>(inst.size());
     O.inst.push_back(i);
-    for (uint32_t r = 0; r < I.S.n; r += 256) otiles.push_back({slot[i], r});
     inst.push_back(I);
   }
   const int n = static_cast<int>(inst.size());
@@ -2365,7 +2472,6 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
       if (!R.entries.empty()) L.rounds.push_back(R);
     }
   }
-  O.n_otiles = static_cast<int>(otiles.size());
   if (n == 0) {
     O.built = true;
     return MDPVI_OK;
@@ -2385,7 +2491,6 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
   };
   const size_t o_inst = take(n * sizeof(mdpvi::OrbitInst));   // filled below
   const size_t o_slot = put(slot.data(), slot.size() * sizeof(int32_t));
-  const size_t o_ot = put(otiles.data(), otiles.size() * sizeof(mdpvi::Tile));
   std::vector<size_t> o_list, o_rlist, o_rt;
   int words[kOrbitWords] = {};
   for (auto& L : O.op) {
@@ -2414,6 +2519,8 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
   }
   const size_t o_tt = put(ttiles.data(), ttiles.size() * sizeof(mdpvi::Tile));
   const size_t uploaded = at;
+  const size_t o_ctl = take(n * sizeof(mdpvi::OrbitCtl));
+  const size_t o_found = take(b->tiles_all.size() * sizeof(uint32_t));
   for (int e = 0; e < n; ++e) {
     const Model& M = b->models[inst[e].inst];
     const mdpvi::OrbitShape& S = inst[e].S;
@@ -2430,27 +2537,26 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
     o_rep[e] = o_rep[owner];
     o_tab[e] = o_tab[owner];
   }
-  const size_t o_ctl = take(n * sizeof(mdpvi::OrbitCtl));
   std::vector<char> round(n, 0);
   for (auto& L : O.op)
     for (auto& r : L.rounds)
       for (int32_t e : r.entries) round[e] = 1;
-  std::vector<size_t> o_buf[7];   // V0 V1 A0 A1 act load res
+  std::vector<size_t> o_buf[6];   // V0 V1 A0 A1 act res
   for (int e = 0; e < n; ++e) {
     const mdpvi::OrbitShape& S = inst[e].S;
     const size_t v = static_cast<size_t>(S.n) * S.L;
     for (int k = 0; k < 2; ++k) o_buf[k].push_back(take(v * sizeof(double)));
     for (int k = 2; k < 4; ++k) o_buf[k].push_back(take((S.n + 1) * sizeof(double)));
-    for (int k = 4; k < 6; ++k) o_buf[k].push_back(take(v * sizeof(uint32_t)));
-    o_buf[6].push_back(round[e] ? take(static_cast<size_t>(mdpvi::kResSlots) * mdpvi::kOrbitGrid * sizeof(double)) : 0);
+    o_buf[4].push_back(take(v * sizeof(uint32_t)));
+    o_buf[5].push_back(round[e] ? take(static_cast<size_t>(mdpvi::kResSlots) * mdpvi::kOrbitGrid * sizeof(double)) : 0);
   }
   std::vector<size_t> o_act;
   for (auto& L : O.op)
     for (auto& r : L.rounds)
       for (int k = 0; k < 2; ++k) o_act.push_back(take(r.tiles.size() * sizeof(mdpvi::Tile)));
   unsigned char* d = nullptr;
-  if ((!O.h_ctl && !pinned_malloc(&O.h_ctl, n * sizeof(mdpvi::OrbitCtl))) ||
-      (!O.h_words && !pinned_malloc(&O.h_words, 2 * kOrbitWords * sizeof(int))) || !batch_malloc(b, &d, at)) {
+  if ((!O.h_ctl && !pinned_malloc(&O.h_ctl, n * sizeof(mdpvi::OrbitCtl) + 2 * kOrbitWords * sizeof(int))) ||
+      !batch_malloc(b, &d, at)) {
     O.no_memory = true;
     return fail(MDPVI_ENOMEM, "allocation of %zu orbit bytes failed", at);
   }
@@ -2465,9 +2571,9 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
       I.W.A[k] = reinterpret_cast<double*>(d + o_buf[2 + k][e]);
     }
     I.W.act = reinterpret_cast<uint32_t*>(d + o_buf[4][e]);
-    I.W.load = reinterpret_cast<int32_t*>(d + o_buf[5][e]);
-    I.W.res = round[e] ? reinterpret_cast<double*>(d + o_buf[6][e]) : nullptr;
+    I.W.res = round[e] ? reinterpret_cast<double*>(d + o_buf[5][e]) : nullptr;
     I.W.ctl = reinterpret_cast<mdpvi::OrbitCtl*>(d + o_ctl) + e;
+    I.W.found = nullptr;
   }
   std::memcpy(up.data() + o_inst, inst.data(), n * sizeof(mdpvi::OrbitInst));
   O.d_inst = reinterpret_cast<mdpvi::OrbitInst*>(d + o_inst);
@@ -2483,8 +2589,8 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
     (void)hipFree(d);
     return fail_hip(e, "batch orbit plan");
   }
+  O.h_words = reinterpret_cast<int*>(O.h_ctl + n);
   O.d_slot = reinterpret_cast<int32_t*>(d + o_slot);
-  O.d_otiles = reinterpret_cast<mdpvi::Tile*>(d + o_ot);
   O.d_words = reinterpret_cast<int*>(d + o_words);
   O.d_ctl = reinterpret_cast<mdpvi::OrbitCtl*>(d + o_ctl);
   size_t il = 0, ir = 0, ia = 0;
@@ -2496,6 +2602,7 @@ int orbit_batch_ensure(mdpvi_batch* b, hipStream_t s) {
       for (auto& act : r.d_act) act = reinterpret_cast<mdpvi::Tile*>(d + o_act[ia++]);
     }
   }
+  O.d_found = reinterpret_cast<uint32_t*>(d + o_found);
   O.dev = d;
   O.built = true;
   return MDPVI_OK;
@@ -2515,10 +2622,12 @@ bool orbit_batch_applies(const mdpvi_batch* b, int64_t max_iter) {
 // instances with active[i] != 0 (device, nullable: all; h_active its host
 // copy).  done[i] := sweeps and residual of the instances solved; *n_left
 // counts the active ones that were not (refused or not covered), whose V is
-// untouched.
+// untouched; *infeasible (if there are any) := the first instance whose policy
+// has an infeasible action: nothing was solved then.
 template <class Op>
 int orbit_batch_solve(mdpvi_batch* b, const uint8_t* pi, typename Op::T* V, double tol, int64_t max_iter,
-                      hipStream_t s, const int* active, std::vector<mdpvi::BatchOut>& done, int* n_left) {
+                      hipStream_t s, const int* active, std::vector<mdpvi::BatchOut>& done, int* n_left,
+                      int* infeasible) {
   int rc = orbit_batch_ensure(b, s);
   if (rc == MDPVI_ENOMEM) return MDPVI_OK;   // the full forms need none of it
   if (rc) return rc;
@@ -2526,12 +2635,12 @@ int orbit_batch_solve(mdpvi_batch* b, const uint8_t* pi, typename Op::T* V, doub
   const int n = static_cast<int>(O.inst.size()), nt = static_cast<int>(b->tiles_all.size());
   if (n == 0) return MDPVI_OK;
   OrbitBatch::Operation& L = O.op[Op::kEval ? 1 : 0];
-  auto on = [&](int32_t e) { return !active || b->h_active[O.inst[e]]; };
-  int n_round = 0;
-  for (auto& r : L.rounds)
-    for (int32_t e : r.entries) n_round += on(e) ? 1 : 0;
-  HIP_TRY(mdpvi::launch_orbit_batch_begin<Op>(O.d_inst, O.d_slot, O.d_otiles, O.n_otiles, b->d_tiles_all, nt, V, pi,
-                                              active, tol, O.d_words, n_round, s));
+  auto read_ctl = [&]() -> hipError_t {
+    const hipError_t e = hipMemcpyAsync(O.h_ctl, O.d_ctl, n * sizeof(mdpvi::OrbitCtl), hipMemcpyDeviceToHost, s);
+    return e != hipSuccess ? e : hipStreamSynchronize(s);
+  };
+  HIP_TRY(mdpvi::launch_orbit_batch_check<Op>(O.d_inst, n, O.d_slot, b->d_tiles_all, nt, b->d_tile_begin, V, pi, active, tol,
+                                              O.d_found, s));
   int64_t lds_sweeps = 0;
   auto lds = [&]() -> hipError_t {
     const int64_t m = std::min(kOrbitLdsSweeps, max_iter - lds_sweeps);
@@ -2548,29 +2657,63 @@ int orbit_batch_solve(mdpvi_batch* b, const uint8_t* pi, typename Op::T* V, doub
     lds_sweeps += m;
     return e;
   };
-  HIP_TRY(lds());
+  // the check's verdicts before the first round, which refused instances do
+  // not take, and before an evaluation writes any value
+  std::vector<char> on(n), in_round(n, 0);   // solved here; by rounds
+  auto verdicts = [&]() {
+    for (int e = 0; e < n; ++e) {
+      if (Op::kEval && *infeasible < 0 && (O.h_ctl[e].refused & mdpvi::kOrbitNoRoom)) *infeasible = O.inst[e];
+      on[e] = (!active || b->h_active[O.inst[e]]) && !O.h_ctl[e].refused;
+    }
+  };
+  int n_round = 0;
+  if (Op::kEval || !L.rounds.empty()) {
+    HIP_TRY(read_ctl());
+    verdicts();
+    if (*infeasible >= 0 || std::count(on.begin(), on.end(), 1) == 0) return MDPVI_OK;
+    for (auto& r : L.rounds)
+      for (int32_t e : r.entries)
+        if (on[e]) {
+          in_round[e] = 1;
+          ++n_round;
+        }
+  }
+  const bool any_lds = !L.lds.empty();
+  if (any_lds) HIP_TRY(lds());
   int64_t issued = 0;
   if (n_round > 0) {
-    // chunks of rounds; the tiles still running are compacted after each, and
-    // the host reads their counts one chunk late
+    // chunks of rounds; the tiles still running are compacted after each but
+    // the first, and the host reads their counts after the first two, short
+    // ones and one chunk late from then on
     const size_t nr = L.rounds.size();
     std::vector<const mdpvi::Tile*> tiles(nr);
     std::vector<int*> cnt(nr);
     std::vector<int> most(nr);
+    HIP_TRY(mdpvi::launch_orbit_words(O.d_words, n_round, static_cast<int>(L.rounds[0].tiles.size()),
+                                      nr > 1 ? static_cast<int>(L.rounds[1].tiles.size()) : 0, s));
     for (size_t q = 0; q < nr; ++q) {
       tiles[q] = L.rounds[q].d_tiles;
       most[q] = static_cast<int>(L.rounds[q].tiles.size());
       cnt[q] = O.d_words + 1 + 3 * q;
-      HIP_TRY(mdpvi::launch_orbit_set(cnt[q], most[q], s));
+      int kept = 0;
+      for (const mdpvi::Tile& t : L.rounds[q].tiles) kept += on[t.inst];
+      if (kept < most[q]) {
+        int* to = O.d_words + 2 + 3 * q;
+        HIP_TRY(mdpvi::launch_orbit_compact(O.d_inst, tiles[q], cnt[q], most[q], L.rounds[q].d_act[0], to, s));
+        tiles[q] = L.rounds[q].d_act[0];
+        cnt[q] = to;
+        most[q] = kept;
+      }
     }
+    bool running = true;
     for (int k = 0; issued < max_iter; ++k) {
-      const int64_t m = std::min<int64_t>(mdpvi::kOrbitChunk, max_iter - issued);
+      const int64_t m = std::min<int64_t>(k < 2 ? mdpvi::kOrbitFirst << k : mdpvi::kOrbitChunk, max_iter - issued);
       for (int64_t j = issued; j < issued + m; ++j)
         for (size_t q = 0; q < nr; ++q)
           HIP_TRY(mdpvi::launch_orbit_round<Op>(O.d_inst, tiles[q], cnt[q], most[q], L.rounds[q].main_kernel,
                                                 O.d_words, j, s));
       issued += m;
-      for (size_t q = 0; q < nr; ++q) {
+      for (size_t q = 0; q < nr && k > 0; ++q) {
         int* to = O.d_words + 2 + 3 * q + (k & 1);
         HIP_TRY(mdpvi::launch_orbit_compact(O.d_inst, tiles[q], cnt[q], most[q], L.rounds[q].d_act[k & 1], to, s));
         tiles[q] = L.rounds[q].d_act[k & 1];
@@ -2579,35 +2722,32 @@ int orbit_batch_solve(mdpvi_batch* b, const uint8_t* pi, typename Op::T* V, doub
       HIP_TRY(hipMemcpyAsync(O.h_words + (k & 1) * kOrbitWords, O.d_words, kOrbitWords * sizeof(int),
                              hipMemcpyDeviceToHost, s));
       HIP_TRY(hipEventRecord(O.step[k & 1], s));
-      if (k > 0) {
-        HIP_TRY(hipEventSynchronize(O.step[(k - 1) & 1]));
-        const int* h = O.h_words + ((k - 1) & 1) * kOrbitWords;
-        if (h[0] <= 0) break;
-        for (size_t q = 0; q < nr; ++q) most[q] = std::min(most[q], h[2 + 3 * q + ((k - 1) & 1)]);
-      }
+      const int look = k < 2 ? k : k - 1;
+      HIP_TRY(hipEventSynchronize(O.step[look & 1]));
+      const int* h = O.h_words + (look & 1) * kOrbitWords;
+      running = h[0] > 0;
+      if (!running) break;
+      for (size_t q = 0; q < nr && look > 0; ++q) most[q] = std::min(most[q], h[2 + 3 * q + (look & 1)]);
     }
     for (auto& r : L.rounds)
-      HIP_TRY(mdpvi::launch_orbit_batch_residual(O.d_inst, r.dev, static_cast<int>(r.entries.size()), issued, s));
+      if (running)
+        HIP_TRY(mdpvi::launch_orbit_batch_residual(O.d_inst, r.dev, static_cast<int>(r.entries.size()), issued, s));
   }
-  std::vector<char> in_round(n, 0);
-  for (auto& r : L.rounds)
-    for (int32_t e : r.entries) in_round[e] = 1;
   for (;;) {
-    HIP_TRY(hipStreamWaitEvent(s, O.join[0], 0));
-    HIP_TRY(hipStreamWaitEvent(s, O.join[1], 0));
+    for (int k = 0; any_lds && k < 2; ++k) HIP_TRY(hipStreamWaitEvent(s, O.join[k], 0));
     // an LDS-resident instance that has not stopped ran lds_sweeps, a round
     // instance `issued`: both are max_iter when the last pass comes here
     HIP_TRY(mdpvi::launch_orbit_batch_expand<Op>(O.d_inst, O.d_slot, b->d_tiles_all, nt, V,
                                                  lds_sweeps < max_iter ? issued : max_iter, s));
-    HIP_TRY(hipMemcpyAsync(O.h_ctl, O.d_ctl, n * sizeof(mdpvi::OrbitCtl), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(read_ctl());
+    verdicts();
     bool more = false;
-    for (int e = 0; e < n; ++e) more = more || (!in_round[e] && O.h_ctl[e].done < 0 && !O.h_ctl[e].flag);
+    for (int e = 0; e < n; ++e) more = more || (on[e] && !in_round[e] && O.h_ctl[e].done < 0);
     if (!more || lds_sweeps >= max_iter) break;
     HIP_TRY(lds());
   }
   for (int e = 0; e < n; ++e) {
-    if (!on(e) || O.h_ctl[e].flag) continue;
+    if (!on[e]) continue;
     const long long it = O.h_ctl[e].done >= 0 ? O.h_ctl[e].done : max_iter;
     done[O.inst[e]] = {it, O.h_ctl[e].residual};
     --*n_left;
@@ -2719,10 +2859,10 @@ int vi_solve_batch(mdpvi_batch_t b, float* V, double tol, int64_t max_iter, void
   HIP_TRY(hipEventRecord(b->ev0, s));
   std::vector<mdpvi::BatchOut> done(b->n, mdpvi::BatchOut{0, 0.0});
   int n_left = b->n;
-  if (orbit_batch_applies<mdpvi::OrbitVi>(b, max_iter)) {
-    rc = orbit_batch_solve<mdpvi::OrbitVi>(b, nullptr, V, tol, max_iter, s, nullptr, done, &n_left);
-    if (rc) return rc;
-  }
+  int bad = -1;
+  if (orbit_batch_applies<mdpvi::OrbitVi>(b, max_iter) &&
+      (rc = orbit_batch_solve<mdpvi::OrbitVi>(b, nullptr, V, tol, max_iter, s, nullptr, done, &n_left, &bad)))
+    return rc;
   if (n_left > 0) {
     for (int i = 0; i < b->n; ++i) b->h_active[i] = done[i].iterations == 0;
     rc = batch_vi_full(b, V, tol, max_iter, s, n_left < b->n ? b->h_active : nullptr);
@@ -2930,15 +3070,20 @@ int policy_eval_batch(mdpvi_batch_t b, const uint8_t* pi, double* V, double tol,
   if (!b->W2 && !batch_malloc(b, &b->W2, std::max<int64_t>(b->offsets[b->n], 1) * sizeof(double)))
     return fail(MDPVI_ENOMEM, "hipMalloc of the FP64 batch scratch failed");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  // the orbit form's check finds infeasible actions too, in the instances it covers
+  const bool orbits = orbit_batch_applies<mdpvi::OrbitEval>(b, max_iter);
+  if (orbits && (rc = orbit_batch_ensure(b, s)) && rc != MDPVI_ENOMEM) return rc;
   int bad = -1;
-  if ((rc = batch_check_policy(b, pi, s, &bad))) return rc;
-  if (bad >= 0) return fail(MDPVI_EINVAL, "instance %d: policy has an infeasible action", bad);
+  if (!(orbits && b->orbit.built && static_cast<int>(b->orbit.inst.size()) == b->n) &&
+      (rc = batch_check_policy(b, pi, s, &bad)))
+    return rc;
   std::vector<mdpvi::BatchOut> done(b->n, mdpvi::BatchOut{0, 0.0});
   int n_left = b->n;
   HIP_TRY(hipEventRecord(b->ev0, s));
-  if (orbit_batch_applies<mdpvi::OrbitEval>(b, max_iter) &&
-      (rc = orbit_batch_solve<mdpvi::OrbitEval>(b, pi, V, tol, max_iter, s, nullptr, done, &n_left)))
+  if (bad < 0 && orbits && b->orbit.built &&
+      (rc = orbit_batch_solve<mdpvi::OrbitEval>(b, pi, V, tol, max_iter, s, nullptr, done, &n_left, &bad)))
     return rc;
+  if (bad >= 0) return fail(MDPVI_EINVAL, "instance %d: policy has an infeasible action", bad);
   if (n_left < b->n) {
     for (int i = 0; i < b->n; ++i) b->h_active[i] = done[i].iterations == 0;
     HIP_TRY(hipMemcpyAsync(b->d_active[0], b->h_active, b->n * sizeof(int), hipMemcpyHostToDevice, s));
@@ -2995,7 +3140,8 @@ int policy_iteration_batch(mdpvi_batch_t b, uint8_t* pi, double* V, double eval_
     int n_left = n_active;
     HIP_TRY(hipEventRecord(b->ev0, s));
     if (orbit_batch_applies<mdpvi::OrbitEval>(b, eval_max_iter) &&
-        (rc = orbit_batch_solve<mdpvi::OrbitEval>(b, pi, V, eval_tol, eval_max_iter, s, b->d_active[a], done, &n_left)))
+        (rc = orbit_batch_solve<mdpvi::OrbitEval>(b, pi, V, eval_tol, eval_max_iter, s, b->d_active[a], done, &n_left,
+                                                  &bad)))
       break;
     const int* left = b->d_active[a];   // the instances evaluated by full sweeps
     if (n_left < n_active) {

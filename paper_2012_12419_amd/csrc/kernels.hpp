@@ -45,19 +45,22 @@ int slab_digits(const Model& M);
 struct TileShape;
 
 // Orbit form (orbit.hip; Op: OrbitVi or OrbitEval).  launch_orbit_table fills
-// the table behind S; launch_orbit_begin sets the control and residual words
-// and the orbits' start from V (and the policy pi) and raises the flag when
-// V or pi is not invariant under host permutations (mirror: the control
-// words' copy in pinned host memory, written by the kernels); then either
-// sweeps (orbit_grid workgroups; a chunk's sweeps i = 0.. and its end, or a
-// whole chunk recorded as a graph) or LDS-resident solves of up to `most`
-// sweeps each; launch_orbit_expand writes the iterate of ctl->done (or of
-// `issued` sweeps) to every state of V.
+// the table behind S; launch_orbit_check starts a solve: it sets the control
+// and residual words and the orbits' start from V (and the policy pi), it0
+// sweeps (a multiple of kResSlots) having been done, and looks whether V or pi
+// is not invariant under host permutations.  Then either launch_orbit_verdict
+// and, unless refused, sweeps (orbit_grid workgroups; a chunk's sweeps i = 0..
+// and its end, or a whole chunk recorded as a graph), or LDS-resident solves of
+// up to `most` sweeps each; launch_orbit_expand writes the iterate of ctl->done
+// (or of `issued` sweeps) to every state of V.  The latter two do nothing for a
+// refused solve.  mirror: the control words' copy in pinned host memory, written
+// by the sweeps, the LDS-resident solve and launch_orbit_verdict.
 hipError_t launch_orbit_table(const OrbitShape& S, const OrbitParams& P, uint64_t* dig, uint32_t* rep, void* tab,
                               hipStream_t s);
 template <class Op>
-hipError_t launch_orbit_begin(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, const typename Op::T* V,
-                              const uint8_t* pi, double tol, OrbitCtl* mirror, hipStream_t s);
+hipError_t launch_orbit_check(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, const typename Op::T* V,
+                              const uint8_t* pi, double tol, long long it0, hipStream_t s);
+hipError_t launch_orbit_verdict(const OrbitShape& S, const OrbitWork& W, OrbitCtl* mirror, hipStream_t s);
 uint32_t orbit_grid(const OrbitShape& S);
 template <class Op>
 hipError_t launch_orbit_sweep(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, OrbitCtl* mirror, int i,
@@ -79,15 +82,16 @@ template <class Op>
 hipError_t launch_orbit_expand(const OrbitShape& S, const OrbitWork& W, typename Op::T* V, long long issued,
                                hipStream_t s);
 
-// Orbit form of a batch (orbit_batch.hip).  slot: batch instance -> entry of
-// insts or -1; otiles: {entry, first orbit} of 256 orbits each; tiles: the
-// batch's tiles over every instance; active (nullable): instances to solve.
-// main_kernel: every listed instance has K <= 5 and J <= 4.
+// Orbit form of a batch (orbit_batch.hip) of n_inst entries.  slot: batch
+// instance -> entry of insts or -1; tiles: the batch's tiles over every instance,
+// tile_begin its first of each instance; active (nullable): instances to solve;
+// found: a word per tile.  main_kernel: every listed instance has K <= 5 and
+// J <= 4.
 hipError_t launch_orbit_batch_table(const OrbitInst* insts, const Tile* tiles, int n_tiles, hipStream_t s);
 template <class Op>
-hipError_t launch_orbit_batch_begin(const OrbitInst* insts, const int32_t* slot, const Tile* otiles, int n_otiles,
-                                    const Tile* tiles, int n_tiles, const typename Op::T* V, const uint8_t* pi,
-                                    const int* active, double tol, int* remaining, int n_remaining, hipStream_t s);
+hipError_t launch_orbit_batch_check(const OrbitInst* insts, int n_inst, const int32_t* slot, const Tile* tiles,
+                                    int n_tiles, const int32_t* tile_begin, const typename Op::T* V,
+                                    const uint8_t* pi, const int* active, double tol, uint32_t* found, hipStream_t s);
 template <class Op>
 hipError_t launch_orbit_batch_expand(const OrbitInst* insts, const int32_t* slot, const Tile* tiles, int n_tiles,
                                      typename Op::T* V, long long issued, hipStream_t s);
@@ -95,13 +99,13 @@ template <class Op>
 hipError_t launch_orbit_batch_lds(const OrbitInst* insts, const int32_t* list, int n_list, bool main_kernel,
                                   bool small, size_t lds, long long it0, long long most, double tol, hipStream_t s);
 // A round over the first *n_tiles (at most most_tiles) tiles {entry,
-// workgroup of its grid}; the tiles still running after it.
+// workgroup of its grid}; the tiles still running after it (or accepted).
 template <class Op>
 hipError_t launch_orbit_round(const OrbitInst* insts, const Tile* tiles, const int* n_tiles, int most_tiles,
                               bool main_kernel, int* remaining, long long j, hipStream_t s);
 hipError_t launch_orbit_compact(const OrbitInst* insts, const Tile* in, const int* n_in, int most_in, Tile* out,
                                 int* n_out, hipStream_t s);
-hipError_t launch_orbit_set(int* p, int v, hipStream_t s);
+hipError_t launch_orbit_words(int* p, int remaining, int tiles0, int tiles1, hipStream_t s);
 hipError_t launch_orbit_batch_residual(const OrbitInst* insts, const int32_t* list, int n_list, long long issued,
                                        hipStream_t s);
 

@@ -28,40 +28,48 @@ __global__ __launch_bounds__(256) void orbit_table_kernel(OrbitShape S, OrbitPar
 
 // ------------------------------------------------------------ start and end
 
-template <class Op>
-__global__ __launch_bounds__(256) void orbit_begin_kernel(OrbitShape S, OrbitParams P, OrbitWork W,
+// The start of a solve from V after it0 sweeps: control words, the orbits'
+// values, and the check that V (and pi) is invariant.  Each workgroup leaves
+// what it found in a word of its own (raising one shared word, even only after
+// a look at it, took 40 us more for a refused policy of a million states).
+template <class Op, int KX>
+__global__ __launch_bounds__(256) void orbit_check_kernel(OrbitShape S, OrbitParams P, OrbitWork W,
                                                           const typename Op::T* __restrict__ V,
-                                                          const uint8_t* __restrict__ pi, double tol) {
-  const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
+                                                          const uint8_t* __restrict__ pi, double tol, long long it0) {
+  const uint64_t step = static_cast<uint64_t>(gridDim.x) * blockDim.x;
+  const uint64_t first = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   // the slot before the first sweep's holds one word that passes no test
   if (blockIdx.x == 0)
     for (uint32_t w = threadIdx.x; w < kResSlots * kOrbitGrid; w += blockDim.x)
       W.res[w] = w == (kResSlots - 1) * kOrbitGrid ? INFINITY : 0.0;
-  if (r == 0) {
+  if (first == 0) {
     W.ctl->done = -1;
-    W.ctl->flag = 0;
-    W.ctl->bad = 0;
-    W.ctl->base = 0;
+    W.ctl->base = it0;
     W.ctl->tol = tol;
     W.A[0][S.n] = -INFINITY;
     W.A[1][S.n] = -INFINITY;
   }
-  if (r < S.n) orbit_begin<Op>(S, P, W, V, pi, r);
+  uint32_t bits = 0;
+  for (uint64_t o = first; o < S.n_occ; o += step) {
+    if (o < S.n) orbit_begin<Op>(S, P, W, V, pi, static_cast<uint32_t>(o));
+    bits |= orbit_check<Op, KX>(S, P, V, pi, static_cast<uint32_t>(o));
+  }
+  bits = orbit_found(bits);
+  if (threadIdx.x == 0) W.found[blockIdx.x] = bits;
 }
 
-// Every state against its orbit's representative.
-template <class Op, int KX>
-__global__ __launch_bounds__(256) void orbit_check_kernel(OrbitShape S, OrbitParams P, OrbitWork W,
-                                                          const typename Op::T* __restrict__ V,
-                                                          const uint8_t* __restrict__ pi, OrbitCtl* mirror) {
-  __shared__ uint32_t B[kOrbitBinom];
-  orbit_stage_binom(S, B);
-  bool bad = false, infeasible = false;
-  const uint64_t step = static_cast<uint64_t>(gridDim.x) * blockDim.x;
-  for (uint64_t o = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; o < S.n_occ; o += step)
-    bad = orbit_differs<Op, KX>(S, P, W, B, V, pi, static_cast<uint32_t>(o), infeasible) || bad;
-  const bool any = __ballot(bad || infeasible) != 0, inf = __ballot(infeasible) != 0;
-  if (any && threadIdx.x % kWave == 0) orbit_refuse(W.ctl, mirror, inf);
+// The check's verdict from the words of its `grid` workgroups (a whole
+// workgroup calls it): true where it refuses.
+__device__ __forceinline__ bool orbit_refused(const OrbitWork& W, uint32_t grid, OrbitCtl* mirror) {
+  const uint32_t bits = orbit_found(W.found, grid);
+  if (threadIdx.x == 0) {
+    W.ctl->refused = bits;
+    if (bits) mirror->done = bits & kOrbitNoRoom ? kOrbitDoneInfeasible : kOrbitDoneRefused;
+  }
+  return bits != 0;
+}
+__global__ __launch_bounds__(1024) void orbit_verdict_kernel(OrbitWork W, uint32_t grid, OrbitCtl* mirror) {
+  orbit_refused(W, grid, mirror);
 }
 
 // V := the final iterate (ctl->done, or `issued` sweeps when none stopped the
@@ -70,7 +78,7 @@ template <class Op, int KX>
 __global__ __launch_bounds__(256) void orbit_expand_kernel(OrbitShape S, OrbitWork W,
                                                            typename Op::T* __restrict__ V, long long issued) {
   using T = typename Op::T;
-  if (W.ctl->flag) return;
+  if (W.ctl->refused) return;
   const long long done = W.ctl->done;
   const T* Vr = static_cast<const T*>(W.V[(done >= 0 ? done : issued) & 1]);
   __shared__ uint32_t B[kOrbitBinom];
@@ -83,7 +91,7 @@ __global__ __launch_bounds__(256) void orbit_expand_kernel(OrbitShape S, OrbitWo
 // ----------------------------------------------------------------- sweeps
 
 // Sweep i of a chunk (orbit_sweep).  The chunk starts after ctl->base sweeps,
-// a multiple of kOrbitChunk, so that i alone decides the buffers and the
+// a multiple of kResSlots, so that i alone decides the buffers and the
 // residual slot; a small kernel after the chunk moves base on.  A chunk is a
 // recorded graph: issued one by one, the launches are bound by the host (5.3
 // us each at 360 bytes of arguments); a graph node with no work takes 2.0 us,
@@ -94,7 +102,7 @@ __global__ __launch_bounds__(kOrbitBlock) void orbit_sweep_kernel(OrbitShape S, 
                                                                   OrbitCtl* mirror, uint32_t grid, int i) {
   orbit_sweep<Op, K, L, Idx>(S, P, W, i, blockIdx.x, grid, [&](double residual) {
     OrbitCtl* ctl = W.ctl;
-    if (ctl->flag == 0 && ctl->done < 0) {
+    if (ctl->done < 0) {
       ctl->done = ctl->base + i;
       mirror->residual = residual;
       mirror->done = ctl->base + i;
@@ -127,10 +135,10 @@ __global__ __launch_bounds__(256) void orbit_last_residual_kernel(OrbitWork W, u
 // The LDS-resident solve (orbit_lds).
 template <class Op, int K, int L, int HOIST>
 __global__ __launch_bounds__(kOrbitLdsBlock) void orbit_lds_kernel(OrbitShape S, OrbitParams P, OrbitWork W,
-                                                                   OrbitCtl* mirror, long long it0, long long most,
-                                                                   double tol) {
+                                                                   OrbitCtl* mirror, uint32_t check_grid,
+                                                                   long long it0, long long most, double tol) {
   extern __shared__ double orbit_lds_mem[];
-  if (W.ctl->flag || W.ctl->done >= 0) return;
+  if (it0 == 0 ? orbit_refused(W, check_grid, mirror) : W.ctl->done >= 0) return;
   orbit_lds<Op, K, L, HOIST, kOrbitLdsBlock>(S, P, W, it0, most, tol, orbit_lds_mem,
                                              [&](long long it, double residual, bool stopped) {
                                                mirror->residual = residual;
@@ -177,20 +185,24 @@ hipError_t launch_orbit_table(const OrbitShape& S, const OrbitParams& P, uint64_
 
 // Workgroups of a pass over the full state space: enough to fill the chip a
 // few times over, several occupancies per thread beyond that (each workgroup
-// reads the rank table once).
+// of the expansion reads the rank table once).
 static uint32_t full_grid(const OrbitShape& S) {
   const uint64_t g = (S.n_occ + 255) / 256;
-  return static_cast<uint32_t>(g < 8192 ? g : 8192);
+  return static_cast<uint32_t>(g < kOrbitCheckGrid ? g : kOrbitCheckGrid);
 }
 
 template <class Op>
-hipError_t launch_orbit_begin(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, const typename Op::T* V,
-                              const uint8_t* pi, double tol, OrbitCtl* mirror, hipStream_t s) {
-  hipLaunchKernelGGL((orbit_begin_kernel<Op>), dim3((S.n + 255) / 256), dim3(256), 0, s, S, P, W, V, pi, tol);
+hipError_t launch_orbit_check(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W, const typename Op::T* V,
+                              const uint8_t* pi, double tol, long long it0, hipStream_t s) {
 #define MDPVI_CALL(KX_) \
-  hipLaunchKernelGGL((orbit_check_kernel<Op, KX_>), dim3(full_grid(S)), dim3(256), 0, s, S, P, W, V, pi, mirror)
+  hipLaunchKernelGGL((orbit_check_kernel<Op, KX_>), dim3(full_grid(S)), dim3(256), 0, s, S, P, W, V, pi, tol, it0)
   MDPVI_ORBIT_K(S.K, MDPVI_CALL)
 #undef MDPVI_CALL
+  return hipGetLastError();
+}
+
+hipError_t launch_orbit_verdict(const OrbitShape& S, const OrbitWork& W, OrbitCtl* mirror, hipStream_t s) {
+  hipLaunchKernelGGL(orbit_verdict_kernel, dim3(1), dim3(1024), 0, s, W, full_grid(S), mirror);
   return hipGetLastError();
 }
 
@@ -287,7 +299,8 @@ static void lds_h(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W,
   const uint32_t threads = lanes < kOrbitLdsBlock ? (lanes + kWave - 1) / kWave * kWave : kOrbitLdsBlock;
   const size_t lds = orbit_lds_bytes(S, sizeof(typename Op::T));
 #define MDPVI_CALL(H_)                                                                                         \
-  hipLaunchKernelGGL((orbit_lds_kernel<Op, K, L, H_>), dim3(1), dim3(threads), lds, s, S, P, W, mirror, it0, most, tol)
+  hipLaunchKernelGGL((orbit_lds_kernel<Op, K, L, H_>), dim3(1), dim3(threads), lds, s, S, P, W, mirror, full_grid(S), \
+                     it0, most, tol)
   // the table rows of more orbits, or of more hosts, would not fit the 128
   // registers that 16 wavefronts leave a lane
   if (K <= 8 && lanes <= threads) MDPVI_CALL((K <= 8 ? 1 : 0));
@@ -316,16 +329,16 @@ hipError_t launch_orbit_lds(const OrbitShape& S, const OrbitParams& P, const Orb
   return hipGetLastError();
 }
 
-#define MDPVI_ORBIT_OP(OP_)                                                                                         \
-  template hipError_t launch_orbit_begin<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&,              \
-                                              const OP_::T*, const uint8_t*, double, OrbitCtl*, hipStream_t);       \
-  template hipError_t launch_orbit_expand<OP_>(const OrbitShape&, const OrbitWork&, OP_::T*, long long,             \
-                                               hipStream_t);                                                        \
-  template hipError_t launch_orbit_sweep<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&, OrbitCtl*,   \
-                                              int, hipStream_t);                                                    \
-  template hipError_t build_orbit_chunk<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&, OrbitCtl*,    \
-                                             hipGraphExec_t*);                                                      \
-  template hipError_t launch_orbit_lds<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&, OrbitCtl*,     \
+#define MDPVI_ORBIT_OP(OP_)                                                                                       \
+  template hipError_t launch_orbit_check<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&,            \
+                                              const OP_::T*, const uint8_t*, double, long long, hipStream_t);     \
+  template hipError_t launch_orbit_expand<OP_>(const OrbitShape&, const OrbitWork&, OP_::T*, long long,           \
+                                               hipStream_t);                                                      \
+  template hipError_t launch_orbit_sweep<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&, OrbitCtl*, \
+                                              int, hipStream_t);                                                  \
+  template hipError_t build_orbit_chunk<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&, OrbitCtl*,  \
+                                             hipGraphExec_t*);                                                    \
+  template hipError_t launch_orbit_lds<OP_>(const OrbitShape&, const OrbitParams&, const OrbitWork&, OrbitCtl*,   \
                                             long long, long long, double, hipStream_t);
 MDPVI_ORBIT_OP(OrbitVi)
 MDPVI_ORBIT_OP(OrbitEval)

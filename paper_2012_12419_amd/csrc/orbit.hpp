@@ -36,6 +36,7 @@ constexpr uint32_t kOrbitBinom = 2048;         // entries of the rank table (K (
 constexpr int kOrbitBlock = 128;               // threads of a sweep workgroup
 constexpr uint32_t kOrbitGrid = 1024;          // most workgroups of a sweep
 constexpr int kOrbitChunk = 32;                // sweeps of a chunk (a multiple of kResSlots)
+constexpr int kOrbitFirst = 8;                 // ... of a solve's first one (likewise)
 constexpr int kOrbitLdsBlock = 1024;           // most threads of an LDS-resident solve
 constexpr int kOrbitSmallBlock = 256;          // ... of a batch's instances of at most as many lanes
 constexpr int kOrbitBigBlock = 512;            // ... of its larger ones
@@ -51,16 +52,22 @@ struct OrbitEval {
   static constexpr bool kEval = true;
 };
 
+// What the check of a start (and a policy) found, as bits; the host's copy of
+// OrbitCtl::done says it too.
+constexpr uint32_t kOrbitDiffers = 1, kOrbitNoRoom = 2;   // not invariant; an infeasible action
+constexpr long long kOrbitDoneRefused = -2, kOrbitDoneInfeasible = -3;
+constexpr uint32_t kOrbitCheckGrid = 8192;                // most workgroups of the check
+
 // Control words of an orbit solve, in device memory and, as the host's copy,
 // in pinned host memory.
 struct OrbitCtl {
-  long long done;      // -1 while running, else the index of the final iterate
+  long long done;      // -1 while running, else the index of the final iterate; host copy
+                       // also kOrbitDoneRefused or kOrbitDoneInfeasible
   double residual;     // its residual
-  long long flag;      // 1: the start or the policy is not invariant, or an action infeasible
-  long long bad;       // 1: an action is infeasible
   long long base;      // sweeps done before the chunk that runs (device copy)
   double tol;          // the stopping tolerance (device copy)
-  long long pad[10];
+  long long refused;   // the check's bits (device copy)
+  long long pad[11];
 };
 
 struct OrbitShape {
@@ -89,9 +96,9 @@ struct OrbitWork {
   void* V[2];          // iterates [n][L]
   double* A[2];        // their arrival terms [n + 1], the last -inf
   uint32_t* act;       // evaluation [n][L]: rank the arrival leads to, top bit: placed on a host
-  int32_t* load;       // evaluation [n][L]: the policy's target load, -1 the paid cloud
   double* res;         // residual words: kResSlots slots of kOrbitGrid
   OrbitCtl* ctl;
+  uint32_t* found;     // a single instance's check: a workgroup's bits each
 };
 
 // One instance of a batch (orbit_batch.hip).

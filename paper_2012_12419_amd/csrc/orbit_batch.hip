@@ -62,56 +62,6 @@ __global__ __launch_bounds__(256) void orbit_batch_table_kernel(const OrbitInst*
   else orbit_table<16, uint16_t>(S, I.P, B, r, dig, rep, tab);
 }
 
-// The orbits [first, first + 256) of the tile's instance; the first tile
-// also sets the control and residual words.  An instance that is not active
-// counts as stopped before its first sweep.
-template <class Op>
-__global__ __launch_bounds__(256) void orbit_batch_begin_kernel(const OrbitInst* __restrict__ insts,
-                                                                const Tile* __restrict__ tiles,
-                                                                const typename Op::T* __restrict__ V,
-                                                                const uint8_t* __restrict__ pi,
-                                                                const int* __restrict__ active, double tol,
-                                                                int* remaining, int n_remaining) {
-  const Tile t = tiles[blockIdx.x];
-  const OrbitInst& I = insts[t.inst];
-  const OrbitWork W = I.W;
-  const bool on = !active || active[I.inst];
-  if (blockIdx.x == 0 && threadIdx.x == 0) *remaining = n_remaining;
-  if (t.first == 0) {
-    if (W.res) {
-      const uint32_t words = (I.grid + kOrbitBlock - 1) / kOrbitBlock * kOrbitBlock;
-      for (uint32_t w = threadIdx.x; w < words; w += blockDim.x)
-        for (int slot = 0; slot < kResSlots; ++slot)
-          W.res[slot * kOrbitGrid + w] = slot == kResSlots - 1 && w == 0 ? INFINITY : 0.0;
-    }
-    if (threadIdx.x == 0) {
-      W.ctl->done = on ? -1 : 0;
-      W.ctl->residual = 0.0;
-      W.ctl->flag = 0;
-      W.ctl->bad = 0;
-      W.ctl->base = 0;
-      W.ctl->tol = on ? tol : NAN;
-      W.A[0][I.S.n] = -INFINITY;
-      W.A[1][I.S.n] = -INFINITY;
-    }
-  }
-  const uint32_t r = t.first + threadIdx.x;
-  if (on && r < I.S.n) orbit_begin<Op>(I.S, I.P, W, V + I.offset, pi ? pi + I.offset : nullptr, r);
-}
-
-// The occupancies [first, first + kBlock * kOccPerThread) of the tile's
-// instance against their orbits.
-template <class Op, int KX>
-__device__ __forceinline__ bool batch_differs(const OrbitInst& I, const uint32_t* B, const typename Op::T* V,
-                                              const uint8_t* pi, uint32_t first, bool& infeasible) {
-  bool bad = false;
-  for (int k = 0; k < kOccPerThread; ++k) {
-    const uint32_t o = first + threadIdx.x + static_cast<uint32_t>(k * kBlock);
-    if (o < I.S.n_occ) bad = orbit_differs<Op, KX>(I.S, I.P, I.W, B, V, pi, o, infeasible) || bad;
-  }
-  return bad;
-}
-
 #define MDPVI_OB_K(BODY)        \
   switch (I.S.K) {              \
     case 1: BODY(1); break;     \
@@ -125,29 +75,75 @@ __device__ __forceinline__ bool batch_differs(const OrbitInst& I, const uint32_t
     default: BODY(16);          \
   }
 
-// slot: batch instance -> its entry in insts, -1 for one the form does not
-// cover (the tiles are the batch's own, over every instance).
+template <class Op, int KX>
+__device__ __forceinline__ uint32_t batch_check(const OrbitInst& I, const typename Op::T* V, const uint8_t* pi,
+                                                uint32_t first) {
+  uint32_t bits = 0;
+  for (int k = 0; k < kOccPerThread; ++k) {
+    const uint32_t o = first + threadIdx.x + static_cast<uint32_t>(k * kBlock);
+    if (o >= I.S.n_occ) break;
+    if (o < I.S.n) orbit_begin<Op>(I.S, I.P, I.W, V, pi, o);
+    bits |= orbit_check<Op, KX>(I.S, I.P, V, pi, o);
+  }
+  return bits;
+}
+
+// The start of a solve of the tile's instance (orbit_check_kernel): the
+// occupancies, and the orbits of the same numbers, [first, first + kBlock *
+// kOccPerThread); what the tile found into its word.  slot: batch instance ->
+// its entry in insts, -1 for one the form does not cover (the tiles are the
+// batch's own, over every instance).  An instance that is not active counts as
+// stopped before its first sweep.
 template <class Op>
 __global__ __launch_bounds__(kBlock) void orbit_batch_check_kernel(const OrbitInst* __restrict__ insts,
                                                                    const int32_t* __restrict__ slot,
                                                                    const Tile* __restrict__ tiles,
                                                                    const typename Op::T* __restrict__ V,
-                                                                   const uint8_t* __restrict__ pi) {
-  __shared__ uint32_t B[kOrbitBinom];
+                                                                   const uint8_t* __restrict__ pi,
+                                                                   const int* __restrict__ active, double tol,
+                                                                   uint32_t* __restrict__ found) {
   const Tile t = tiles[blockIdx.x];
   const int at = slot[t.inst];
   if (at < 0) return;
   const OrbitInst& I = insts[at];
-  if (I.W.ctl->done >= 0) return;   // not active
-  orbit_stage_binom(I.S, B);
-  const typename Op::T* Vi = V + I.offset;
-  const uint8_t* p = pi ? pi + I.offset : nullptr;
-  bool bad = false, infeasible = false;
-#define MDPVI_BODY(KX_) bad = batch_differs<Op, KX_>(I, B, Vi, p, t.first, infeasible)
-  MDPVI_OB_K(MDPVI_BODY)
+  const bool on = !active || active[t.inst];
+  if (t.first == 0) {
+    const OrbitWork W = I.W;
+    if (W.res) {
+      const uint32_t words = (I.grid + kOrbitBlock - 1) / kOrbitBlock * kOrbitBlock;
+      for (uint32_t w = threadIdx.x; w < words; w += blockDim.x)
+        for (int q = 0; q < kResSlots; ++q)
+          W.res[q * kOrbitGrid + w] = q == kResSlots - 1 && w == 0 ? INFINITY : 0.0;
+    }
+    if (threadIdx.x == 0) {
+      W.ctl->done = on ? -1 : 0;
+      W.ctl->residual = 0.0;
+      W.ctl->base = 0;
+      W.ctl->tol = tol;
+      W.A[0][I.S.n] = -INFINITY;
+      W.A[1][I.S.n] = -INFINITY;
+    }
+  }
+  uint32_t bits = 0;
+  if (on) {
+    const typename Op::T* Vi = V + I.offset;
+    const uint8_t* p = pi ? pi + I.offset : nullptr;
+#define MDPVI_BODY(KX_) bits = batch_check<Op, KX_>(I, Vi, p, t.first)
+    MDPVI_OB_K(MDPVI_BODY)
 #undef MDPVI_BODY
-  const bool any = __ballot(bad || infeasible) != 0, inf = __ballot(infeasible) != 0;
-  if (any && threadIdx.x % kWave == 0) orbit_refuse(I.W.ctl, nullptr, inf);
+  }
+  bits = orbit_found(bits);
+  if (threadIdx.x == 0) found[blockIdx.x] = bits;
+}
+
+// An entry's verdict from its tiles' words.
+__global__ __launch_bounds__(256) void orbit_batch_verdict_kernel(const OrbitInst* __restrict__ insts,
+                                                                  const int32_t* __restrict__ tile_begin,
+                                                                  const uint32_t* __restrict__ found) {
+  const OrbitInst& I = insts[blockIdx.x];
+  const int32_t first = tile_begin[I.inst], last = tile_begin[I.inst + 1];
+  const uint32_t bits = orbit_found(found + first, static_cast<uint32_t>(last - first));
+  if (threadIdx.x == 0) I.W.ctl->refused = bits;
 }
 
 template <class T, int KX>
@@ -174,7 +170,7 @@ __global__ __launch_bounds__(kBlock) void orbit_batch_expand_kernel(const OrbitI
   if (at < 0) return;
   const OrbitInst& I = insts[at];
   const long long done = I.W.ctl->done;
-  if (I.W.ctl->flag || done == 0) return;
+  if (I.W.ctl->refused || done == 0) return;
   orbit_stage_binom(I.S, B);
   const T* Vr = static_cast<const T*>(I.W.V[(done > 0 ? done : issued) & 1]);
   T* Vi = V + I.offset;
@@ -191,7 +187,7 @@ __global__ __launch_bounds__(NB) void orbit_batch_lds_kernel(const OrbitInst* __
   extern __shared__ double orbit_batch_mem[];
   const OrbitInst& I = insts[__builtin_amdgcn_readfirstlane(list[blockIdx.x])];
   OrbitCtl* ctl = I.W.ctl;
-  if (ctl->flag || ctl->done >= 0) return;
+  if (ctl->refused || ctl->done >= 0) return;
   const OrbitShape S = I.S;
   const OrbitParams P = I.P;
   const OrbitWork W = I.W;
@@ -229,8 +225,8 @@ __global__ __launch_bounds__(kOrbitBlock) void orbit_round_kernel(const OrbitIns
 #undef MDPVI_BODY
 }
 
-// The tiles whose instance has not stopped, into out; their count into
-// *n_out (cleared by the caller).
+// The tiles whose instance was not refused and has not stopped, into out;
+// their count into *n_out (cleared by the caller).
 __global__ __launch_bounds__(256) void orbit_compact_kernel(const OrbitInst* __restrict__ insts,
                                                             const Tile* __restrict__ in,
                                                             const int* __restrict__ n_in, Tile* __restrict__ out,
@@ -240,7 +236,8 @@ __global__ __launch_bounds__(256) void orbit_compact_kernel(const OrbitInst* __r
   bool keep = false;
   if (t < *n_in) {
     tile = in[t];
-    keep = insts[tile.inst].W.ctl->done < 0;
+    const OrbitCtl* ctl = insts[tile.inst].W.ctl;
+    keep = ctl->done < 0 && !ctl->refused;
   }
   const unsigned long long mask = __ballot(keep);
   const int lane = threadIdx.x % kWave;
@@ -253,13 +250,20 @@ __global__ __launch_bounds__(256) void orbit_compact_kernel(const OrbitInst* __r
 
 __global__ void orbit_set_kernel(int* p, int v) { *p = v; }
 
+// The words of a solve's rounds: instances running, tiles of either list.
+__global__ void orbit_words_kernel(int* p, int remaining, int tiles0, int tiles1) {
+  p[0] = remaining;
+  p[1] = tiles0;
+  p[4] = tiles1;
+}
+
 // The residual of the last of `issued` sweeps of a round instance that has
 // not stopped.
 __global__ __launch_bounds__(256) void orbit_batch_residual_kernel(const OrbitInst* __restrict__ insts,
                                                                    const int32_t* __restrict__ list,
                                                                    long long issued) {
   const OrbitInst& I = insts[list[blockIdx.x]];
-  if (I.W.ctl->done >= 0) return;
+  if (I.W.ctl->done >= 0 || I.W.ctl->refused) return;
   __shared__ double part[256 / kWave];
   const double* w = I.W.res + static_cast<size_t>((issued - 1) % kResSlots) * kOrbitGrid;
   double m = 0.0;
@@ -284,12 +288,12 @@ hipError_t launch_orbit_batch_table(const OrbitInst* insts, const Tile* tiles, i
 }
 
 template <class Op>
-hipError_t launch_orbit_batch_begin(const OrbitInst* insts, const int32_t* slot, const Tile* otiles, int n_otiles,
-                                    const Tile* tiles, int n_tiles, const typename Op::T* V, const uint8_t* pi,
-                                    const int* active, double tol, int* remaining, int n_remaining, hipStream_t s) {
-  hipLaunchKernelGGL((orbit_batch_begin_kernel<Op>), dim3(n_otiles), dim3(256), 0, s, insts, otiles, V, pi, active,
-                     tol, remaining, n_remaining);
-  hipLaunchKernelGGL((orbit_batch_check_kernel<Op>), dim3(n_tiles), dim3(kBlock), 0, s, insts, slot, tiles, V, pi);
+hipError_t launch_orbit_batch_check(const OrbitInst* insts, int n_inst, const int32_t* slot, const Tile* tiles,
+                                    int n_tiles, const int32_t* tile_begin, const typename Op::T* V,
+                                    const uint8_t* pi, const int* active, double tol, uint32_t* found, hipStream_t s) {
+  hipLaunchKernelGGL((orbit_batch_check_kernel<Op>), dim3(n_tiles), dim3(kBlock), 0, s, insts, slot, tiles, V, pi,
+                     active, tol, found);
+  hipLaunchKernelGGL(orbit_batch_verdict_kernel, dim3(n_inst), dim3(256), 0, s, insts, tile_begin, found);
   return hipGetLastError();
 }
 
@@ -341,8 +345,8 @@ hipError_t launch_orbit_compact(const OrbitInst* insts, const Tile* in, const in
   return hipGetLastError();
 }
 
-hipError_t launch_orbit_set(int* p, int v, hipStream_t s) {
-  hipLaunchKernelGGL(orbit_set_kernel, dim3(1), dim3(1), 0, s, p, v);
+hipError_t launch_orbit_words(int* p, int remaining, int tiles0, int tiles1, hipStream_t s) {
+  hipLaunchKernelGGL(orbit_words_kernel, dim3(1), dim3(1), 0, s, p, remaining, tiles0, tiles1);
   return hipGetLastError();
 }
 
@@ -353,14 +357,14 @@ hipError_t launch_orbit_batch_residual(const OrbitInst* insts, const int32_t* li
   return hipGetLastError();
 }
 
-#define MDPVI_ORBIT_OP(OP_)                                                                                         \
-  template hipError_t launch_orbit_batch_begin<OP_>(const OrbitInst*, const int32_t*, const Tile*, int, const Tile*, \
-                                                    int, const OP_::T*, const uint8_t*, const int*, double, int*,   \
-                                                    int, hipStream_t);                                              \
-  template hipError_t launch_orbit_batch_expand<OP_>(const OrbitInst*, const int32_t*, const Tile*, int, OP_::T*,   \
-                                                     long long, hipStream_t);                                       \
-  template hipError_t launch_orbit_batch_lds<OP_>(const OrbitInst*, const int32_t*, int, bool, bool, size_t,        \
-                                                  long long, long long, double, hipStream_t);                       \
+#define MDPVI_ORBIT_OP(OP_)                                                                                          \
+  template hipError_t launch_orbit_batch_check<OP_>(const OrbitInst*, int, const int32_t*, const Tile*, int,         \
+                                                    const int32_t*, const OP_::T*, const uint8_t*, const int*,       \
+                                                    double, uint32_t*, hipStream_t);                                 \
+  template hipError_t launch_orbit_batch_expand<OP_>(const OrbitInst*, const int32_t*, const Tile*, int, OP_::T*,    \
+                                                     long long, hipStream_t);                                        \
+  template hipError_t launch_orbit_batch_lds<OP_>(const OrbitInst*, const int32_t*, int, bool, bool, size_t,         \
+                                                  long long, long long, double, hipStream_t);                        \
   template hipError_t launch_orbit_round<OP_>(const OrbitInst*, const Tile*, const int*, int, bool, int*, long long, \
                                               hipStream_t);
 MDPVI_ORBIT_OP(OrbitVi)

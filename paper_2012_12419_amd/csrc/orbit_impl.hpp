@@ -83,9 +83,8 @@ __device__ __forceinline__ void orbit_table(const OrbitShape& S, const OrbitPara
 }
 
 // Orbit r's start: its representative's values and their arrival term; for
-// an evaluation also the orbit its policy's arrival leads to and the target
-// load.  (An infeasible action, which the check reports, reads as the paid
-// cloud here.)
+// an evaluation also the orbit its policy's arrival leads to.  (An infeasible
+// action, which the check reports, reads as the paid cloud here.)
 template <class Op>
 __device__ __forceinline__ void orbit_begin(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W,
                                             const typename Op::T* __restrict__ V, const uint8_t* __restrict__ pi,
@@ -102,71 +101,84 @@ __device__ __forceinline__ void orbit_begin(const OrbitShape& S, const OrbitPara
     if (e < S.J) a = fma(P.p[e], static_cast<double>(v), a);
     if constexpr (Op::kEval) {
       uint32_t act = r;
-      int load = -1;
       const int x = e < S.J ? pi[s] : S.K;
       if (x < S.K) {
         const size_t w = static_cast<size_t>((2 + e) * S.K + x) * S.n + r;
         const uint32_t t = S.wide ? static_cast<const uint32_t*>(S.tab)[w] : static_cast<const uint16_t*>(S.tab)[w];
-        if (t != S.n) {
-          act = t | 0x80000000u;
-          load = static_cast<int>((S.dig[r] >> (S.dig_bits * x)) & ((1u << S.dig_bits) - 1u));
-        }
+        if (t != S.n) act = t | 0x80000000u;
       }
       W.act[at] = act;
-      W.load[at] = load;
     }
   }
   W.A[0][r] = a;
 }
 
-// Occupancy o against its orbit: the start (value iteration's bit for bit) and
-// an evaluation's target load; `infeasible` for an action without room.
-template <class Op, int KX>
-__device__ __forceinline__ bool orbit_differs(const OrbitShape& S, const OrbitParams& P, const OrbitWork& W,
-                                              const uint32_t* B, const typename Op::T* __restrict__ V,
-                                              const uint8_t* __restrict__ pi, uint32_t o,
-                                              bool& infeasible) {
-  using T = typename Op::T;
-  const T* Vr = static_cast<const T*>(W.V[0]);
-  int n[KX], d[KX];
-  orbit_digits<KX>(S, o, n);
+// n[x] for a host x, -1 for any other action.
+template <int KX>
+__device__ __forceinline__ int orbit_load(const OrbitShape& S, const int (&n)[KX], int x) {
+  int load = -1;
 #pragma unroll
-  for (int k = 0; k < KX; ++k) d[k] = n[k];
-  const uint32_t r = orbit_rank<KX>(S, B, n);
-  bool bad = false;
-  for (int e = 0; e < S.J; ++e) {
-    const uint64_t s = o + static_cast<uint64_t>(e) * S.n_occ;
-    const uint32_t at = r * static_cast<uint32_t>(S.L) + e;
-    if constexpr (Op::kEval) {
-      const int x = pi[s];
-      int load = -1;
-#pragma unroll
-      for (int k = 0; k < KX; ++k) load = (KX <= 8 || k < S.K) && k == x ? d[k] : load;
-      if (x > S.K || (x < S.K && load + P.size[e] > S.C)) infeasible = true;
-      bad = bad || load != W.load[at] || V[s] != Vr[at];
-    } else {
-      bad = bad || __float_as_uint(V[s]) != __float_as_uint(Vr[at]);
-    }
-  }
-  return bad;
+  for (int k = 0; k < KX; ++k) load = (KX <= 8 || k < S.K) && k == x ? n[k] : load;
+  return load;
 }
 
-// Raises the control words of a refused start or policy (one lane of a
-// wavefront, after reading them still clear: a word sees few stores).
-__device__ __forceinline__ void orbit_refuse(OrbitCtl* ctl, OrbitCtl* mirror, bool infeasible) {
-  if (infeasible) {
-    volatile long long* b = &ctl->bad;
-    if (*b == 0) {
-      *b = 1;
-      if (mirror) mirror->bad = 1;
+// The start (value iteration's bit for bit) and an evaluation's target load of
+// occupancy o, every class, against those of the occupancy with the first two
+// neighbouring digits out of order exchanged: where all agree, each occupancy
+// agrees with its orbit's representative, which has none (and mostly the two
+// are near each other in memory).  Also the actions' room.  The bits found.
+template <class Op, int KX>
+__device__ __forceinline__ uint32_t orbit_check(const OrbitShape& S, const OrbitParams& P,
+                                                const typename Op::T* __restrict__ V, const uint8_t* __restrict__ pi,
+                                                uint32_t o) {
+  int n[KX];
+  orbit_digits<KX>(S, o, n);
+  int at = -1, lo = 0, hi = 0;   // the place, and the digits there and behind it
+  uint32_t stride = 1, other = o;
+#pragma unroll
+  for (int k = 0; k < KX - 1; ++k) {
+    if ((KX <= 8 || k < S.K - 1) && at < 0 && n[k] > n[k + 1]) {
+      at = k;
+      lo = n[k];
+      hi = n[k + 1];
+      other = o + static_cast<uint32_t>(lo - hi) * stride * static_cast<uint32_t>(S.R - 1);
+    }
+    stride *= static_cast<uint32_t>(S.R);
+  }
+  bool differs = false, infeasible = false;
+  for (int e = 0; e < S.J; ++e) {
+    const uint64_t cls = static_cast<uint64_t>(e) * S.n_occ;
+    if constexpr (Op::kEval) {
+      const int x = pi[o + cls], load = orbit_load<KX>(S, n, x);
+      infeasible = infeasible || x > S.K || (x < S.K && load + P.size[e] > S.C);
+      if (at >= 0) {
+        const int y = pi[other + cls];
+        const int there = y == at ? hi : y == at + 1 ? lo : orbit_load<KX>(S, n, y);
+        differs = differs || load != there || V[o + cls] != V[other + cls];
+      }
+    } else {
+      differs = differs || (at >= 0 && __float_as_uint(V[o + cls]) != __float_as_uint(V[other + cls]));
     }
   }
-  volatile long long* f = &ctl->flag;
-  if (*f == 0) {
-    *f = 1;
-    ctl->tol = NAN;   // no residual is >= NaN: every sweep stops
-    if (mirror) mirror->flag = 1;
-  }
+  return (differs || infeasible ? kOrbitDiffers : 0u) | (infeasible ? kOrbitNoRoom : 0u);
+}
+
+// The bits of all threads of the workgroup (every thread calls it).
+__device__ __forceinline__ uint32_t orbit_found(uint32_t bits) {
+  __shared__ uint32_t all;
+  if (threadIdx.x == 0) all = 0;
+  __syncthreads();
+  const uint32_t wave = (__ballot(bits & kOrbitDiffers) ? kOrbitDiffers : 0u) | (__ballot(bits & kOrbitNoRoom) ? kOrbitNoRoom : 0u);
+  if (wave && threadIdx.x % kWave == 0) atomicOr(&all, wave);
+  __syncthreads();
+  return all;
+}
+
+// The bits of n workgroups' words.
+__device__ __forceinline__ uint32_t orbit_found(const uint32_t* words, uint32_t n) {
+  uint32_t bits = 0;
+  for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) bits |= words[i];
+  return orbit_found(bits);
 }
 
 // Every class of occupancy o := its orbit's value.

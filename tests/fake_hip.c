@@ -2,7 +2,7 @@
  * library's host code: "device" memory is host memory filled with 0xff, kernels
  * are named in a log instead of run, and allocations and copies fail on demand.
  * Of the kernels it imitates the clearing of a handle's control words and,
- * when asked, the orbit check's refusal. */
+ * when asked, the orbit form's refusal. */
 #include <stddef.h>
 #include <stdint.h>
 #include <stdio.h>
@@ -94,20 +94,24 @@ int hipMemcpy2DAsync(void* d, size_t dp, const void* s, size_t sp, size_t w, siz
 }
 int hipMemsetAsync(void* d, int v, size_t n, void* q) { (void)q; memset(d, v, n); return OK; }
 
+static void note(const char* name) {
+  int w = snprintf(log_ + log_len, sizeof log_ - log_len, "%s\n", name);
+  if (w > 0 && log_len + w < sizeof log_) log_len += w;
+}
 static void launched(const void* fn, void** args) {
   for (int i = 0; i < n_kernels; ++i) {
     if (kernels[i].fn != fn) continue;
     const char* name = kernels[i].name;
-    int w = snprintf(log_ + log_len, sizeof log_ - log_len, "%s\n", name);
-    if (w > 0 && log_len + w < sizeof log_) log_len += w;
+    note(name);
     last_arg0[i] = args ? *(void**)args[0] : NULL;
     if (strstr(name, "mdpvi15ctl_init_kernel")) {   /* done_iter, flag */
       int64_t* ctl = *(int64_t**)args[0];
       ctl[0] = -1;
       ctl[1] = 0;
-    } else if (refuse && strstr(name, "orbit_check_kernel") && !strstr(name, "batch")) {
-      int64_t* mirror = *(int64_t**)args[5];        /* done, residual, flag */
-      mirror[2] = 1;
+    } else if (refuse && strstr(name, "orbit_verdict_kernel")) {
+      **(int64_t**)args[2] = -2;                      /* OrbitCtl::done of the host's copy: refused */
+    } else if (refuse && strstr(name, "orbit_lds_kernel")) {
+      **(int64_t**)args[3] = -2;
     }
     return;
   }
@@ -170,6 +174,14 @@ int hipGraphAddKernelNode(void** n, void* g, const void* const* d, size_t nd, co
   *n = NULL;
   return OK;
 }
-int hipGraphInstantiate(void** x, void* g, void** n, char* l, size_t s) { (void)g, (void)n, (void)l, (void)s; return handle(x); }
-int hipGraphLaunch(void* x, void* s) { (void)x, (void)s; return OK; }
+int hipGraphInstantiate(void** x, void* g, void** n, char* l, size_t s) {
+  (void)g, (void)n, (void)l, (void)s;
+  note("hipGraphInstantiate");
+  return handle(x);
+}
+int hipGraphLaunch(void* x, void* s) {
+  (void)x, (void)s;
+  note("hipGraphLaunch");
+  return OK;
+}
 int hipGraphExecDestroy(void* x) { return unhandle(x); }
