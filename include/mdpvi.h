@@ -486,8 +486,8 @@ int mdp_set_orbits(mdpvi_mdp_t h, int32_t on);
 
 /* Choice of the adjoint sweep kernels for this handle (a tuning knob: every
  * form gives bit-identical w and gradients).  0: automatic (the default);
- * MDPVI_ADJOINT_GROUP: the group form (each workgroup takes whole groups of
- * the (C+1)^2 occupancies that share digits 2..K-1, one occupancy per lane;
+ * MDPVI_ADJOINT_GROUP: the group form (each workgroup takes one group of the
+ * (C+1)^2 occupancies that share digits 2..K-1, a lane per state;
  * neighbours along digits 0 and 1, including the reset line sums of the
  * transposed backup of Eq. (18), are read from LDS; K in 3..8, J <= 3,
  * C <= 15, fewer than 2^29 states); 16 + OPT or OPT as for mdp_adjoint_form.

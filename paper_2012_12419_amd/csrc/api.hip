@@ -611,13 +611,17 @@ std::vector<uint32_t> orbit_binom(const mdpvi::OrbitShape& S) {
   return b;
 }
 
-// Whether the solve fits one workgroup and is faster there than with a
-// launch per sweep.  One workgroup's sweep costs 0.5 us and then, bound by
-// its LDS reads, about 63 ps per lane and 4-byte read (value iteration: 3K +
-// 2): 0.66 us at K = 3, C = 8, J = 2 (330 lanes), 1.6 us at K = 5, C = 6, J = 3
-// (1,848), 6.8 us at K = 5, C = 10, J = 2 (6,006).  A launched sweep takes
-// 3.4-3.7 us up to tens of thousands of lanes, and the first solve of a
-// handle pays for recording the chunk.  The line lies where the two meet.
+// Whether the solve fits one workgroup and takes no longer there than with a
+// launch per sweep.  Sweeps in LDS against launched ones, us (the difference of
+// the times of solves of 600 and 200 sweeps over 400), by lanes times
+// 4-byte reads per lane (value iteration 3K + 2): 0.52 and 3.0 at K = 3, C = 8,
+// J = 2 (3,630), 1.55 and 3.5 at K = 5, C = 6, J = 3 (31,416), 3.2 and 3.5 at
+// K = 7, C = 6, J = 1 (39,468), 4.1 and 3.6 at K = 8, C = 4, J = 4 (51,480), 5.4
+// and 3.4 at K = 4, C = 17, J = 1 (83,790); evaluation (4K + 4 reads) 1.15 and
+// 3.3 at K = 5, C = 6, J = 3 (44,352), 2.5 and 3.2 at K = 3, C = 20, J = 2
+// (56,672).  A launched solve has 0.1 to 0.2 ms of its own (waits, the first 24
+// sweeps in full, the recording): at the line a few hundred sweeps take as
+// long either way.
 template <class Op>
 bool orbit_in_lds(const mdpvi::OrbitShape& S) {
   const uint64_t reads = Op::kEval ? 2 * (2 * S.K + 2) : 3 * S.K + 2;
@@ -636,8 +640,10 @@ bool orbit_allowed(const mdpvi_mdp* h) {
 }
 
 // Whether a solve tries the form.  Launched sweeps need at least four times
-// fewer orbits than occupancies (K = 2 has two: its full sweep is as fast);
-// a handful of sweeps does not pay for the check and the expansion.
+// fewer orbits than occupancies (K = 2 has two: its full sweep is as fast); at
+// the most orbits and the least gain, K = 3, C = 180, J = 1 (988,260 orbits of
+// 5.9 million states), they take 21 us against 41 in full.  A handful of sweeps
+// does not pay for the check and the expansion.
 template <class Op>
 bool orbit_applies(mdpvi_mdp* h, int64_t max_iter) {
   OrbitPlan& O = h->orbit;

@@ -7,8 +7,8 @@
 // 5,314,683-state instance, whose values, policy and gaps are 48 MB.  Here a
 // workgroup stages one tile of (C+1)^T occupancies and their arrival terms in
 // LDS; neighbours along the T low digits are LDS reads, neighbours along a high
-// digit are loads at the lane's own offset plus a workgroup-uniform one: 46 us
-// for that instance (FP64 values 137 -> 65 us), by then the FP64 units' and
+// digit are loads at the lane's own offset plus a workgroup-uniform one: 42 us
+// for that instance (FP64 values 137 -> 62 us), by then the FP64 units' and
 // the remaining 48 loads' time.  One occupancy per lane: 2 and 4 consecutive
 // ones with 8- and 16-byte loads took 130 to 211 registers and 61 and 91 us;
 // the classes in a loop, since unrolled they took 54 us; workgroups of 256

@@ -4,11 +4,12 @@
 // one workgroup's LDS) and the expansion to the full state space.
 //
 // Measured against the full sweeps of the same solve.  Value iteration to
-// ||dV|| < 1e-6, wall time: K = 6, C = 10, J = 3 47.5 -> 5.7 ms (31 -> 3.6 us
-// per sweep); K = 7 565 -> 7.2 ms (408 -> 4.5 us); K = 4, C = 12, J = 3 2.7 ->
-// 1.7 ms; in LDS K = 3, C = 8, J = 2 1.80 -> 0.17 ms (0.63 us per sweep).
+// ||dV|| < 1e-6, wall time: K = 6, C = 10, J = 3 43 -> 5.4 ms (31 -> 3.4 us per
+// sweep); K = 7 530 -> 7.6 ms (392 -> 4.8 us); K = 4, C = 12, J = 3 2.75 -> 1.86
+// ms; in LDS K = 3, C = 8, J = 2 2.28 -> 0.17 ms (0.42 us per sweep in the
+// kernel's own time).
 // Evaluation of the least-loaded heuristic to 1e-10: K = 6, C = 10, J = 3 94 ->
-// 8.2 ms (43 -> 3.6 us per sweep); in LDS K = 3, C = 8, J = 2 2.4 -> 0.24 ms.
+// 8.3 ms (42 -> 3.5 us per sweep); in LDS K = 3, C = 8, J = 2 2.35 -> 0.20 ms.
 #include "kernels.hpp"
 #include "orbit.hpp"
 #include "orbit_impl.hpp"
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(256) void orbit_expand_kernel(OrbitShape S, OrbitWo
 // a multiple of kResSlots, so that i alone decides the buffers and the
 // residual slot; a small kernel after the chunk moves base on.  A chunk is a
 // recorded graph: issued one by one, the launches are bound by the host (5.3
-// us each at 360 bytes of arguments); a graph node with no work takes 2.0 us,
+// us each at 360 bytes of arguments); a graph node with no work takes 1.8 us,
 // the table rows 0.85, values and backup 0.7, the verdict and the residual
 // 0.2 (K = 6, C = 10, J = 3).
 template <class Op, int K, int L, typename Idx>
@@ -132,7 +133,8 @@ __global__ __launch_bounds__(256) void orbit_last_residual_kernel(OrbitWork W, u
   }
 }
 
-// The LDS-resident solve (orbit_lds).
+// The LDS-resident solve (orbit_lds).  HIP on this GPU takes a launch's dynamic
+// LDS up to the CU's 160 KB, without the attribute that raises a limit.
 template <class Op, int K, int L, int HOIST>
 __global__ __launch_bounds__(kOrbitLdsBlock) void orbit_lds_kernel(OrbitShape S, OrbitParams P, OrbitWork W,
                                                                    OrbitCtl* mirror, uint32_t check_grid,

@@ -5,7 +5,7 @@
 // sweeps; the larger ones advance one sweep per launch over all of them
 // (rounds), concurrently on another stream.  The workgroup bodies are the
 // single-instance kernels', so an instance gets the same bits either way.
-// The 512-instance sweep's value iteration: 67.6 -> 8.8 ms against the full
+// The 512-instance sweep's value iteration: 66.6 -> 8.4 ms against the full
 // sweeps.
 //
 // Kernels carry the bodies of K <= 5 and J <= 4 (MAIN) or all the others: an

@@ -165,8 +165,8 @@ __global__ __launch_bounds__(kWave* kStaticWaves) void static_score_kernel(
 // 64 scenarios by up to 64 tasks, so that global memory is read and written a
 // row (one scenario) at a time.  Rows of 65 words: lane l's task i lies in bank
 // l + i.  A million such scenarios take 207 us and their scoring 183 us, bound by
-// the 5 vector instructions per VC and task (2.25 wavefronts per SIMD, as many
-// as the LDS holds); taking the first match with masks of the wavefront instead
+// the 5 vector instructions per VC and task (two wavefronts per SIMD, as many
+// as the LDS holds at 12 VCs); taking the first match with masks of the wavefront instead
 // (4 vector instructions, but a chain of scalar ones) took 214 us.
 
 constexpr int kLaneTasks = 64;
